@@ -15,6 +15,7 @@ LIB = os.path.join(HERE, "libfg.so")
 SOURCES = [
     "fg_quant.hip",
     "fg_norm.hip",
+    "fg_gemm_fewrows.hip",
     "fg_gemm_small_m.hip",
     "fg_gemm_large_m.hip",
     "fg_gemm_stream.hip",

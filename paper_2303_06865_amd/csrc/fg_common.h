@@ -76,6 +76,9 @@ struct LinearArgs {
 size_t linear_workspace_bytes(int dtype, int64_t n, int64_t k, int64_t m);
 int linear_launch(const LinearArgs& a, void* ws, size_t ws_bytes, hipStream_t stream);
 
+// a few rows, any weight format (csrc/fg_gemm_fewrows.hip); needs no workspace
+bool gemm_fewrows_takes(int dtype, int64_t n, int64_t k, int64_t m);
+int gemm_fewrows_launch(const LinearArgs& a, hipStream_t stream);
 // small-M (decode) and large-M (prefill) kernels behind linear_launch
 size_t gemm_small_m_workspace(int dtype, int64_t n, int64_t k, int64_t m);
 int gemm_small_m_launch(const LinearArgs& a, void* ws, size_t ws_bytes, hipStream_t stream);
@@ -83,6 +86,7 @@ int gemm_large_m_launch(const LinearArgs& a, hipStream_t stream);
 // tiled 4-bit weights: weight-streaming kernel for few rows, and the repacking kernel
 // row-major FP16 weights, up to 128 rows (csrc/fg_gemm_f16w.hip); pick_cols returns 0 for shapes it does not take
 int gemm_f16w_pick_cols(int64_t n, int64_t k, int64_t m);
+int gemm_f16w_forced(int64_t n);   // column tiles fixed by the environment, or 0
 size_t gemm_f16w_workspace(int64_t n, int64_t k, int64_t m);
 int gemm_f16w_launch(const LinearArgs& a, void* ws, size_t ws_bytes, hipStream_t stream);
 size_t gemm_stream_workspace(int64_t n, int64_t k, int64_t m);

@@ -338,6 +338,15 @@ int launch_f16w_ct(int ct, const F16wArgs& a, int64_t rem_tiles, hipStream_t str
 
 }  // namespace
 
+// FG_F16W_COLS = 1..4 in the environment fixes the column tiles of 16 per workgroup tile where the width divides N
+// (tests cover every instantiation with it; sweeps calibrate the model below)
+int gemm_f16w_forced(int64_t n) {
+  const char* env = getenv("FG_F16W_COLS");
+  if (!env) return 0;
+  const int ct = atoi(env);
+  return ct >= 1 && ct <= 4 && n % (16 * ct) == 0 ? ct : 0;
+}
+
 // Column tiles of 16 per workgroup tile (0: this kernel does not take the shape, the caller falls back
 // on the 256-column stream kernel).  Cost of a choice in microseconds, fitted to measurements at 128 rows
 // (12288 x 4096, 4096 x 4096, 16384 x 4096, 4096 x 16384 and 50272 x 4096, every width): the HBM time of
@@ -348,12 +357,7 @@ int launch_f16w_ct(int ct, const F16wArgs& a, int64_t rem_tiles, hipStream_t str
 // as the LM head.
 int gemm_f16w_pick_cols(int64_t n, int64_t k, int64_t m) {
   if (m < 1 || m > 128 || k % kKS != 0 || k < kKS || n < 16) return 0;
-  // FG_F16W_COLS = 1..4 in the environment fixes the choice where the width divides N (tests cover every
-  // instantiation with it; sweeps calibrate the model)
-  if (const char* env = getenv("FG_F16W_COLS")) {
-    const int ct = atoi(env);
-    if (ct >= 1 && ct <= 4 && n % (16 * ct) == 0) return ct;
-  }
+  if (const int ct = gemm_f16w_forced(n)) return ct;
   const double rows = (double)(((m + 31) / 32) * 32), ksteps = (double)(k / kKS);
   const double hbm_us = (double)n * k * 2 / 6.0e6;
   int best = 0;

@@ -1,9 +1,10 @@
 // Fused dequant + GEMM for the decode-phase projections (Section 3: t.wQ, t.wK, t.wV, .wO, .w1, .w2
 // with the weights stored as in Section 5), for a small number of activation rows M (the block
 // of sequences in a decode step), on weights in the CANONICAL row-major 4-bit format, and on FP16
-// weights whose shape the streaming kernels do not take (N % 32 != 0, or 320 < M <= 512).  Tiled
-// 4-bit weights and the common FP16 cases go through fg_gemm_stream.hip, which is faster: in the
-// canonical format the 32 bytes a lane pair needs per K step lie K/2 bytes apart from row to row.
+// weights whose shape the streaming kernels do not take (N % 32 != 0), from 33 rows up (fewer rows:
+// fg_gemm_fewrows.hip).  Tiled 4-bit weights and the common FP16 cases go through fg_gemm_stream.hip,
+// which is faster: in the canonical format the 32 bytes a lane pair needs per K step lie K/2 bytes
+// apart from row to row.
 //
 // out[M, N] = act(x[M, K] . W[N, K]^T + bias) + residual
 //
@@ -334,9 +335,11 @@ int launch_t(const SmallArgs& a, hipStream_t stream) {
 
 template <bool Q4>
 int launch_q(int mt, const SmallArgs& a, hipStream_t stream) {
+  if constexpr (!Q4) {   // 4-bit weights come here from 33 rows up (gemm_fewrows_takes)
+    if (mt == 1) return launch_t<1, Q4>(a, stream);
+    if (mt == 2) return launch_t<2, Q4>(a, stream);
+  }
   switch (mt) {
-    case 1: return launch_t<1, Q4>(a, stream);
-    case 2: return launch_t<2, Q4>(a, stream);
     case 3: return launch_t<3, Q4>(a, stream);
     case 4: return launch_t<4, Q4>(a, stream);
     case 6: return launch_t<6, Q4>(a, stream);

@@ -2048,7 +2048,6 @@ int gemm_stream_launch(const LinearArgs& la, void* ws, size_t ws_bytes, hipStrea
     rc = h16m ? launch_dec16<MT, true>(a, stream) : launch_dec16<MT, false>(a, stream);            \
     break;
       switch (mt16) {
-        FG_DEC16_CASE(1)
         FG_DEC16_CASE(3)
         FG_DEC16_CASE(5)
         FG_DEC16_CASE(6)

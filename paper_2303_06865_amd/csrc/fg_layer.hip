@@ -137,7 +137,14 @@ static bool use_f16w(int dtype, int64_t n, int64_t k, int64_t m) {
   return dtype == FG_F16 && use_stream(dtype, n, m) && gemm_f16w_pick_cols(n, k, m) != 0;
 }
 
+// A few rows: the kernel that splits nothing over workgroups, on every weight format.  (FG_F16W_COLS in the
+// environment asks for the narrow-tile kernel on FP16 weights: gemm_f16w_pick_cols.)
+static bool use_fewrows(int dtype, int64_t n, int64_t k, int64_t m) {
+  return gemm_fewrows_takes(dtype, n, k, m) && !(dtype == FG_F16 && gemm_f16w_forced(n));
+}
+
 size_t linear_workspace_bytes(int dtype, int64_t n, int64_t k, int64_t m) {
+  if (use_fewrows(dtype, n, k, m)) return 0;
   if (use_f16w(dtype, n, k, m)) return gemm_f16w_workspace(n, k, m);
   if (use_stream(dtype, n, m)) return gemm_stream_workspace(n, k, m);
   if (m > kSmallMLimit) return 0;
@@ -145,6 +152,7 @@ size_t linear_workspace_bytes(int dtype, int64_t n, int64_t k, int64_t m) {
 }
 
 int linear_launch(const LinearArgs& a, void* ws, size_t ws_bytes, hipStream_t stream) {
+  if (use_fewrows(a.dtype, a.n, a.k, a.m)) return gemm_fewrows_launch(a, stream);
   if (use_f16w(a.dtype, a.n, a.k, a.m)) return gemm_f16w_launch(a, ws, ws_bytes, stream);
   if (use_stream(a.dtype, a.n, a.m)) return gemm_stream_launch(a, ws, ws_bytes, stream);
   if (a.m > kSmallMLimit) return gemm_large_m_launch(a, stream);

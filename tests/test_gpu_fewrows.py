@@ -1,0 +1,46 @@
+"""fg_linear with up to 32 rows (csrc/fg_gemm_fewrows.hip) on every weight format, against the oracle: every number of
+four-row pieces, every count of column tiles per workgroup and of waves, ragged columns, contractions of one group, of
+an odd number of groups (the last step is half empty), shorter and longer than the steps the waves keep in flight."""
+import pytest
+
+from tests.test_gpu_kernels import _linear_case
+from tests.util import assert_close
+
+pytestmark = pytest.mark.gpu
+
+# format: (quantized, tiled, FP16 pairs)
+FORMATS = {"f16": (False, False, False), "q4": (True, False, False), "q4t": (True, True, False), "q4h": (True, True, True)}
+
+CASES = [
+    # m, n, k, bias, relu, residual
+    (1, 32, 64, True, False, True),          # one group: one half-empty step, seven waves without work
+    (4, 96, 192, False, True, False),
+    (5, 544, 1984, True, False, True),       # 31 groups: 16 steps, two per wave, the last half empty
+    (8, 160, 3072, True, True, False),       # three steps per wave
+    (9, 256, 4160, False, False, True),      # 33 steps: four and five per wave
+    (16, 2304, 768, True, False, True),
+    (17, 768, 832, True, False, True),
+    (32, 1056, 1024, True, True, True),
+    (3, 7168, 128, True, False, False),      # two column tiles per workgroup
+    (12, 12288, 64, False, False, True),     # three
+    (16, 16384, 192, True, False, True),     # four
+    (29, 12256, 128, False, False, True),    # three, ragged
+    (2, 128, 8256, True, False, True),       # 65 steps: sixteen waves (tiled), eight (canonical, FP16)
+    (13, 64, 16448, True, False, True),      # 129 steps: sixteen waves on FP16 weights too
+    (7, 6144, 8256, True, False, False),     # sixteen waves, two column tiles (tiled)
+]
+
+
+@pytest.mark.parametrize("fmt", sorted(FORMATS))
+@pytest.mark.parametrize("m,n,k,bias,relu,residual", CASES)
+def test_linear_few_rows(m, n, k, bias, relu, residual, fmt):
+    quant, tiled, h16 = FORMATS[fmt]
+    got, ref = _linear_case(m, n, k, quant, bias, relu, residual, seed=m + n + k, tiled=tiled, meta_f16=h16)
+    assert_close(got, ref, "few rows m=%d n=%d k=%d %s" % (m, n, k, fmt))
+
+
+@pytest.mark.parametrize("quant", [True, False])
+@pytest.mark.parametrize("m,n", [(1, 8), (6, 1000), (31, 264)])
+def test_linear_few_rows_columns_not_a_multiple_of_16(m, n, quant):
+    got, ref = _linear_case(m, n, 320, quant, True, False, True, seed=m + n)
+    assert_close(got, ref, "few rows m=%d n=%d q=%s" % (m, n, quant))
