@@ -6,8 +6,73 @@
 namespace fg {
 namespace {
 
-// first unit of workgroup p when `total` units are cut into `grid` equal contiguous ranges
-__device__ __forceinline__ int64_t work_begin(int64_t total, int grid, int p) { return (total * p) / grid; }
+// ---- work shared along K: `total` (tile, K step) units cut into `parts` equal contiguous ranges, parts <= total.
+// first unit of range p (p >= parts: the end)
+__device__ __forceinline__ int64_t work_begin(int64_t total, int parts, int p) { return p < parts ? (total * p) / parts : total; }
+// the range of workgroup blockIdx.x: consecutive ranges on one XCD, all XCDs equally loaded; >= parts: none
+__device__ __forceinline__ int part_of_block(int parts) {
+  const int per_xcd = (parts + 7) >> 3, i = blockIdx.x >> 3;
+  return i < per_xcd ? (int)(blockIdx.x & 7) * per_xcd + i : parts;
+}
+// ranges lo .. hi share tile t of `ksteps` units; the tile is the first segment of every one of them but perhaps of lo
+struct TileParts {
+  int lo, hi;
+  bool lo_second;   // tile t is the second segment of range lo
+};
+__device__ __forceinline__ TileParts tile_parts(int64_t total, int parts, int ksteps, int64_t t) {
+  // work_begin(p) <= w  <=>  p <= ((w + 1) * parts - 1) / total
+  const int64_t w0 = t * ksteps, w1 = w0 + ksteps;
+  TileParts r;
+  if (total * parts < 0xffffffffll) {   // (a 64-bit division is some hundred instructions)
+    r.lo = (int)((uint32_t)((w0 + 1) * parts - 1) / (uint32_t)total);
+    r.hi = (int)((uint32_t)(w1 * parts - 1) / (uint32_t)total);
+    r.lo_second = (uint32_t)total * (uint32_t)r.lo / (uint32_t)parts != (uint32_t)w0;
+  } else {
+    r.lo = (int)(((w0 + 1) * parts - 1) / total);
+    r.hi = (int)((w1 * parts - 1) / total);
+    r.lo_second = work_begin(total, parts, r.lo) != w0;
+  }
+  return r;
+}
+// host: ranges that `total` units are cut into on `grid` workgroups.  Fewer than three K steps are not worth a
+// workgroup: its pipeline does not fill and its partial sums cost more than the steps.  Measured with the reduction pass,
+// 768 x 3072 4-bit weights at 33 / 144 / 600 rows, at least 1 / 3 / 6 / 12 steps (us): 14.5 / 10.7 / 11.3 / 14.3,
+// 23.5 / 16.8 / 17.2 / 21.2, 41.3 / 29.7 / 28.8 / 31.9 (and 49.6 / 56.5 / - with ranges of less than one step).
+constexpr int kMinPartSteps = 3;
+static inline int work_parts(int64_t total, int grid) {
+  const int64_t p = total / kMinPartSteps;
+  return p < 1 ? 1 : p < grid ? (int)p : grid;
+}
+
+// Sum, in ascending K order, of what ranges lo .. hi left of a tile: v[i] = float4 number `at + i * step` of each
+// range's slot (2 slots of slot4 float4s per range).  The loads of eight ranges are in flight together.
+template <int ITEMS>
+__device__ __forceinline__ void sum_parts(const float4* partial, int64_t slot4, const TileParts& tp, int64_t at, int64_t step,
+                                          float4 (&v)[ITEMS]) {
+  constexpr int kFly = ITEMS > 1 ? 4 : 8;
+#pragma unroll
+  for (int i = 0; i < ITEMS; ++i) v[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int p = tp.lo; p <= tp.hi; p += kFly) {
+    float4 x[kFly][ITEMS];
+#pragma unroll
+    for (int c = 0; c < kFly; ++c) {
+      const float4* src = partial + ((int64_t)(p + c) * 2 + (p + c == tp.lo && tp.lo_second ? 1 : 0)) * slot4 + at;
+#pragma unroll
+      for (int i = 0; i < ITEMS; ++i) x[c][i] = p + c <= tp.hi ? src[i * step] : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+#pragma unroll
+    for (int c = 0; c < kFly; ++c)
+      if (p + c <= tp.hi) {
+#pragma unroll
+        for (int i = 0; i < ITEMS; ++i) {
+          v[i].x += x[c][i].x;
+          v[i].y += x[c][i].y;
+          v[i].z += x[c][i].z;
+          v[i].w += x[c][i].w;
+        }
+      }
+  }
+}
 __device__ __forceinline__ int swz(int row, int kc) { return kc ^ ((row >> 1) & 7); }
 
 typedef const __attribute__((address_space(1))) void* gptr_t;

@@ -42,7 +42,8 @@ struct F16wArgs {
   int M, N, K;
   int n_tiles, ksteps;
   int rounds;           // whole rounds: tiles [0, rounds * 256) go one per workgroup per round
-  int64_t rem_work;     // (remaining tiles) * ksteps, cut into 256 equal ranges
+  int64_t rem_work;     // (remaining tiles) * ksteps, cut into `parts` equal ranges
+  int parts;
   const half_t* bias;
   const half_t* residual;
   int64_t ldr;
@@ -50,7 +51,7 @@ struct F16wArgs {
   half_t* out16;
   float* out32;
   int64_t ldo;
-  float* partial;       // [256][2][128 rows x BN columns] in register order
+  float* partial;       // [parts][2][128 rows x BN columns] in register order
 };
 
 constexpr int kNW = 8;             // waves per workgroup (two per SIMD): wave w owns the 16-row tile w
@@ -80,7 +81,8 @@ __global__ __launch_bounds__(kNW * 64) void gemm_f16w_kernel(F16wArgs a) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, g4 = lane >> 4;
   const int p = (blockIdx.x & 7) * (kGrid >> 3) + (blockIdx.x >> 3);
-  const int64_t rem_begin = work_begin(a.rem_work, kGrid, p), rem_end = work_begin(a.rem_work, kGrid, p + 1);
+  const int part = part_of_block(a.parts);
+  const int64_t rem_begin = work_begin(a.rem_work, a.parts, part), rem_end = work_begin(a.rem_work, a.parts, part + 1);
   int64_t pos = rem_begin;
   int round = 0, seg = 0;
   const uint32_t lds0 = (uint32_t)(uintptr_t)(lptr_t)smem;
@@ -237,7 +239,7 @@ __global__ __launch_bounds__(kNW * 64) void gemm_f16w_kernel(F16wArgs a) {
       }
     } else if (16 * wave < a.M) {
       // partial sums in register order: float4 number ct of thread tid
-      float4* dst = reinterpret_cast<float4*>(a.partial + ((int64_t)p * 2 + (seg == 0 ? 0 : 1)) * ((int64_t)C::kSlotRows * kBN)) + tid;
+      float4* dst = reinterpret_cast<float4*>(a.partial + ((int64_t)part * 2 + (seg == 0 ? 0 : 1)) * ((int64_t)C::kSlotRows * kBN)) + tid;
 #pragma unroll
       for (int ct = 0; ct < CT; ++ct) dst[ct * (kNW * 64)] = make_float4(acc[ct][0], acc[ct][1], acc[ct][2], acc[ct][3]);
     }
@@ -251,56 +253,32 @@ __global__ __launch_bounds__(kNW * 64) void gemm_f16w_kernel(F16wArgs a) {
   __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
-// Reduction pass: thread tid of a block adds, in ascending K order, the float4s that thread tid of the
-// contributing workgroups wrote for one tile, then applies the epilogue.  One block per tile.
+// Reduction pass: thread tid of a block adds, in ascending K order, the float4 number blockIdx.y that thread tid of
+// the contributing workgroups wrote for tile blockIdx.x (column tile blockIdx.y of it), then applies the epilogue.
 template <int CT>
 __global__ __launch_bounds__(kNW * 64) void gemm_f16w_finish_kernel(F16wArgs a) {
   constexpr int kBN = CT * 16;
-  const int64_t t = blockIdx.x;
-  const int64_t w0 = t * a.ksteps, w1 = w0 + a.ksteps;
-  int p_lo = (int)((w0 * kGrid) / a.rem_work);
-  while (p_lo + 1 < kGrid && work_begin(a.rem_work, kGrid, p_lo + 1) <= w0) ++p_lo;
-  while (p_lo > 0 && work_begin(a.rem_work, kGrid, p_lo) > w0) --p_lo;
-  if (work_begin(a.rem_work, kGrid, p_lo + 1) >= w1) return;   // one workgroup owned the whole tile and stored it
+  const TileParts tp = tile_parts(a.rem_work, a.parts, a.ksteps, blockIdx.x);
+  if (tp.lo == tp.hi) return;   // one workgroup owned the whole tile and stored it
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l16 = lane & 15, g4 = lane >> 4;
   if (16 * wave >= a.M) return;
-  const int64_t slot = (int64_t)kNW * 16 * kBN;
-  float4 v[CT];
+  const int ct = blockIdx.y;
+  float4 v[1];
+  sum_parts<1>(reinterpret_cast<const float4*>(a.partial), (int64_t)kNW * 16 * kBN / 4, tp, (int64_t)ct * (kNW * 64) + tid, 0, v);
+  const int col = ((int)((int64_t)a.rounds * kGrid + blockIdx.x)) * kBN + 16 * ct + l16;
+  const float o[4] = {v[0].x, v[0].y, v[0].z, v[0].w};
+  const float bvv = a.bias ? (float)a.bias[col] : 0.f;
 #pragma unroll
-  for (int e = 0; e < CT; ++e) v[e] = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int p = p_lo; p < kGrid; ++p) {
-    const int64_t pb = work_begin(a.rem_work, kGrid, p), pe = work_begin(a.rem_work, kGrid, p + 1);
-    if (pb >= w1) break;
-    if (pe == pb) continue;
-    const int s = pb >= w0 ? 0 : 1;   // the tile is the workgroup's first segment, or its second
-    const float4* src = reinterpret_cast<const float4*>(a.partial + ((int64_t)p * 2 + s) * slot) + tid;
-#pragma unroll
-    for (int e = 0; e < CT; ++e) {
-      const float4 x = src[e * (kNW * 64)];
-      v[e].x += x.x;
-      v[e].y += x.y;
-      v[e].z += x.z;
-      v[e].w += x.w;
-    }
-  }
-  const int n0 = (int)((int64_t)a.rounds * kGrid + t) * kBN;
-#pragma unroll
-  for (int ct = 0; ct < CT; ++ct) {
-    const int col = n0 + 16 * ct + l16;
-    const float o[4] = {v[ct].x, v[ct].y, v[ct].z, v[ct].w};
-    const float bvv = a.bias ? (float)a.bias[col] : 0.f;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int row = 16 * wave + 4 * g4 + r;
-      if (row >= a.M) continue;
-      float x = o[r] + bvv;
-      if (a.relu) x = fmaxf(x, 0.f);
-      if (a.residual) x += (float)a.residual[(int64_t)row * a.ldr + col];
-      if (a.out32)
-        a.out32[(int64_t)row * a.ldo + col] = x;
-      else
-        a.out16[(int64_t)row * a.ldo + col] = (half_t)x;
-    }
+  for (int r = 0; r < 4; ++r) {
+    const int row = 16 * wave + 4 * g4 + r;
+    if (row >= a.M) continue;
+    float x = o[r] + bvv;
+    if (a.relu) x = fmaxf(x, 0.f);
+    if (a.residual) x += (float)a.residual[(int64_t)row * a.ldr + col];
+    if (a.out32)
+      a.out32[(int64_t)row * a.ldo + col] = x;
+    else
+      a.out16[(int64_t)row * a.ldo + col] = (half_t)x;
   }
 }
 
@@ -320,7 +298,7 @@ int launch_f16w(const F16wArgs& a, int64_t rem_tiles, hipStream_t stream) {
   }
   if (rem_tiles > 0) {
     ProfScope prof(FG_K_GEMM_SMALL_M_FINISH, stream);
-    hipLaunchKernelGGL((gemm_f16w_finish_kernel<CT>), dim3((unsigned)rem_tiles), dim3(kNW * 64), 0, stream, a);
+    hipLaunchKernelGGL((gemm_f16w_finish_kernel<CT>), dim3((unsigned)rem_tiles, CT), dim3(kNW * 64), 0, stream, a);
     FG_LAUNCH_CHECK();
   }
   return FG_OK;
@@ -407,6 +385,7 @@ int gemm_f16w_launch(const LinearArgs& la, void* ws, size_t ws_bytes, hipStream_
   a.rounds = a.n_tiles / kGrid;
   const int64_t rem_tiles = a.n_tiles - (int64_t)a.rounds * kGrid;
   a.rem_work = rem_tiles * a.ksteps;
+  a.parts = work_parts(a.rem_work, kGrid);
   a.bias = la.bias;
   a.residual = la.residual;
   a.ldr = la.ldr;

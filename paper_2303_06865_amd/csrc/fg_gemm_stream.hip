@@ -44,8 +44,6 @@ constexpr int kBStageF16 = kBN * kKS * 2;     // FP16 weights: 256 rows of 128 b
 constexpr int kMaxMT = 5;     // decode shape: up to 5 row tiles of 32 (160 rows)
 constexpr int kGroupM = 4;    // row blocks per group in the tile walk
 constexpr int kLdsBytes = 160 * 1024;
-constexpr int kFinishItems = 4;   // float4 items per thread of the reduction pass
-constexpr int kFinishParts = 4;   // contributors whose loads are in flight together
 
 struct StreamArgs {
   const uint8_t* w;     // tiled codes
@@ -55,7 +53,8 @@ struct StreamArgs {
   int M, N, K;
   int m_blocks, n_tiles, ksteps, n32;   // n32 = N / 32
   int rounds;           // whole rounds: tiles [0, rounds*grid) go one per workgroup per round
-  int64_t rem_work;     // (remaining tiles) * ksteps, cut into grid equal ranges
+  int64_t rem_work;     // (remaining tiles) * ksteps, cut into `parts` equal ranges
+  int parts;
   int grid;
   const half_t* bias;
   const half_t* residual;
@@ -64,7 +63,7 @@ struct StreamArgs {
   half_t* out16;
   float* out32;
   int64_t ldo;
-  float* partial;       // [grid][2][block rows][256]
+  float* partial;       // [parts][2][block rows][256]
 };
 
 // linear tile number -> (row block, column block): groups of kGroupM row blocks, inside a group the
@@ -123,7 +122,8 @@ __global__ __launch_bounds__(NW * 64) void gemm_stream_kernel(StreamArgs a) {
   const int l32 = lane & 31, kb = lane >> 5;
 
   const int p = (blockIdx.x & 7) * (a.grid >> 3) + (blockIdx.x >> 3);
-  const int64_t rem_begin = work_begin(a.rem_work, a.grid, p), rem_end = work_begin(a.rem_work, a.grid, p + 1);
+  const int part = part_of_block(a.parts);
+  const int64_t rem_begin = work_begin(a.rem_work, a.parts, part), rem_end = work_begin(a.rem_work, a.parts, part + 1);
   int64_t pos = rem_begin;
   int round = 0, seg = 0;
 
@@ -439,7 +439,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_stream_kernel(StreamArgs a) {
     } else {
       // partial sums in register order: float4 number ((m*NT + j)*4 + q) of thread tid holds rows
       // 32m + 8q + 4kb + 0..3 of one column -> every store is 1 KiB contiguous per wave
-      float4* dst = reinterpret_cast<float4*>(a.partial + ((int64_t)p * 2 + (seg == 0 ? 0 : 1)) * ((int64_t)C::kRows * kBN)) + tid;
+      float4* dst = reinterpret_cast<float4*>(a.partial + ((int64_t)part * 2 + (seg == 0 ? 0 : 1)) * ((int64_t)C::kRows * kBN)) + tid;
 #pragma unroll
       for (int m = 0; m < MT; ++m)
 #pragma unroll
@@ -463,70 +463,28 @@ __global__ __launch_bounds__(NW * 64) void gemm_stream_kernel(StreamArgs a) {
 
 // Second pass of the stream-K schedule: tiles whose K range was shared get their partial sums added
 // in ascending K order, then the epilogue.  Thread tid of a block takes the float4s that thread tid of
-// the GEMM kernel wrote (four rows of one column each).  blockIdx.x counts the tiles after the whole
-// rounds.
+// the GEMM kernel wrote (four rows of one column each), ITEMS of them, gridDim.y apart.  blockIdx.x counts the
+// tiles after the whole rounds.
+template <int ITEMS>
 __global__ __launch_bounds__(512) void gemm_stream_finish_kernel(StreamArgs a, int mt, int nt, int wm_n) {
-  const int64_t t = blockIdx.x;
-  const int64_t w0 = t * a.ksteps, w1 = w0 + a.ksteps;
-  int p_lo = (int)((w0 * a.grid) / a.rem_work);
-  while (p_lo + 1 < a.grid && work_begin(a.rem_work, a.grid, p_lo + 1) <= w0) ++p_lo;
-  while (p_lo > 0 && work_begin(a.rem_work, a.grid, p_lo) > w0) --p_lo;
-  if (work_begin(a.rem_work, a.grid, p_lo + 1) >= w1) return;   // one workgroup owned the whole tile
-  int p_hi = p_lo;
-  while (p_hi + 1 < a.grid && work_begin(a.rem_work, a.grid, p_hi + 1) < w1) ++p_hi;
-
+  const TileParts tp = tile_parts(a.rem_work, a.parts, a.ksteps, blockIdx.x);
+  if (tp.lo == tp.hi) return;   // one workgroup owned the whole tile
   int mblk, n_tile;
-  tile_coords((int64_t)a.rounds * a.grid + t, a.m_blocks, a.n_tiles, mblk, n_tile);
+  tile_coords((int64_t)a.rounds * a.grid + blockIdx.x, a.m_blocks, a.n_tiles, mblk, n_tile);
   const int nthr = blockDim.x;   // = threads of the GEMM workgroup
   const int rows_t = wm_n * mt * 32, wn_n = (nthr >> 6) / wm_n;
   const int m0 = mblk * rows_t;
-  const int64_t slot = (int64_t)rows_t * kBN;
   const int tid = threadIdx.x, wave = tid >> 6, l32 = tid & 31, kb = (tid >> 5) & 1;
   const int wm = wave / wn_n, wn = wave - wm * wn_n;
-  // this thread's float4 items e = blockIdx.y + i * gridDim.y, e = (m*nt + j)*4 + q; the launch keeps
-  // their number within kFinishItems.  The loads of up to kFinishParts contributors for all items are
-  // in flight together (a tile of the decode shapes has 2 to 7 contributors: one or two dependent
-  // round trips instead of one per contributor); the sum still runs in ascending K order per item.
-  const int n_items = mt * nt * 4;
-  float4 v[kFinishItems];
+  // item e = (m * nt + j) * 4 + q: rows 8 q .. 8 q + 7 of row tile m; those wholly beyond M were never written
+  const int e0 = blockIdx.y, step = gridDim.y;
+  if (m0 + (wm * mt + (e0 >> 2) / nt) * 32 + (e0 & 3) * 8 >= a.M) return;   // (rows grow with e: the later ones neither)
+  float4 v[ITEMS];
+  sum_parts<ITEMS>(reinterpret_cast<const float4*>(a.partial), (int64_t)rows_t * (kBN / 4), tp, (int64_t)e0 * nthr + tid,
+                   (int64_t)step * nthr, v);
 #pragma unroll
-  for (int i = 0; i < kFinishItems; ++i) v[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-  int p = p_lo;
-  while (p <= p_hi) {
-    const float4* src[kFinishParts];
-    int n = 0;
-    for (; p <= p_hi && n < kFinishParts; ++p) {
-      const int64_t pb = work_begin(a.rem_work, a.grid, p);
-      if (work_begin(a.rem_work, a.grid, p + 1) == pb) continue;
-      const int s = pb >= w0 ? 0 : 1;
-      src[n++] = reinterpret_cast<const float4*>(a.partial + ((int64_t)p * 2 + s) * slot) + tid;
-    }
-    float4 x[kFinishParts][kFinishItems];
-#pragma unroll
-    for (int c = 0; c < kFinishParts; ++c)
-#pragma unroll
-      for (int i = 0; i < kFinishItems; ++i) {
-        const int e = blockIdx.y + i * gridDim.y;
-        // items whose eight rows (8q .. 8q+7 of row tile m) all lie beyond M were never written
-        const bool live = e < n_items && m0 + (wm * mt + (e >> 2) / nt) * 32 + (e & 3) * 8 < a.M;
-        x[c][i] = (c < n && live) ? src[c < n ? c : 0][(int64_t)e * nthr] : make_float4(0.f, 0.f, 0.f, 0.f);
-      }
-#pragma unroll
-    for (int c = 0; c < kFinishParts; ++c)
-      if (c < n) {
-#pragma unroll
-        for (int i = 0; i < kFinishItems; ++i) {
-          v[i].x += x[c][i].x;
-          v[i].y += x[c][i].y;
-          v[i].z += x[c][i].z;
-          v[i].w += x[c][i].w;
-        }
-      }
-  }
-#pragma unroll
-  for (int i = 0; i < kFinishItems; ++i) {
-    const int e = blockIdx.y + i * gridDim.y;
-    if (e >= n_items) break;
+  for (int i = 0; i < ITEMS; ++i) {
+    const int e = e0 + i * step;
     const int q = e & 3, mj = e >> 2, m = mj / nt, j = mj - m * nt;
     const int row0 = m0 + (wm * mt + m) * 32 + q * 8 + kb * 4;
     const int col = n_tile * kBN + (wn * nt + j) * 32 + l32;
@@ -607,7 +565,8 @@ __global__ __launch_bounds__(256) void gemm_decode16_kernel(StreamArgs a) {
   const int l16 = lane & 15, g4 = lane >> 4;
 
   const int p = (blockIdx.x & 7) * (a.grid >> 3) + (blockIdx.x >> 3);
-  const int64_t rem_begin = work_begin(a.rem_work, a.grid, p), rem_end = work_begin(a.rem_work, a.grid, p + 1);
+  const int part = part_of_block(a.parts);
+  const int64_t rem_begin = work_begin(a.rem_work, a.parts, part), rem_end = work_begin(a.rem_work, a.parts, part + 1);
   int64_t pos = rem_begin;
   int round = 0, seg = 0;
 
@@ -881,7 +840,7 @@ __global__ __launch_bounds__(256) void gemm_decode16_kernel(StreamArgs a) {
     } else {
       // partial sums in register order: float4 number (m * 4 + ct) of thread tid holds rows
       // 16 m + 4 g4 + 0..3 of one column -> every store is 1 KiB contiguous per wave
-      float4* dst = reinterpret_cast<float4*>(a.partial + ((int64_t)p * 2 + (seg == 0 ? 0 : 1)) * ((int64_t)C::kRows * kBN)) + tid;
+      float4* dst = reinterpret_cast<float4*>(a.partial + ((int64_t)part * 2 + (seg == 0 ? 0 : 1)) * ((int64_t)C::kRows * kBN)) + tid;
 #pragma unroll
       for (int m = 0; m < MT16; ++m)
 #pragma unroll
@@ -951,7 +910,8 @@ __global__ __launch_bounds__(512) void gemm_decode16x2_kernel(StreamArgs a) {
   const int l16 = lane & 15, g4 = lane >> 4;
 
   const int p = (blockIdx.x & 7) * (a.grid >> 3) + (blockIdx.x >> 3);
-  const int64_t rem_begin = work_begin(a.rem_work, a.grid, p), rem_end = work_begin(a.rem_work, a.grid, p + 1);
+  const int part = part_of_block(a.parts);
+  const int64_t rem_begin = work_begin(a.rem_work, a.parts, part), rem_end = work_begin(a.rem_work, a.parts, part + 1);
   int64_t pos = rem_begin;
   int round = 0, seg = 0;
 
@@ -1204,7 +1164,7 @@ __global__ __launch_bounds__(512) void gemm_decode16x2_kernel(StreamArgs a) {
     auto finish_kept = [&](auto SL_) __attribute__((always_inline)) {
       constexpr int keep = decltype(SL_)::value == 0 ? 0 : 2;
       const int partner = wave ^ 4;
-      float4* pdst = reinterpret_cast<float4*>(a.partial + ((int64_t)p * 2 + (seg == 0 ? 0 : 1)) * ((int64_t)C::kRows * kBN)) +
+      float4* pdst = reinterpret_cast<float4*>(a.partial + ((int64_t)part * 2 + (seg == 0 ? 0 : 1)) * ((int64_t)C::kRows * kBN)) +
                      (cg * 64 + lane);
 #pragma unroll
       for (int c = 0; c < 2; ++c) {
@@ -1293,7 +1253,7 @@ static_assert(p16_pos_cur(13) <= 32 - 4 && p16_pos_nxt(0) > 39 && p16_pos_nxt(13
 
 // What both prefill kernels on 16 x 16 x 32 MFMAs do with a finished segment of a 256 x 256 tile: acc[m][ct]
 // of wave w holds rows 16 m + 4 g4 + 0..3 of column 32 w + 16 ct + l16.
-__device__ __forceinline__ void prefill16_finish_tile(const StreamArgs& a, f4_t (&acc)[16][2], bool full, int m0, int nt0, int p,
+__device__ __forceinline__ void prefill16_finish_tile(const StreamArgs& a, f4_t (&acc)[16][2], bool full, int m0, int nt0, int part,
                                                       int seg, int wave, int l16, int g4) {
   // The MFMAs are opaque instructions to the compiler: wait out the last of them (16 cycles each)
   // before the accumulators are read.
@@ -1349,7 +1309,7 @@ __device__ __forceinline__ void prefill16_finish_tile(const StreamArgs& a, f4_t 
     // Partial sums in the layout of gemm_stream_kernel<8, 1, 1, 8> (its reduction pass finishes these
     // tiles too): float4 number (2 m + g4 / 2) of "thread" 64 wave + 32 (g4 % 2) + 16 ct + l16 holds
     // rows 16 m + 4 g4 + 0..3 of column 32 wave + 16 ct + l16.
-    float4* base = reinterpret_cast<float4*>(a.partial + ((int64_t)p * 2 + (seg == 0 ? 0 : 1)) * ((int64_t)kP16Rows * kBN));
+    float4* base = reinterpret_cast<float4*>(a.partial + ((int64_t)part * 2 + (seg == 0 ? 0 : 1)) * ((int64_t)kP16Rows * kBN));
 #pragma unroll
     for (int m = 0; m < 16; ++m)
 #pragma unroll
@@ -1371,7 +1331,8 @@ __global__ __launch_bounds__(512) void gemm_prefill16_kernel(StreamArgs a) {
   const int l16 = lane & 15, g4 = lane >> 4;
 
   const int p = (blockIdx.x & 7) * (a.grid >> 3) + (blockIdx.x >> 3);
-  const int64_t rem_begin = work_begin(a.rem_work, a.grid, p), rem_end = work_begin(a.rem_work, a.grid, p + 1);
+  const int part = part_of_block(a.parts);
+  const int64_t rem_begin = work_begin(a.rem_work, a.parts, part), rem_end = work_begin(a.rem_work, a.parts, part + 1);
   int64_t pos = rem_begin;
   int round = 0, seg = 0;
 
@@ -1588,7 +1549,7 @@ __global__ __launch_bounds__(512) void gemm_prefill16_kernel(StreamArgs a) {
       wslot = wslot1;
     }
 
-    prefill16_finish_tile(a, acc, (ks0 == 0) && (ks1 == a.ksteps), m0, nt0, p, seg, wave, l16, g4);
+    prefill16_finish_tile(a, acc, (ks0 == 0) && (ks1 == a.ksteps), m0, nt0, part, seg, wave, l16, g4);
     if (whole_round) {
       ++round;
     } else {
@@ -1621,7 +1582,8 @@ __global__ __launch_bounds__(512) void gemm_prefill16_f16_kernel(StreamArgs a) {
   const int l16 = lane & 15, g4 = lane >> 4;
 
   const int p = (blockIdx.x & 7) * (a.grid >> 3) + (blockIdx.x >> 3);
-  const int64_t rem_begin = work_begin(a.rem_work, a.grid, p), rem_end = work_begin(a.rem_work, a.grid, p + 1);
+  const int part = part_of_block(a.parts);
+  const int64_t rem_begin = work_begin(a.rem_work, a.parts, part), rem_end = work_begin(a.rem_work, a.parts, part + 1);
   int64_t pos = rem_begin;
   int round = 0, seg = 0;
 
@@ -1780,7 +1742,7 @@ __global__ __launch_bounds__(512) void gemm_prefill16_f16_kernel(StreamArgs a) {
       wslot = wslot1;
     }
 
-    prefill16_finish_tile(a, acc, (ks0 == 0) && (ks1 == a.ksteps), m0, nt0, p, seg, wave, l16, g4);
+    prefill16_finish_tile(a, acc, (ks0 == 0) && (ks1 == a.ksteps), m0, nt0, part, seg, wave, l16, g4);
     if (whole_round) {
       ++round;
     } else {
@@ -1793,61 +1755,23 @@ __global__ __launch_bounds__(512) void gemm_prefill16_f16_kernel(StreamArgs a) {
 
 // Reduction pass for gemm_decode16_kernel: thread tid of a block adds, in ascending K order, the float4s
 // that thread tid of the contributing workgroups wrote, then applies the epilogue.  blockIdx.x counts the
-// tiles after the whole rounds, blockIdx.y spreads a thread's MT16 * 4 items.
+// tiles after the whole rounds, blockIdx.y the MT16 * 4 items of a thread, ITEMS of them gridDim.y apart.
+template <int ITEMS>
 __global__ __launch_bounds__(256) void gemm_decode16_finish_kernel(StreamArgs a, int mt16) {
-  const int64_t t = blockIdx.x;
-  const int64_t w0 = t * a.ksteps, w1 = w0 + a.ksteps;
-  int p_lo = (int)((w0 * a.grid) / a.rem_work);
-  while (p_lo + 1 < a.grid && work_begin(a.rem_work, a.grid, p_lo + 1) <= w0) ++p_lo;
-  while (p_lo > 0 && work_begin(a.rem_work, a.grid, p_lo) > w0) --p_lo;
-  if (work_begin(a.rem_work, a.grid, p_lo + 1) >= w1) return;   // one workgroup owned the whole tile
-  int p_hi = p_lo;
-  while (p_hi + 1 < a.grid && work_begin(a.rem_work, a.grid, p_hi + 1) < w1) ++p_hi;
-
+  const TileParts tp = tile_parts(a.rem_work, a.parts, a.ksteps, blockIdx.x);
+  if (tp.lo == tp.hi) return;   // one workgroup owned the whole tile
   int mblk, n_tile;
-  tile_coords((int64_t)a.rounds * a.grid + t, a.m_blocks, a.n_tiles, mblk, n_tile);
+  tile_coords((int64_t)a.rounds * a.grid + blockIdx.x, a.m_blocks, a.n_tiles, mblk, n_tile);
   const int rows_t = mt16 * 16;
   const int m0 = mblk * rows_t;
-  const int64_t slot = (int64_t)rows_t * kBN;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l16 = lane & 15, g4 = lane >> 4;
-  const int n_items = mt16 * 4;
-  float4 v[kFinishItems];
+  const int e0 = blockIdx.y, step = gridDim.y;
+  float4 v[ITEMS];
+  sum_parts<ITEMS>(reinterpret_cast<const float4*>(a.partial), (int64_t)rows_t * (kBN / 4), tp, (int64_t)e0 * 256 + tid,
+                   (int64_t)step * 256, v);
 #pragma unroll
-  for (int i = 0; i < kFinishItems; ++i) v[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-  int p = p_lo;
-  while (p <= p_hi) {
-    const float4* src[kFinishParts];
-    int n = 0;
-    for (; p <= p_hi && n < kFinishParts; ++p) {
-      const int64_t pb = work_begin(a.rem_work, a.grid, p);
-      if (work_begin(a.rem_work, a.grid, p + 1) == pb) continue;
-      const int s = pb >= w0 ? 0 : 1;
-      src[n++] = reinterpret_cast<const float4*>(a.partial + ((int64_t)p * 2 + s) * slot) + tid;
-    }
-    float4 x[kFinishParts][kFinishItems];
-#pragma unroll
-    for (int c = 0; c < kFinishParts; ++c)
-#pragma unroll
-      for (int i = 0; i < kFinishItems; ++i) {
-        const int e = blockIdx.y + i * gridDim.y;
-        x[c][i] = (c < n && e < n_items) ? src[c < n ? c : 0][(int64_t)e * 256] : make_float4(0.f, 0.f, 0.f, 0.f);
-      }
-#pragma unroll
-    for (int c = 0; c < kFinishParts; ++c)
-      if (c < n) {
-#pragma unroll
-        for (int i = 0; i < kFinishItems; ++i) {
-          v[i].x += x[c][i].x;
-          v[i].y += x[c][i].y;
-          v[i].z += x[c][i].z;
-          v[i].w += x[c][i].w;
-        }
-      }
-  }
-#pragma unroll
-  for (int i = 0; i < kFinishItems; ++i) {
-    const int e = blockIdx.y + i * gridDim.y;
-    if (e >= n_items) break;
+  for (int i = 0; i < ITEMS; ++i) {
+    const int e = e0 + i * step;
     const int m = e >> 2, ct = e & 3;
     const int row0 = m0 + 16 * m + 4 * g4;
     const int col = n_tile * kBN + wave * 64 + ct * 16 + l16;
@@ -1908,8 +1832,34 @@ Shape pick_shape(int64_t m) {
   return {need < 1 ? 1 : need, 2, 1, 4};
 }
 
-// blocks along y of the reduction pass: every thread takes at most kFinishItems of the mt*nt*4 items
-static inline unsigned finish_y(const Shape& sh) { return (unsigned)ceil_div(sh.mt * sh.nt * 4, kFinishItems); }
+// The reduction pass reads what the contraction wrote a moment ago, and is short: one item per thread, so that every CU
+// has work and each thread's few loads are all in flight at once, until there are more than 26 workgroups of 256 threads
+// per CU; from there two items per thread, for fewer of them.  Measured (us, four items as it was with its ranges searched
+// one by one / four / two / one): 36864 x 12288 x 144 rows 16.7 / 14.8 / 13.4 / 13.9; 12288 x 49152 x 144 18.8 / 16.4 /
+// 12.8 / 11.6; 7168 x 28672 x 37 16.7 / 11.6 / 8.6 / 6.6; 49152 x 12288 x 144 18.5 / 16.8 / 14.4 / 16.4; 12288 x 4096 x
+// 333 19.6 / 19.1 / 16.2 / 16.5; 28672 x 7168 x 1000 33.6 / 28.6 / 23.3 / 31.
+bool finish_two_items(int64_t rem_tiles, int n_items, int nthr) { return rem_tiles * n_items * (nthr / 256) > 26 * 256; }
+
+int launch_stream_finish(const StreamArgs& a, const Shape& sh, int64_t rem_tiles, hipStream_t stream) {
+  const int n_items = sh.mt * sh.nt * 4;
+  const dim3 block(sh.nw * 64);
+  if (finish_two_items(rem_tiles, n_items, sh.nw * 64))
+    hipLaunchKernelGGL(gemm_stream_finish_kernel<2>, dim3((unsigned)rem_tiles, n_items / 2), block, 0, stream, a, sh.mt, sh.nt, sh.wm);
+  else
+    hipLaunchKernelGGL(gemm_stream_finish_kernel<1>, dim3((unsigned)rem_tiles, n_items), block, 0, stream, a, sh.mt, sh.nt, sh.wm);
+  FG_LAUNCH_CHECK();
+  return FG_OK;
+}
+
+int launch_dec16_finish(const StreamArgs& a, int mt16, int64_t rem_tiles, hipStream_t stream) {
+  const int n_items = mt16 * 4;
+  if (finish_two_items(rem_tiles, n_items, 256))
+    hipLaunchKernelGGL(gemm_decode16_finish_kernel<2>, dim3((unsigned)rem_tiles, n_items / 2), dim3(256), 0, stream, a, mt16);
+  else
+    hipLaunchKernelGGL(gemm_decode16_finish_kernel<1>, dim3((unsigned)rem_tiles, n_items), dim3(256), 0, stream, a, mt16);
+  FG_LAUNCH_CHECK();
+  return FG_OK;
+}
 
 template <int MT, int NT, int WM, int NW, bool F16W, bool H16M = false>
 int launch_t(const StreamArgs& a, hipStream_t stream) {
@@ -2008,6 +1958,7 @@ int gemm_stream_launch(const LinearArgs& la, void* ws, size_t ws_bytes, hipStrea
   a.rounds = (int)(tiles / a.grid);
   const int64_t rem_tiles = tiles - (int64_t)a.rounds * a.grid;
   a.rem_work = rem_tiles * a.ksteps;
+  a.parts = work_parts(a.rem_work, a.grid);
   a.bias = la.bias;
   a.residual = la.residual;
   a.ldr = la.ldr;
@@ -2026,9 +1977,7 @@ int gemm_stream_launch(const LinearArgs& la, void* ws, size_t ws_bytes, hipStrea
                                                     : launch_prefill16<false>(a, stream);
     if (rc) return rc;
     if (rem_tiles > 0) {
-      hipLaunchKernelGGL(gemm_stream_finish_kernel, dim3((unsigned)rem_tiles, finish_y(sh)), dim3(sh.nw * 64), 0, stream, a, sh.mt,
-                         sh.nt, sh.wm);
-      FG_LAUNCH_CHECK();
+      return launch_stream_finish(a, sh, rem_tiles, stream);
     }
     return FG_OK;
   }
@@ -2060,9 +2009,7 @@ int gemm_stream_launch(const LinearArgs& la, void* ws, size_t ws_bytes, hipStrea
     }
     if (rem_tiles > 0) {
       ProfScope prof(FG_K_GEMM_SMALL_M_FINISH, stream);
-      hipLaunchKernelGGL(gemm_decode16_finish_kernel, dim3((unsigned)rem_tiles, (unsigned)ceil_div(mt16 * 4, kFinishItems)),
-                         dim3(256), 0, stream, a, mt16);
-      FG_LAUNCH_CHECK();
+      return launch_dec16_finish(a, mt16, rem_tiles, stream);
     }
     return FG_OK;
   }
@@ -2088,9 +2035,7 @@ int gemm_stream_launch(const LinearArgs& la, void* ws, size_t ws_bytes, hipStrea
   }
   if (rem_tiles > 0) {
     ProfScope prof(FG_K_GEMM_SMALL_M_FINISH, stream);
-    hipLaunchKernelGGL(gemm_stream_finish_kernel, dim3((unsigned)rem_tiles, finish_y(sh)),
-                       dim3(sh.nw * 64), 0, stream, a, sh.mt, sh.nt, sh.wm);
-    FG_LAUNCH_CHECK();
+    return launch_stream_finish(a, sh, rem_tiles, stream);
   }
   return FG_OK;
 }
