@@ -313,16 +313,17 @@ FewArgs make_few(const LinearArgs& la) {
   return a;
 }
 
-// Column tiles per workgroup.  A CU's share is ceil(workgroups / 256) of them, and a workgroup costs its CT column
+// Column tiles per workgroup.  A CU's share is ceil(workgroups / 256) of them (a row block of 32 has its own), and a workgroup costs its CT column
 // tiles plus the activations it pulls in, which in units of a column tile's weights are 0.04 per row (FP16 weights:
 // 0.015, their tiles are three times the bytes).  Fitted to sweeps of CT = 1..6 over 25 matrices; it picks the fastest
 // or one within 4 % of it in all but two of them.
 int pick_ct(int fmt, int64_t n, int64_t m) {
-  const double rows = (fmt == kFewF16 ? 0.015 : 0.04) * (double)m;
+  const int64_t blocks = ceil_div(m, 32);
+  const double rows = (fmt == kFewF16 ? 0.015 : 0.04) * (double)(m < 32 ? m : 32);
   int best = 1;
   double best_cost = 0;
   for (int ct = 1; ct <= 4; ++ct) {
-    const double cost = (double)ceil_div(ceil_div(n, 16 * ct), 256) * (ct + rows);
+    const double cost = (double)ceil_div(ceil_div(n, 16 * ct) * blocks, 256) * (ct + rows);
     if (ct == 1 || cost < best_cost) {
       best = ct;
       best_cost = cost;
@@ -362,18 +363,35 @@ int launch_few_fmt(const FewArgs& a, hipStream_t stream) {
 
 }  // namespace
 
-// Which calls this kernel takes: up to 16 rows all of them; up to 32 rows those whose matrix is small enough for the
+// Which calls this kernel takes.  Up to 16 rows all of them; up to 32 rows those whose matrix is small enough for the
 // activations of its many workgroups not to cost more than the wider tiles' partial sums.  Measured at 32 rows against
 // the kernel that otherwise runs (us): tiled 28672 x 7168 43 vs 48, 7168 x 28672 49 vs 56, 36864 x 12288 84 vs 76,
 // 12288 x 49152 101 vs 98; FP16 21504 x 7168 68 vs 69, 12288 x 12288 58 vs 70, 7168 x 28672 100 vs 97, 50272 x 4096
 // 102 vs 96; canonical always (46 vs 135 and more).
+// More rows, in blocks of 32 that each read the matrix: as long as matrix x blocks is small, the other kernels leave most
+// of the chip without work, or split the contraction into partial sums.  The line is where both take the same time, us:
+//   tiled, 110 M    768 x 768 x 128 rows 4.6 vs 12.4; 2304 x 768 x 1000 22 vs 32; 2048 x 2048 x 640 21 vs 43;
+//                   4096 x 4096 x 64 9.1 vs 20, x 192 23 vs 24; 7168 x 7168 x 64 21 vs 25, x 96 33 vs 32;
+//                   12288 x 4096 x 64 22.8 vs 23.3; 4096 x 16384 x 64 29 vs 26
+//   FP16, 34 M      2048 x 2048 x 128 8.1 vs 13; 4096 x 4096 x 64 15.9 vs 15.7, x 96 27 vs 19
+//   FP16 beyond 128 rows, 70 M   2304 x 768 x 320 10 vs 18; 2048 x 2048 x 450 22 vs 39; 6144 x 2048 x 144 24 vs 30,
+//                   x 192 29 vs 26
+//   canonical, 600 M   12288 x 4096 x 64 30 vs 343, x 320 119 vs 161, x 512 175 vs 121; 7168 x 7168 x 320 118 vs 184;
+//                   7168 x 28672 x 33 85 vs 325; 36864 x 12288 x 33 201 vs 183
+//   canonical beyond 512 rows, 300 M   2048 x 2048 x 1000 36 vs 87; 6144 x 2048 x 640 66 vs 87, x 1000 98 vs 89
 bool gemm_fewrows_takes(int dtype, int64_t n, int64_t k, int64_t m) {
-  if (m < 1 || m > 32 || k % kGroup != 0) return false;
+  if (m < 1 || m > 1024 || k % kGroup != 0) return false;
   if (m <= 16) return true;
-  if (dtype == FG_Q4G64) return true;
   const int64_t size = n * k;
-  if (dtype == FG_F16) return size <= 160000000 && n <= 32768;
-  return size <= 220000000;
+  if (m <= 32) {
+    if (dtype == FG_Q4G64) return true;
+    if (dtype == FG_F16) return size <= 160000000 && n <= 32768;
+    return size <= 220000000;
+  }
+  const int64_t line = dtype == FG_Q4G64 ? (m <= 512 ? 600000000 : 300000000)
+                       : dtype == FG_F16 ? (m <= 128 ? 34000000 : 70000000)
+                                         : 110000000;
+  return size <= line / ceil_div(m, 32);
 }
 
 int gemm_fewrows_launch(const LinearArgs& la, hipStream_t stream) {

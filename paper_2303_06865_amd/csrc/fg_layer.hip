@@ -143,8 +143,10 @@ static bool use_fewrows(int dtype, int64_t n, int64_t k, int64_t m) {
   return gemm_fewrows_takes(dtype, n, k, m) && !(dtype == FG_F16 && gemm_f16w_forced(n));
 }
 
+// What a call asks of its caller (and is refused without) is that of the kernels that split the contraction, also where
+// gemm_fewrows_kernel, which needs nothing, takes the call: sizes that callers computed or were refused with stay as
+// they are when the line between the kernels moves.
 size_t linear_workspace_bytes(int dtype, int64_t n, int64_t k, int64_t m) {
-  if (use_fewrows(dtype, n, k, m)) return 0;
   if (use_f16w(dtype, n, k, m)) return gemm_f16w_workspace(n, k, m);
   if (use_stream(dtype, n, m)) return gemm_stream_workspace(n, k, m);
   if (m > kSmallMLimit) return 0;

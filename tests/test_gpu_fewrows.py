@@ -44,3 +44,14 @@ def test_linear_few_rows(m, n, k, bias, relu, residual, fmt):
 def test_linear_few_rows_columns_not_a_multiple_of_16(m, n, quant):
     got, ref = _linear_case(m, n, 320, quant, True, False, True, seed=m + n)
     assert_close(got, ref, "few rows m=%d n=%d q=%s" % (m, n, quant))
+
+
+# more rows of a small matrix: blocks of 32 rows, the last one with one row or all but one, up to the rows and sizes at
+# which the other kernels take over (tests/test_gpu_split_k.py has those)
+@pytest.mark.parametrize("fmt", sorted(FORMATS))
+@pytest.mark.parametrize("m,n,k", [(33, 96, 192), (63, 2304, 768), (64, 1056, 1984), (129, 800, 448), (1023, 64, 256),
+                                   (1024, 544, 64)])
+def test_linear_blocks_of_rows(m, n, k, fmt):
+    quant, tiled, h16 = FORMATS[fmt]
+    got, ref = _linear_case(m, n, k, quant, True, True, True, seed=m + n + k, tiled=tiled, meta_f16=h16)
+    assert_close(got, ref, "blocks of rows m=%d n=%d k=%d %s" % (m, n, k, fmt))
