@@ -179,6 +179,12 @@ int fg_quantize_groupwise_h16(const void* x_f16, int64_t rows, int64_t cols, int
  * or 4 bytes).  src->rows % 32 == 0.  Done once per weight matrix, e.g. at load time. */
 int fg_pack_weights(const fg_mat* src, void* data_out, void* meta_out, void* stream);
 
+/* Both at once, as a loader wants it: quantize x [rows, cols] FP16 straight into FG_Q4G64_TILED (meta_f16 == 0)
+ * or FG_Q4G64_H16_TILED (otherwise), the same bytes as fg_quantize_groupwise(_h16) followed by fg_pack_weights,
+ * without the canonical matrix in between.  cols % 64 == 0, rows > 0 and rows % 32 == 0. */
+int fg_quantize_tiled(const void* x_f16, int64_t rows, int64_t cols, int meta_f16, void* data_out, void* meta_out,
+                      void* stream);
+
 /* Inverse map of Section 5 (stored 4-bit -> values before computation): out_f32[r][c] =
  * min + code*scale rounded once to binary32 (a fused multiply-add). */
 int fg_dequantize_groupwise(const void* codes, const void* meta, int64_t rows, int64_t cols,

@@ -67,6 +67,7 @@ EXPORTS = {
                                         C.c_void_p]),
     "fg_quantize_groupwise_h16": (C.c_int, [C.c_void_p, C.c_int64, C.c_int64, C.c_int, C.c_int, C.c_void_p,
                                             C.c_void_p, C.c_void_p]),
+    "fg_quantize_tiled": (C.c_int, [C.c_void_p, C.c_int64, C.c_int64, C.c_int, C.c_void_p, C.c_void_p, C.c_void_p]),
     "fg_pack_weights": (C.c_int, [C.POINTER(fg_mat), C.c_void_p, C.c_void_p, C.c_void_p]),
     "fg_dequantize_groupwise": (C.c_int, [C.c_void_p, C.c_void_p, C.c_int64, C.c_int64, C.c_void_p, C.c_void_p]),
     "fg_dequantize_groupwise_h16": (C.c_int, [C.c_void_p, C.c_void_p, C.c_int64, C.c_int64, C.c_void_p, C.c_void_p]),
@@ -193,15 +194,20 @@ class Mat:
 
     @staticmethod
     def from_f16(w: torch.Tensor, quantize: bool, tiled: bool = False, meta_f16: bool = False) -> "Mat":
-        """quantize: store as 4-bit groups of 64 (quantized on the GPU); tiled: additionally reorder
-        into the streaming layout with fg_pack_weights (rows must be a multiple of 32); meta_f16: the
+        """quantize: store as 4-bit groups of 64 (quantized on the GPU); tiled: directly in the
+        streaming layout (fg_quantize_tiled; rows must be a multiple of 32); meta_f16: the
         {min, scale} pairs are FP16 (only the tiled form of such a matrix can be multiplied)."""
         w = _f16(w)
         r, c = w.shape
+        if quantize and tiled:
+            codes = torch.empty((r, c // 2), dtype=torch.uint8, device=w.device)
+            meta = torch.empty((r, c // 64, 2), dtype=torch.float16 if meta_f16 else torch.float32, device=w.device)
+            _check(lib().fg_quantize_tiled(_p(w), r, c, int(meta_f16), _p(codes), _p(meta), _stream()),
+                   "fg_quantize_tiled")
+            return Mat(r, c, FG_Q4G64_H16_TILED if meta_f16 else FG_Q4G64_TILED, codes, meta)
         if quantize:
             codes, meta = fg_quantize_groupwise(w, meta_f16=meta_f16)
-            m = Mat(r, c, FG_Q4G64_H16 if meta_f16 else FG_Q4G64, codes, meta)
-            return m.tiled() if tiled else m
+            return Mat(r, c, FG_Q4G64_H16 if meta_f16 else FG_Q4G64, codes, meta)
         return Mat(r, c, FG_F16, w, None)
 
     def tiled(self) -> "Mat":

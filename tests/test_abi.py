@@ -54,6 +54,11 @@ def test_quantize_argument_errors_need_no_gpu():
     assert L.fg_quantize_groupwise(p, -1, 128, 64, 4, p, p, None) == B.FG_ERR_SHAPE
     assert L.fg_quantize_groupwise(None, 4, 128, 64, 4, p, p, None) == B.FG_ERR_NULL
     assert L.fg_quantize_groupwise(p, 0, 128, 64, 4, p, p, None) == B.FG_OK      # empty input: no-op
+    assert L.fg_quantize_tiled(p, 33, 64, 0, p, p, None) == B.FG_ERR_SHAPE
+    assert L.fg_quantize_tiled(p, 0, 64, 0, p, p, None) == B.FG_ERR_SHAPE
+    assert L.fg_quantize_tiled(p, 32, 96, 1, p, p, None) == B.FG_ERR_SHAPE
+    assert L.fg_quantize_tiled(p, 32, 64, 1, C.c_void_p(24), p, None) == B.FG_ERR_SHAPE
+    assert L.fg_quantize_tiled(p, 32, 64, 0, p, None, None) == B.FG_ERR_NULL
     assert L.fg_dequantize_groupwise(p, p, 2, 100, p, None) == B.FG_ERR_SHAPE
     assert L.fg_layernorm(p, p, p, 2, 12, 1e-5, p, None) == B.FG_ERR_SHAPE
 

@@ -107,6 +107,27 @@ def test_quantize_arbitrary_finite_bit_patterns_bit_exact(meta_f16):
         assert np.array_equal(got.astype(np.float32), w_ref[:, k0:k0 + 64].T.astype(np.float32))
 
 
+@pytest.mark.parametrize("rows,cols", [(32, 64), (64, 192), (96, 64 * 5), (2304, 768), (4096, 12288)])
+@pytest.mark.parametrize("meta_f16", [False, True])
+def test_quantize_tiled_is_quantize_then_tile(rows, cols, meta_f16):
+    """One pass into the tile order: the oracle's codes and pairs in tile_weights' order, byte for byte, also where a
+    group holds infinities or NaNs (compared with the canonical quantizer followed by fg_pack_weights)."""
+    x = _rand16((rows, cols), 0.02, rows + cols)
+    x[0, :64] = 0.25
+    if rows * cols <= 64 * 1024:
+        codes_ref, meta_ref = tile_weights(*(O.quantize_groupwise_h16 if meta_f16 else O.quantize_groupwise)(x))
+        m = B.Mat.from_f16(dev(x), True, tiled=True, meta_f16=meta_f16)
+        torch.cuda.synchronize()
+        assert np.array_equal(host(m.data), codes_ref)
+        assert host(m.meta).tobytes() == meta_ref.tobytes()
+    x[1, 3], x[2, 5], x[rows - 1, cols - 1] = np.inf, np.nan, -np.inf
+    m = B.Mat.from_f16(dev(x), True, tiled=True, meta_f16=meta_f16)
+    two = B.Mat.from_f16(dev(x), True, meta_f16=meta_f16).tiled()
+    torch.cuda.synchronize()
+    assert m.dtype == two.dtype and torch.equal(m.data, two.data)
+    assert host(m.meta).tobytes() == host(two.meta).tobytes()
+
+
 def test_quantize_empty_input_is_a_noop():
     x = torch.empty((0, 128), dtype=torch.float16, device="cuda")
     codes, meta = B.fg_quantize_groupwise(x)
