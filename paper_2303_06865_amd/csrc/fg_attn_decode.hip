@@ -1,14 +1,13 @@
 // Decode-phase attention over the stored KV cache (Section 3, decode: softmax(tQ.K^T/sqrt(h)).V),
 // with the cache read in its storage format of Section 5 and dequantized in registers.
 //
-// WPH = 1, 2 or 4 waves per (sequence, head), four waves per workgroup.  The rows of that head's K
-// and V are one contiguous byte stream in the cache, read 16 bytes per lane (1 KiB per wave load).
+// WPH = 1, 2, 4 or (4-bit caches) 8 waves per (sequence, head), four waves per workgroup (eight where they
+// share a head).  The rows of that head's K and V are one contiguous byte stream in the cache, read 16 bytes
+// per lane (1 KiB per wave load).
 // The waves of a head take 4 KiB chunks of the stream round-robin, keep a running (max, sum, output)
 // triple each, and the triples are merged through LDS at the end (log-sum-exp merge); with one wave
-// per head there is nothing to merge.  The host picks the smallest WPH that still fills the chip:
-// a stream of c chunks costs ceil(c / WPH) chunk times, so at 528 rows (8.25 chunks) four waves
-// per head would idle a quarter of the time.  The next chunk's loads are issued before the current
-// one is processed.
+// per head there is nothing to merge.  The host picks WPH (pick_waves_per_head).  The next chunk's loads are
+// issued before the current one is processed.
 //
 // 4-bit path, per chunk of 128 quantization groups (64 rows at head size 128, 128 rows at 64):
 //   scores  : q.k_hat = sum_g scale_g * (q_g . c_g) + min_g * sum(q_g).  The code dot products run on
@@ -47,12 +46,15 @@ struct AttnArgs {
 
 // Merge the WPH per-wave triples of each head of the block and write the outputs.  o_w already
 // includes the per-group constant term.  out0 = output row of the block's first head.
+// waves of a workgroup: four, or all of one head where more than four share it
+constexpr int block_waves(int wph) { return wph > 4 ? wph : 4; }
+
 template <int DH, int WPH>
 __device__ __forceinline__ void merge_and_store(const float* sm_m, const float* sm_l, const float* sm_o, half_t* out0,
                                                 int heads_valid) {
   __syncthreads();
-  constexpr int HPB = 4 / WPH;
-  for (int idx = threadIdx.x; idx < HPB * DH; idx += 256) {
+  constexpr int NW = block_waves(WPH), HPB = NW / WPH;
+  for (int idx = threadIdx.x; idx < HPB * DH; idx += 64 * NW) {
     const int hl = idx / DH, t = idx - hl * DH;
     if (hl >= heads_valid) break;
     const float* mm = sm_m + hl * WPH;
@@ -74,14 +76,14 @@ __device__ __forceinline__ void merge_and_store(const float* sm_m, const float* 
 // row of the page table, and every sequence has its own length.  A wave keeps 64 consecutive table
 // entries in one register (one per lane) and picks the page of a chunk with a lane read.
 template <int DH, int WPH, bool H16, bool PAGED = false>
-__global__ __launch_bounds__(256, 3) void attn_decode_q4_kernel(AttnArgs a) {
+__global__ __launch_bounds__(64 * block_waves(WPH), WPH > 4 ? WPH / 4 : 3) void attn_decode_q4_kernel(AttnArgs a) {
   using meta_t = typename MetaRaw<H16>::type;
   constexpr int GPR = DH / 64;       // quantization groups per row of this head
   constexpr int NS = 2 / GPR;        // scores per lane per chunk (lane owns groups 2L, 2L+1)
-  constexpr int HPB = 4 / WPH;       // heads per workgroup
+  constexpr int NW = block_waves(WPH), HPB = NW / WPH;   // waves, heads per workgroup
   __shared__ __attribute__((aligned(16))) half_t sm_q[HPB * DH];
-  __shared__ float sm_m[4], sm_l[4];
-  __shared__ float sm_o[WPH > 1 ? 4 * DH : 1];
+  __shared__ float sm_m[NW], sm_l[NW];
+  __shared__ float sm_o[WPH > 1 ? NW * DH : 1];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -261,13 +263,8 @@ __global__ __launch_bounds__(256, 3) void attn_decode_q4_kernel(AttnArgs a) {
   // ---- reduce inside the wave: lanes with the same head-dimension range add up
 #pragma unroll
   for (int e = 0; e < 32; ++e) {
-    float v = o[e];
-    v += __shfl_xor(v, 1, 64);
-    v += __shfl_xor(v, 2, 64);
-    v += __shfl_xor(v, 4, 64);
-    v += __shfl_xor(v, 8, 64);
-    if (DH == 64) v += __shfl_xor(v, 32, 64);
-    o[e] = v;
+    const float v = row16_reduce(o[e], OpAdd());
+    o[e] = DH == 64 ? xor32_reduce(v, OpAdd()) : v;
   }
   const float lw = wave_sum(l_run);
   const float mt0 = wave_sum(mterm[0]), mt1 = wave_sum(mterm[1]);
@@ -306,12 +303,12 @@ __global__ __launch_bounds__(256, 3) void attn_decode_q4_kernel(AttnArgs a) {
 // PAGED: a chunk of 64 rows is exactly one page of the sequence (FG_PAGE_ROWS = 64), found through the
 // page table; every sequence has its own length.
 template <int DH, int WPH, bool PAGED = false>
-__global__ __launch_bounds__(256) void attn_decode_f16_kernel(AttnArgs a) {
+__global__ __launch_bounds__(64 * block_waves(WPH)) void attn_decode_f16_kernel(AttnArgs a) {
   constexpr int NU = DH / 32;        // 32-wide head-dimension blocks
-  constexpr int HPB = 4 / WPH;       // heads per workgroup
+  constexpr int NW = block_waves(WPH), HPB = NW / WPH;   // waves, heads per workgroup
   __shared__ __attribute__((aligned(16))) half_t sm_q[HPB * DH];
-  __shared__ float sm_m[4], sm_l[4];
-  __shared__ float sm_o[WPH > 1 ? 4 * DH : 1];
+  __shared__ float sm_m[NW], sm_l[NW];
+  __shared__ float sm_o[WPH > 1 ? NW * DH : 1];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -429,14 +426,7 @@ __global__ __launch_bounds__(256) void attn_decode_f16_kernel(AttnArgs a) {
   }
 
 #pragma unroll
-  for (int e = 0; e < 8 * NU; ++e) {
-    float v = o[e];
-    v += __shfl_xor(v, 1, 64);
-    v += __shfl_xor(v, 2, 64);
-    v += __shfl_xor(v, 4, 64);
-    v += __shfl_xor(v, 8, 64);
-    o[e] = v;
-  }
+  for (int e = 0; e < 8 * NU; ++e) o[e] = row16_reduce(o[e], OpAdd());
   const float lw = wave_sum(l_run);
   half_t* out0 = a.out + (int64_t)hid0 * DH;
   if (WPH == 1) {
@@ -467,17 +457,27 @@ __global__ __launch_bounds__(256) void attn_decode_f16_kernel(AttnArgs a) {
 
 }  // namespace
 
-// Waves per (sequence, head): 1, 2 or 4.  A stream of c chunks costs a wave ceil(c / WPH) chunk times
-// plus the merge, so one wave per head wastes the least, and measured it is the fastest from a few
-// thousand heads up even where the launch is only one or two rounds of workgroups (4096 heads x 528
-// rows: 4.6 / 4.4 / 4.2 TB/s with 1 / 2 / 4 waves per head; 13824 heads: 5.4 / 4.9 / 4.3).  Fewer
-// heads than that get more waves each, so that the chip is not left empty, but never more waves than
-// the stream has chunks.
-static int pick_waves_per_head(int64_t heads, int rows, int rows_per_chunk) {
-  const int chunks = (rows + rows_per_chunk - 1) / rows_per_chunk;
-  int wph = heads >= 2048 ? 1 : (heads >= 1024 ? 2 : 4);
+// Waves per (sequence, head).  A wave pays its ramp (query set-up, first loads, reduction over lanes, merge) once
+// and a chunk time per chunk; few chunks per wave make the ramp weigh, many make the launch uneven and leave SIMDs
+// without work.  Measured, us, with 1 / 2 / 4 / 8 waves per head (4-bit cache unless said; chunks of 64 rows at head
+// size 128):
+//   9 chunks   96 x 36 heads 64 / 59 / 57 / 91; 96 x 144 214 / 211 / 194 / 321; 32 x 128 70 / 69 / 65 / 105
+//   12         56 x 37 59 / 52 / 49 / 68                24   96 x 144 566 / 551 / 543 / 592
+//   5          96 x 144 127 / 119 / 136 / 268           4    32 x 128 30.0 / 31.5 / 33.5 / 67
+//   2          96 x 80 31 / 33 / 46 / 104
+//   FP16 cache 2 chunks 96 x 80 74 / 70 / 83; 4 chunks 32 x 128 81 / 78 / 76; 5 chunks 96 x 144 355 / 348 / 336;
+//              12 chunks 56 x 37 171 / 150 / 140 / 145
+// and where the heads are too few for the chip
+//   22 chunks  32 heads 37 / 21 / 13.8 / 11.2           16   160 heads 28 / 17.5 / 12.2 / 10.9
+//   10         256 heads 19.7 / 13.3 / 11.2 / 10.0, 448 heads 20 / 15 / 14.3 / 16.8
+//   5          160 heads 12 / 9 / 7.5 / 7.0             FP16, 22 chunks, 32 heads 79 / 42 / 23.1 / 23.4
+static int pick_waves_per_head(int64_t heads, int chunks, bool q4) {
+  if (q4 && heads <= 256 && chunks >= 5) return 8;
+  const int by_length = q4 ? (chunks >= 7 ? 4 : (chunks >= 5 ? 2 : 1)) : (chunks >= 4 ? 4 : (chunks >= 2 ? 2 : 1));
+  const int by_heads = heads >= 2048 ? 1 : (heads >= 1024 ? 2 : 4);   // never more waves than chunks for these
+  int wph = by_heads;
   while (wph > 1 && chunks < wph) wph >>= 1;
-  return wph;
+  return wph > by_length ? wph : by_length;
 }
 
 int decode_attention_launch(const fg_model_cfg& cfg, const half_t* q, int64_t q_stride, int32_t b,
@@ -504,8 +504,8 @@ int decode_attention_launch(const fg_model_cfg& cfg, const half_t* q, int64_t q_
   const int64_t heads = (int64_t)b * cfg.nh;
   const bool q4 = kv.dtype == FG_Q4G64 || kv.dtype == FG_Q4G64_H16;
   const bool h16 = kv.dtype == FG_Q4G64_H16;
-  const int wph = pick_waves_per_head(heads, rows, q4 ? 8192 / dh : 64);
-  const dim3 grid((unsigned)ceil_div(heads * wph, 4));
+  const int wph = pick_waves_per_head(heads, (int)ceil_div(rows, q4 ? 8192 / dh : 64), q4);
+  const dim3 grid((unsigned)ceil_div(heads * wph, block_waves(wph)));
   ProfScope prof(FG_K_ATTN_DECODE, stream);
 #define FG_ATTN_LAUNCH(DH_, ...)                                                                      \
   do {                                                                                                \
@@ -513,8 +513,10 @@ int decode_attention_launch(const fg_model_cfg& cfg, const half_t* q, int64_t q_
       hipLaunchKernelGGL((__VA_ARGS__<DH_, 1 FG_ATTN_EXTRA>), grid, dim3(256), 0, stream, a);         \
     else if (wph == 2)                                                                                \
       hipLaunchKernelGGL((__VA_ARGS__<DH_, 2 FG_ATTN_EXTRA>), grid, dim3(256), 0, stream, a);         \
-    else                                                                                              \
+    else if (wph == 4)                                                                                \
       hipLaunchKernelGGL((__VA_ARGS__<DH_, 4 FG_ATTN_EXTRA>), grid, dim3(256), 0, stream, a);         \
+    else                                                                                              \
+      hipLaunchKernelGGL((__VA_ARGS__<DH_, 8 FG_ATTN_EXTRA>), grid, dim3(512), 0, stream, a);         \
   } while (0)
   if (q4 && h16) {
 #define FG_ATTN_EXTRA , true
@@ -531,12 +533,17 @@ int decode_attention_launch(const fg_model_cfg& cfg, const half_t* q, int64_t q_
       FG_ATTN_LAUNCH(64, attn_decode_q4_kernel);
 #undef FG_ATTN_EXTRA
   } else {
-#define FG_ATTN_EXTRA
-    if (dh == 128)
-      FG_ATTN_LAUNCH(128, attn_decode_f16_kernel);
-    else
-      FG_ATTN_LAUNCH(64, attn_decode_f16_kernel);
-#undef FG_ATTN_EXTRA
+#define FG_ATTN_F16(DH_)                                                                              \
+  do {                                                                                                \
+    if (wph == 1)                                                                                     \
+      hipLaunchKernelGGL((attn_decode_f16_kernel<DH_, 1>), grid, dim3(256), 0, stream, a);            \
+    else if (wph == 2)                                                                                \
+      hipLaunchKernelGGL((attn_decode_f16_kernel<DH_, 2>), grid, dim3(256), 0, stream, a);            \
+    else                                                                                              \
+      hipLaunchKernelGGL((attn_decode_f16_kernel<DH_, 4>), grid, dim3(256), 0, stream, a);            \
+  } while (0)
+    if (dh == 128) FG_ATTN_F16(128); else FG_ATTN_F16(64);
+#undef FG_ATTN_F16
   }
 #undef FG_ATTN_LAUNCH
   FG_LAUNCH_CHECK();
@@ -572,8 +579,10 @@ int decode_attention_paged_launch(const fg_model_cfg& cfg, const half_t* q, int6
   const int64_t heads = (int64_t)b * cfg.nh;
   // as in the contiguous launch, with the longest sequence the page table can address standing in for the
   // lengths, which only the device knows
-  const int wph = pick_waves_per_head(heads, seqs.table_stride * FG_PAGE_ROWS, pages.dtype == FG_F16 ? 64 : 8192 / dh);
-  const dim3 grid((unsigned)ceil_div(heads * wph, 4));
+  const int64_t longest = (int64_t)seqs.table_stride * FG_PAGE_ROWS;
+  const bool q4 = pages.dtype != FG_F16;
+  const int wph = pick_waves_per_head(heads, (int)ceil_div(longest, q4 ? 8192 / dh : 64), q4);
+  const dim3 grid((unsigned)ceil_div(heads * wph, block_waves(wph)));
   const bool h16 = pages.dtype == FG_Q4G64_H16;
   ProfScope prof(FG_K_ATTN_DECODE, stream);
   if (pages.dtype == FG_F16) {
@@ -591,18 +600,23 @@ int decode_attention_paged_launch(const fg_model_cfg& cfg, const half_t* q, int6
     FG_LAUNCH_CHECK();
     return FG_OK;
   }
-#define FG_PAGED_LAUNCH(DH_, WPH_)                                                                          \
-  do {                                                                                                      \
-    if (h16)                                                                                                \
-      hipLaunchKernelGGL((attn_decode_q4_kernel<DH_, WPH_, true, true>), grid, dim3(256), 0, stream, a);    \
-    else                                                                                                    \
-      hipLaunchKernelGGL((attn_decode_q4_kernel<DH_, WPH_, false, true>), grid, dim3(256), 0, stream, a);   \
+#define FG_PAGED_LAUNCH(DH_, WPH_)                                                                                \
+  do {                                                                                                            \
+    const dim3 block(64 * block_waves(WPH_));                                                                     \
+    if (h16)                                                                                                      \
+      hipLaunchKernelGGL((attn_decode_q4_kernel<DH_, WPH_, true, true>), grid, block, 0, stream, a);              \
+    else                                                                                                          \
+      hipLaunchKernelGGL((attn_decode_q4_kernel<DH_, WPH_, false, true>), grid, block, 0, stream, a);             \
   } while (0)
-  if (dh == 128) {
-    if (wph == 1) FG_PAGED_LAUNCH(128, 1); else if (wph == 2) FG_PAGED_LAUNCH(128, 2); else FG_PAGED_LAUNCH(128, 4);
-  } else {
-    if (wph == 1) FG_PAGED_LAUNCH(64, 1); else if (wph == 2) FG_PAGED_LAUNCH(64, 2); else FG_PAGED_LAUNCH(64, 4);
-  }
+#define FG_PAGED_WPH(DH_)                                                                                         \
+  do {                                                                                                            \
+    if (wph == 1) FG_PAGED_LAUNCH(DH_, 1);                                                                        \
+    else if (wph == 2) FG_PAGED_LAUNCH(DH_, 2);                                                                   \
+    else if (wph == 4) FG_PAGED_LAUNCH(DH_, 4);                                                                   \
+    else FG_PAGED_LAUNCH(DH_, 8);                                                                                 \
+  } while (0)
+  if (dh == 128) FG_PAGED_WPH(128); else FG_PAGED_WPH(64);
+#undef FG_PAGED_WPH
 #undef FG_PAGED_LAUNCH
   FG_LAUNCH_CHECK();
   return FG_OK;

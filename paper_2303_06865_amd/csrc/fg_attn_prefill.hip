@@ -199,7 +199,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PrefillAttnArgs a)
       for (int j = 0; j < NKB; ++j)
 #pragma unroll
         for (int r = 0; r < 16; ++r) cmax = fmaxf(cmax, t[j][r]);
-      cmax = fmaxf(cmax, __shfl_xor(cmax, 32, 64)) * c2;   // scale > 0: the maximum commutes with it
+      cmax = xor32_reduce(cmax, OpMax()) * c2;   // scale > 0: the maximum commutes with it
       const float m_new = fmaxf(m_run, cmax);
       // every key of a processed tile may still be masked for the clamped duplicate rows beyond s:
       // guard the exponent
@@ -243,7 +243,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PrefillAttnArgs a)
         }
     }
 
-    l_run += __shfl_xor(l_run, 32, 64);
+    l_run = xor32_reduce(l_run, OpAdd());
     if (my_q < a.s) {
       const float inv = 1.0f / l_run;
       half_t* orow = a.out + ((int64_t)cur.seq * a.s + my_q) * a.h1 + cur.head * DH;

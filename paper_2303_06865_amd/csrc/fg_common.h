@@ -137,15 +137,48 @@ int check_kv(const fg_model_cfg* cfg, const fg_kv_cache* kv);
 // ---- device helpers -------------------------------------------------------------------------
 #if defined(__HIPCC__)
 
+// Reductions over lanes, without LDS: inside 16 lanes the partner's value is a DPP operand, across the four rows
+// of 16 it comes from v_permlane16_swap / v_permlane32_swap.  (ds_bpermute, which __shfl_xor becomes, is an LDS
+// round trip per step, and six of them in a chain are most of what a short attention stream or a normalised row
+// waits for.)
+template <int CTRL>
+__device__ __forceinline__ float dpp_f32(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
+}
+// quad_perm 1032 and 2301; lanes reversed inside 8 and inside 16: once the quads (the eights) are uniform, the
+// mirror brings the other quad's (the other eight's) value
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppHalfMirror = 0x141, kDppMirror = 0x140;
+
+template <class Op>
+__device__ __forceinline__ float row16_reduce(float v, Op op) {   // over each 16 lanes, result in all of them
+  v = op(v, dpp_f32<kDppXor1>(v));
+  v = op(v, dpp_f32<kDppXor2>(v));
+  v = op(v, dpp_f32<kDppHalfMirror>(v));
+  return op(v, dpp_f32<kDppMirror>(v));
+}
+template <class Op>
+__device__ __forceinline__ float xor16_reduce(float v, Op op) {
+  const uint32_t b = __builtin_bit_cast(uint32_t, v);
+  const auto s = __builtin_amdgcn_permlane16_swap(b, b, false, false);
+  return op(__builtin_bit_cast(float, (uint32_t)s[0]), __builtin_bit_cast(float, (uint32_t)s[1]));
+}
+template <class Op>
+__device__ __forceinline__ float xor32_reduce(float v, Op op) {
+  const uint32_t b = __builtin_bit_cast(uint32_t, v);
+  const auto s = __builtin_amdgcn_permlane32_swap(b, b, false, false);
+  return op(__builtin_bit_cast(float, (uint32_t)s[0]), __builtin_bit_cast(float, (uint32_t)s[1]));
+}
+struct OpMax {
+  __device__ __forceinline__ float operator()(float a, float b) const { return fmaxf(a, b); }
+};
+struct OpAdd {
+  __device__ __forceinline__ float operator()(float a, float b) const { return a + b; }
+};
 __device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-  return v;
+  return xor32_reduce(xor16_reduce(row16_reduce(v, OpMax()), OpMax()), OpMax());
 }
 __device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
+  return xor32_reduce(xor16_reduce(row16_reduce(v, OpAdd()), OpAdd()), OpAdd());
 }
 
 // Unpack one 32-bit word of eight 4-bit codes c0..c7 (c0 in the lowest nibble) into four FP16

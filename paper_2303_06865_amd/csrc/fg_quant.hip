@@ -16,12 +16,6 @@ namespace fg {
 // kept to seven instructions: the extrema are taken on FP16 pairs (FP16 -> binary32 is exact and monotone) and
 // exchanged between the eight lanes with DPP operands, x - min is one mixed-precision FMA, and the codes are
 // converted and gathered a byte at a time.
-template <int CTRL>
-__device__ __forceinline__ float dpp_f32(float v) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
-}
-constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppHalfMirror = 0x141;   // quad_perm 1032 / 2301; reversed inside 8 lanes
-
 template <bool H16>
 __device__ __forceinline__ void quantize_group_8lanes(const h8_t v, uint32_t& packed, float& mn_out,
                                                       float& scale_out) {

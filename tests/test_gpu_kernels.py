@@ -397,6 +397,20 @@ def test_decode_attention_many_heads(b, nh, dh, rows, quant):
     assert_close(got, ref, "decode attention b=%d nh=%d dh=%d rows=%d q=%s" % (b, nh, dh, rows, quant))
 
 
+@pytest.mark.parametrize("b,nh,dh,rows,quant", [
+    (41, 51, 128, 330, True),     # 2091 heads of six chunks: two waves per head
+    (41, 51, 128, 450, True),     # ... of eight: four
+    (41, 51, 64, 130, False),     # FP16 cache, three chunks: two waves per head
+    (41, 51, 64, 200, False),     # four chunks: four
+    (17, 15, 128, 260, True),     # 255 heads of five chunks: eight waves per head
+    (16, 16, 64, 1030, True),     # 256 heads of nine chunks, one of them for a single wave
+    (257, 1, 128, 321, True),     # 257 heads: four waves per head again
+])
+def test_decode_attention_waves_per_head_by_length(b, nh, dh, rows, quant):
+    got, ref = _decode_attn_case(nh, dh, quant, rows, b=b, batch=b, boff=0, seed=b + rows)
+    assert_close(got, ref, "decode attention b=%d nh=%d dh=%d rows=%d q=%s" % (b, nh, dh, rows, quant))
+
+
 @pytest.mark.parametrize("b,nh,dh,rows,meta_f16", [
     (51, 72, 64, 70, False),     # 3672 heads
     (57, 75, 64, 130, True),     # 4275 heads, the last workgroup has three of its four waves busy
