@@ -1,5 +1,7 @@
 // Row-wise kernels around the projections: LayerNorm (OPT pre-LN placement), token + position
 // embedding, and the greedy argmax over logits.  All are HBM/L2-bound streaming kernels.
+#include <type_traits>
+
 #include "fg_common.h"
 
 namespace fg {
@@ -177,15 +179,16 @@ __global__ __launch_bounds__(256) void embed_ragged_kernel(const half_t* __restr
 
 // Greedy token: argmax over a row of binary32 logits, lowest index on ties.
 // Row r's result goes to out[r * out_stride], or to out[out_index[r]] when out_index is given.
-// One workgroup per row, so with few rows the time is that of one CU taking in a row: sixteen waves with four
-// 16-byte loads each in flight: 8 us for 4 rows of 50272 logits and 14 us for 128 of them (256 threads with one 4-byte
-// load each, a load latency per 1 KiB: 59 and 64 us).  VEC: the rows start on 16-byte boundaries.
+// One workgroup per row, so with few rows the time is that of one CU taking in a row: sixteen waves with
+// sixteen 16-byte loads each in flight (rows of up to 65536 in one go): 7.0 us for 4 rows of 50272 logits and 9.2 us
+// for 128 of them (with four loads each 8.7 and 10.1; 256 threads with one 4-byte load each 59 and 64).  VEC: the
+// rows start on 16-byte boundaries.
 constexpr int kArgmaxThreads = 1024;
 template <bool VEC>
 __global__ __launch_bounds__(kArgmaxThreads) void argmax_kernel(const float* __restrict__ logits, int64_t cols,
                                                                 int32_t* __restrict__ out, int64_t out_stride,
                                                                 const int32_t* __restrict__ out_index) {
-  constexpr int NW = kArgmaxThreads / 64, kW = VEC ? 4 : 1, kLoads = 4;
+  constexpr int NW = kArgmaxThreads / 64, kW = VEC ? 4 : 1, kLoads = 16;
   __shared__ float bv[NW];
   __shared__ int bi[NW];
   const float* r = logits + (int64_t)blockIdx.x * cols;
@@ -219,17 +222,33 @@ __global__ __launch_bounds__(kArgmaxThreads) void argmax_kernel(const float* __r
       idx = oi;
     }
   };
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) merge(__shfl_xor(best, o, 64), __shfl_xor(idx, o, 64));
+  auto merge_dpp = [&](auto CTRL_) {
+    constexpr int ctrl = decltype(CTRL_)::value;
+    merge(dpp_f32<ctrl>(best), __builtin_amdgcn_update_dpp(0, idx, ctrl, 0xF, 0xF, true));
+  };
+  auto merge_row16 = [&]() {
+    merge_dpp(std::integral_constant<int, kDppXor1>{});
+    merge_dpp(std::integral_constant<int, kDppXor2>{});
+    merge_dpp(std::integral_constant<int, kDppHalfMirror>{});
+    merge_dpp(std::integral_constant<int, kDppMirror>{});
+  };
+  merge_row16();
+  merge(__shfl_xor(best, 16, 64), __shfl_xor(idx, 16, 64));
+  merge(__shfl_xor(best, 32, 64), __shfl_xor(idx, 32, 64));
   if ((threadIdx.x & 63) == 0) {
     bv[threadIdx.x >> 6] = best;
     bi[threadIdx.x >> 6] = idx;
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int k = 1; k < NW; ++k) merge(bv[k], bi[k]);
-    const int64_t dst = out_index ? (int64_t)out_index[blockIdx.x] : (int64_t)blockIdx.x * out_stride;
-    out[dst] = idx == 0x7fffffff ? 0 : idx;
+  static_assert(NW == 16, "one DPP row merges the waves");
+  if (threadIdx.x < 64) {
+    best = bv[threadIdx.x & 15];
+    idx = bi[threadIdx.x & 15];
+    merge_row16();
+    if (threadIdx.x == 0) {
+      const int64_t dst = out_index ? (int64_t)out_index[blockIdx.x] : (int64_t)blockIdx.x * out_stride;
+      out[dst] = idx == 0x7fffffff ? 0 : idx;
+    }
   }
 }
 
