@@ -1235,31 +1235,35 @@ __global__ __launch_bounds__(512) void gemm_decode16x2_kernel(StreamArgs a) {
 //     ks + 5 (weights), A operands of the next step's first phase.
 //   Copies are issued weights first, then activations, so that the one vmcnt count that guarantees the
 //   activations of step ks + 1 also covers the weights of step ks + 2.
-constexpr int kP16AStages = 3, kP16WSlots = 5, kP16Rows = 256;
-constexpr int kP16AStage = kP16Rows * kKS * 2;
-constexpr int kP16WBase = kP16AStages * kP16AStage;
-constexpr int kP16Lds = kP16WBase + kP16WSlots * kBStageQ4;
-constexpr int kP16Copies = 6;   // per wave per K step: codes, {min, scale}, four 8-row activation pieces
-static_assert(kP16Lds <= kLdsBytes, "stages must fit in LDS");
+// RG = groups of 64 rows in the tile: 4 (256 rows, as described) or 3 (192 rows, six phases of the same kind).
+constexpr int kP16AStages = 3, kP16WSlots = 5;
+template <int RG>
+struct P16Cfg {
+  static constexpr int kRows = 64 * RG, kPhases = 2 * RG;
+  static constexpr int kAStage = kRows * kKS * 2, kWBase = kP16AStages * kAStage;
+  static constexpr int kLds = kWBase + kP16WSlots * kBStageQ4;
+  static constexpr int kCopies = 2 + RG;   // per wave per K step: codes, {min, scale}, RG 8-row activation pieces
+  static_assert(kLds <= kLdsBytes, "stages must fit in LDS");
+  // position (MFMA number within the K step, 0 .. 16 RG - 1) behind which dequantization piece p of 14 goes: slice 1
+  // of this step over the first half, slice 0 of the next step over what follows the phase that reads its code words
+  static constexpr int pos_cur(int p) { return p * (8 * RG - 2) / 14; }
+  static constexpr int pos_nxt(int p) { return RG == 4 ? 41 + p * 21 / 14 : 33 + p * 11 / 14; }
+  // slice 1's operands are first used by MFMA 8 RG, the next step's slice 0 operands by MFMA 16 RG (= 0 of the next
+  // step), and the code words they are made from land with the wait that ends phase RG (behind MFMA 8 RG + 7): a
+  // piece writes an operand register at least three MFMAs before the first MFMA that reads it
+  static_assert(pos_cur(13) <= 8 * RG - 4 && pos_nxt(0) > 8 * RG + 7 && pos_nxt(13) <= 16 * RG - 4, "dequantization windows");
+};
 
-// position (MFMA number within the K step, 0..63) behind which dequantization piece p of 14 goes: slice 1 of
-// this step over MFMAs 0..29, slice 0 of the next step over MFMAs 41..61
-constexpr int p16_pos_cur(int p) { return p * 30 / 14; }
-constexpr int p16_pos_nxt(int p) { return 41 + p * 21 / 14; }
-// slice 1's operands are first used by MFMA 32, the next step's slice 0 operands by MFMA 64 (= 0 of the next
-// step), and the code words they are made from land with the wait that ends phase 4 (behind MFMA 39): a
-// piece writes an operand register at least three MFMAs before the first MFMA that reads it
-static_assert(p16_pos_cur(13) <= 32 - 4 && p16_pos_nxt(0) > 39 && p16_pos_nxt(13) <= 64 - 4, "dequantization windows");
-
-// What both prefill kernels on 16 x 16 x 32 MFMAs do with a finished segment of a 256 x 256 tile: acc[m][ct]
+// What both prefill kernels on 16 x 16 x 32 MFMAs do with a finished segment of a 64 RG x 256 tile: acc[m][ct]
 // of wave w holds rows 16 m + 4 g4 + 0..3 of column 32 w + 16 ct + l16.
-__device__ __forceinline__ void prefill16_finish_tile(const StreamArgs& a, f4_t (&acc)[16][2], bool full, int m0, int nt0, int part,
+template <int RG>
+__device__ __forceinline__ void prefill16_finish_tile(const StreamArgs& a, f4_t (&acc)[4 * RG][2], bool full, int m0, int nt0, int part,
                                                       int seg, int wave, int l16, int g4) {
   // The MFMAs are opaque instructions to the compiler: wait out the last of them (16 cycles each)
   // before the accumulators are read.
   __asm__ volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");
 #pragma unroll
-  for (int m = 0; m < 16; ++m)
+  for (int m = 0; m < 4 * RG; ++m)
 #pragma unroll
     for (int ct = 0; ct < 2; ++ct) __asm__ volatile("" : "+v"(acc[m][ct]));
   // ---- epilogue: lane holds column l16 of each 16 x 16 tile, rows 4 * g4 + 0..3.  Neighbouring lanes
@@ -1275,7 +1279,7 @@ __device__ __forceinline__ void prefill16_finish_tile(const StreamArgs& a, f4_t 
       int row = m0 + 4 * g4;
       int64_t o_off = (int64_t)row * a.ldo + cs, r_off = (int64_t)row * a.ldr + cs;
 #pragma unroll
-      for (int m = 0; m < 16; ++m) {
+      for (int m = 0; m < 4 * RG; ++m) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           float x0 = acc[m][0][r] + b0, x1 = acc[m][1][r] + b1;
@@ -1306,12 +1310,12 @@ __device__ __forceinline__ void prefill16_finish_tile(const StreamArgs& a, f4_t 
       }
     }
   } else {
-    // Partial sums in the layout of gemm_stream_kernel<8, 1, 1, 8> (its reduction pass finishes these
+    // Partial sums in the layout of gemm_stream_kernel<2 RG, 1, 1, 8> (its reduction pass finishes these
     // tiles too): float4 number (2 m + g4 / 2) of "thread" 64 wave + 32 (g4 % 2) + 16 ct + l16 holds
     // rows 16 m + 4 g4 + 0..3 of column 32 wave + 16 ct + l16.
-    float4* base = reinterpret_cast<float4*>(a.partial + ((int64_t)part * 2 + (seg == 0 ? 0 : 1)) * ((int64_t)kP16Rows * kBN));
+    float4* base = reinterpret_cast<float4*>(a.partial + ((int64_t)part * 2 + (seg == 0 ? 0 : 1)) * ((int64_t)(64 * RG) * kBN));
 #pragma unroll
-    for (int m = 0; m < 16; ++m)
+    for (int m = 0; m < 4 * RG; ++m)
 #pragma unroll
       for (int ct = 0; ct < 2; ++ct) {
         if (m0 + 16 * m + 8 * (g4 >> 1) < a.M)   // rows beyond M: padding, never read back
@@ -1321,8 +1325,9 @@ __device__ __forceinline__ void prefill16_finish_tile(const StreamArgs& a, f4_t 
   }
 }
 
-template <bool H16M>
+template <int RG, bool H16M>
 __global__ __launch_bounds__(512) void gemm_prefill16_kernel(StreamArgs a) {
+  using C = P16Cfg<RG>;
   constexpr int NW = 8, RH = 4;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
 
@@ -1341,9 +1346,9 @@ __global__ __launch_bounds__(512) void gemm_prefill16_kernel(StreamArgs a) {
 #pragma unroll
   for (int sl = 0; sl < 2; ++sl) a_off[sl] = (l16 * kKS + swz(l16, 4 * sl + g4) * 8) * 2;
   // code word of (column tile ct, slice sl) in a weight slot: + ct * 256 + sl * 512
-  const int bq_off = kP16WBase + wave * 1024 + l16 * 16 + g4 * 4;
+  const int bq_off = C::kWBase + wave * 1024 + l16 * 16 + g4 * 4;
   // {min, scale} of column tile ct: + ct * 16 * (H16M ? 4 : 8)
-  const int bm_off = kP16WBase + 8 * 1024 + wave * 256 + l16 * (H16M ? 4 : 8);
+  const int bm_off = C::kWBase + 8 * 1024 + wave * 256 + l16 * (H16M ? 4 : 8);
   const uint32_t lds0 = (uint32_t)(uintptr_t)(lptr_t)smem;
 
   while (round < a.rounds || pos < rem_end) {
@@ -1363,19 +1368,19 @@ __global__ __launch_bounds__(512) void gemm_prefill16_kernel(StreamArgs a) {
     }
     int mblk, n_tile;
     tile_coords(tile, a.m_blocks, a.n_tiles, mblk, n_tile);
-    const int m0 = mblk * kP16Rows;
+    const int m0 = mblk * C::kRows;
     const int nt0 = n_tile * 8 + wave;   // this wave's 32-column weight tile
 
-    f4_t acc[16][2];
+    f4_t acc[4 * RG][2];
 #pragma unroll
-    for (int m = 0; m < 16; ++m)
+    for (int m = 0; m < 4 * RG; ++m)
 #pragma unroll
       for (int ct = 0; ct < 2; ++ct) acc[m][ct] = (f4_t){0.f, 0.f, 0.f, 0.f};
 
-    // this wave's four activation pieces per step: piece c = wave + 8 i covers rows 8 c .. 8 c + 7
-    const half_t* a_src[4];
+    // this wave's RG activation pieces per step: piece c = wave + 8 i covers rows 8 c .. 8 c + 7
+    const half_t* a_src[RG];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < RG; ++i) {
       const int c = wave + NW * i;
       const int prow = 8 * c + (lane >> 3);
       int row = m0 + prow;
@@ -1390,22 +1395,22 @@ __global__ __launch_bounds__(512) void gemm_prefill16_kernel(StreamArgs a) {
       m_src = reinterpret_cast<const float*>(a.meta) +
               (H16M ? (int64_t)nt * a.ksteps * 32 + (lane & 31) : (int64_t)nt * a.ksteps * 64 + lane);
     }
-    // copy c of step ks: 0 = codes, 1 = {min, scale} (into weight slot wslot), 2..5 = activation pieces
+    // copy c of step ks: 0 = codes, 1 = {min, scale} (into weight slot wslot), then activation pieces
     // (into stage).  Past the end of the segment the last step is fetched again: harmless, and it keeps
     // the VMEM counts uniform.
     auto copy_one = [&](int c, int ks_w, int wslot, int ks_a, int stage) {
       if (c == 0) {
         const int kc = ks_w < ks1 ? ks_w : ks1 - 1;
         __builtin_amdgcn_global_load_lds((gptr_t)(w_src + (int64_t)kc * 1024),
-                                         (lptr_t)(smem + kP16WBase + wslot * kBStageQ4 + wave * 1024), 16, 0, 0);
+                                         (lptr_t)(smem + C::kWBase + wslot * kBStageQ4 + wave * 1024), 16, 0, 0);
       } else if (c == 1) {
         const int kc = ks_w < ks1 ? ks_w : ks1 - 1;
         __builtin_amdgcn_global_load_lds((gptr_t)(m_src + (int64_t)kc * (H16M ? 32 : 64)),
-                                         (lptr_t)(smem + kP16WBase + wslot * kBStageQ4 + 8 * 1024 + wave * 256), 4, 0, 0);
+                                         (lptr_t)(smem + C::kWBase + wslot * kBStageQ4 + 8 * 1024 + wave * 256), 4, 0, 0);
       } else {
         const int kc = ks_a < ks1 ? ks_a : ks1 - 1;
         __builtin_amdgcn_global_load_lds((gptr_t)(a_src[c - 2] + kc * kKS),
-                                         (lptr_t)(smem + stage * kP16AStage + (wave + NW * (c - 2)) * 8 * kKS * 2), 16, 0, 0);
+                                         (lptr_t)(smem + stage * C::kAStage + (wave + NW * (c - 2)) * 8 * kKS * 2), 16, 0, 0);
       }
     };
 
@@ -1416,12 +1421,12 @@ __global__ __launch_bounds__(512) void gemm_prefill16_kernel(StreamArgs a) {
     uint32_t cmh[2];
     float s24, s20, mn;
     uint32_t msk[4], r01[2];
-    // A operands of phase q (slice q / 4, row tiles 4 (q % 4) .. + 3) of the stage at st
+    // A operands of phase q (slice q / RG, row tiles 4 (q % RG) .. + 3) of the stage at st
     auto read_a = [&](uint32_t st, auto Q_, h8_t* dst) {
       constexpr int q = decltype(Q_)::value;
-      const uint32_t ad = st + a_off[q >> 2];
+      const uint32_t ad = st + a_off[q / RG];
       static_for<0, RH>([&](auto M_) __attribute__((always_inline)) {
-        constexpr int off = ((q & 3) * RH + decltype(M_)::value) * 16 * kKS * 2;
+        constexpr int off = ((q % RG) * RH + decltype(M_)::value) * 16 * kKS * 2;
         dst[decltype(M_)::value] = __builtin_bit_cast(h8_t, lds_read128<off>(ad));
       });
     };
@@ -1496,8 +1501,8 @@ __global__ __launch_bounds__(512) void gemm_prefill16_kernel(StreamArgs a) {
 #pragma unroll
     for (int t = 0; t < 3; ++t)
 #pragma unroll
-      for (int c = 0; c < kP16Copies; ++c) copy_one(c, ks0 + 2 + t, 2 + t, ks0 + t, t);
-    __asm__ volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * kP16Copies) : "memory");   // weights ks0 .. ks0 + 2, activations ks0
+      for (int c = 0; c < C::kCopies; ++c) copy_one(c, ks0 + 2 + t, 2 + t, ks0 + t, t);
+    __asm__ volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * C::kCopies) : "memory");   // weights ks0 .. ks0 + 2, activations ks0
     __builtin_amdgcn_s_barrier();
     read_a(lds0, IdxC<0>{}, aop[0]);
     read_b(0);
@@ -1512,35 +1517,35 @@ __global__ __launch_bounds__(512) void gemm_prefill16_kernel(StreamArgs a) {
     for (int ks = ks0; ks < ks1; ++ks) {
       const int stage1 = stage + 1 == kP16AStages ? 0 : stage + 1;
       const int wslot1 = wslot + 1 == kP16WSlots ? 0 : wslot + 1;
-      const uint32_t At = lds0 + stage * kP16AStage;
-      static_for<0, 8>([&](auto Q_) __attribute__((always_inline)) {
+      const uint32_t At = lds0 + stage * C::kAStage;
+      static_for<0, C::kPhases>([&](auto Q_) __attribute__((always_inline)) {
         constexpr int q = decltype(Q_)::value;
-        constexpr int sl = q >> 2, cur = q & 1, nxt = cur ^ 1;
-        if constexpr (q < 7)
+        constexpr int sl = q / RG, cur = q & 1, nxt = cur ^ 1;
+        if constexpr (q < C::kPhases - 1)
           read_a(At, IdxC<q + 1>{}, aop[nxt]);
         else
-          read_a(lds0 + stage1 * kP16AStage, IdxC<0>{}, aop[nxt]);
-        if constexpr (q == 4) read_b(wslot1);
+          read_a(lds0 + stage1 * C::kAStage, IdxC<0>{}, aop[nxt]);
+        if constexpr (q == RG) read_b(wslot1);
         __builtin_amdgcn_sched_barrier(0);
         static_for<0, 2 * RH>([&](auto I) __attribute__((always_inline)) {
           constexpr int i = decltype(I)::value;
           constexpr int ct = i / RH, m = i - ct * RH, g = q * 8 + i;
-          mfma16_inplace_v(acc[(q & 3) * RH + m][ct], aop[cur][m], __builtin_bit_cast(h8_t, bop[sl][ct]));
+          mfma16_inplace_v(acc[(q % RG) * RH + m][ct], aop[cur][m], __builtin_bit_cast(h8_t, bop[sl][ct]));
           __builtin_amdgcn_sched_barrier(0);
           static_for<0, 14>([&](auto P_) __attribute__((always_inline)) {
             constexpr int pc = decltype(P_)::value;
-            if constexpr (p16_pos_cur(pc) == g) dq7(1, pc / 7, pc % 7);
-            if constexpr (p16_pos_nxt(pc) == g) dq7(0, pc / 7, pc % 7);
+            if constexpr (C::pos_cur(pc) == g) dq7(1, pc / 7, pc % 7);
+            if constexpr (C::pos_nxt(pc) == g) dq7(0, pc / 7, pc % 7);
           });
-          if constexpr (q == 7 && i < kP16Copies) copy_one(i, ks + kP16WSlots, wslot, ks + kP16AStages, stage);
+          if constexpr (q == C::kPhases - 1 && i < C::kCopies) copy_one(i, ks + kP16WSlots, wslot, ks + kP16AStages, stage);
           __builtin_amdgcn_sched_barrier(0);
         });
         lds_wait();
 #pragma unroll
         for (int m = 0; m < RH; ++m) lds_landed(aop[nxt][m]);
-        if constexpr (q == 4) landed_b();
-        if constexpr (q == 6) {
-          __asm__ volatile("s_waitcnt vmcnt(%0)" ::"n"(kP16Copies) : "memory");
+        if constexpr (q == RG) landed_b();
+        if constexpr (q == C::kPhases - 2) {
+          __asm__ volatile("s_waitcnt vmcnt(%0)" ::"n"(C::kCopies) : "memory");
           __builtin_amdgcn_s_barrier();   // bare barrier: no fence, the copies in flight stay in flight
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -1549,7 +1554,7 @@ __global__ __launch_bounds__(512) void gemm_prefill16_kernel(StreamArgs a) {
       wslot = wslot1;
     }
 
-    prefill16_finish_tile(a, acc, (ks0 == 0) && (ks1 == a.ksteps), m0, nt0, part, seg, wave, l16, g4);
+    prefill16_finish_tile<RG>(a, acc, (ks0 == 0) && (ks1 == a.ksteps), m0, nt0, part, seg, wave, l16, g4);
     if (whole_round) {
       ++round;
     } else {
@@ -1569,11 +1574,18 @@ __global__ __launch_bounds__(512) void gemm_prefill16_kernel(StreamArgs a) {
 // Phases as above; slice 1's B operands are read at the start of phase 2, the next step's slice 0 operands at
 // the start of the last phase, after the barrier.
 constexpr int kP16FWSlots = 2;
-constexpr int kP16FLds = kP16WBase + kP16FWSlots * kBStageF16;
-constexpr int kP16FCopies = 8;   // per wave per K step: four 8-row weight pieces, four 8-row activation pieces
-static_assert(kP16FLds <= kLdsBytes, "stages must fit in LDS");
+template <int RG>
+struct P16FCfg {
+  static constexpr int kRows = 64 * RG, kPhases = 2 * RG;
+  static constexpr int kAStage = kRows * kKS * 2, kWBase = kP16AStages * kAStage;
+  static constexpr int kLds = kWBase + kP16FWSlots * kBStageF16;
+  static constexpr int kCopies = 4 + RG;   // per wave per K step: four 8-row weight pieces, RG 8-row activation pieces
+  static_assert(kLds <= kLdsBytes, "stages must fit in LDS");
+};
 
+template <int RG>
 __global__ __launch_bounds__(512) void gemm_prefill16_f16_kernel(StreamArgs a) {
+  using C = P16FCfg<RG>;
   constexpr int NW = 8, RH = 4;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
 
@@ -1597,7 +1609,7 @@ __global__ __launch_bounds__(512) void gemm_prefill16_f16_kernel(StreamArgs a) {
 #pragma unroll
     for (int ct = 0; ct < 2; ++ct) {
       const int r = wave * 32 + ct * 16 + l16;
-      b_off[sl][ct] = kP16WBase + (r * kKS + swz(r, 4 * sl + g4) * 8) * 2;
+      b_off[sl][ct] = C::kWBase + (r * kKS + swz(r, 4 * sl + g4) * 8) * 2;
     }
   }
   const uint32_t lds0 = (uint32_t)(uintptr_t)(lptr_t)smem;
@@ -1619,43 +1631,46 @@ __global__ __launch_bounds__(512) void gemm_prefill16_f16_kernel(StreamArgs a) {
     }
     int mblk, n_tile;
     tile_coords(tile, a.m_blocks, a.n_tiles, mblk, n_tile);
-    const int m0 = mblk * kP16Rows;
+    const int m0 = mblk * C::kRows;
     const int nt0 = n_tile * 8 + wave;   // this wave's 32 columns, as a 32-column tile number
 
-    f4_t acc[16][2];
+    f4_t acc[4 * RG][2];
 #pragma unroll
-    for (int m = 0; m < 16; ++m)
+    for (int m = 0; m < 4 * RG; ++m)
 #pragma unroll
       for (int ct = 0; ct < 2; ++ct) acc[m][ct] = (f4_t){0.f, 0.f, 0.f, 0.f};
 
-    // this wave's four activation pieces per step: piece c = wave + 8 i covers rows 8 c .. 8 c + 7 of the tile;
+    // this wave's RG activation pieces per step: piece c = wave + 8 i covers rows 8 c .. 8 c + 7 of the tile;
     // its four weight pieces: rows (output columns) 32 wave + 8 i .. + 7 of the block
-    const half_t* a_src[4];
+    const half_t* a_src[RG];
     const uint8_t* w_src[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < RG; ++i) {
       const int c = wave + NW * i;
       const int prow = 8 * c + (lane >> 3);
       int row = m0 + prow;
       row = row < a.M ? row : a.M - 1;
       a_src[i] = a.x + (int64_t)row * a.ldx + swz(prow, lane & 7) * 8;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
       const int wrow = wave * 32 + 8 * i + (lane >> 3);
       int col = n_tile * kBN + wrow;
       col = col < a.N ? col : a.N - 1;   // ragged last column block: load valid data, never store it
       w_src[i] = a.w + ((int64_t)col * a.K + swz(wrow, lane & 7) * 8) * 2;
     }
-    // copy c of a step: 0..3 = weight pieces of step ks_w (into weight slot wslot), 4..7 = activation pieces
+    // copy c of a step: 0..3 = weight pieces of step ks_w (into weight slot wslot), then the activation pieces
     // of step ks_a (into stage).  Past the end of the segment the last step is fetched again: harmless, and it
     // keeps the VMEM counts uniform.
     auto copy_one = [&](int c, int ks_w, int wslot, int ks_a, int stage) {
       if (c < 4) {
         const int kc = ks_w < ks1 ? ks_w : ks1 - 1;
         __builtin_amdgcn_global_load_lds((gptr_t)(w_src[c] + (int64_t)kc * (kKS * 2)),
-                                         (lptr_t)(smem + kP16WBase + wslot * kBStageF16 + (wave * 4 + c) * 8 * kKS * 2), 16, 0, 0);
+                                         (lptr_t)(smem + C::kWBase + wslot * kBStageF16 + (wave * 4 + c) * 8 * kKS * 2), 16, 0, 0);
       } else {
         const int kc = ks_a < ks1 ? ks_a : ks1 - 1;
         __builtin_amdgcn_global_load_lds((gptr_t)(a_src[c - 4] + kc * kKS),
-                                         (lptr_t)(smem + stage * kP16AStage + (wave + NW * (c - 4)) * 8 * kKS * 2), 16, 0, 0);
+                                         (lptr_t)(smem + stage * C::kAStage + (wave + NW * (c - 4)) * 8 * kKS * 2), 16, 0, 0);
       }
     };
 
@@ -1663,9 +1678,9 @@ __global__ __launch_bounds__(512) void gemm_prefill16_f16_kernel(StreamArgs a) {
     u4_t bop[2][2];   // [slice][column tile]
     auto read_a = [&](uint32_t st, auto Q_, h8_t* dst) {
       constexpr int q = decltype(Q_)::value;
-      const uint32_t ad = st + a_off[q >> 2];
+      const uint32_t ad = st + a_off[q / RG];
       static_for<0, RH>([&](auto M_) __attribute__((always_inline)) {
-        constexpr int off = ((q & 3) * RH + decltype(M_)::value) * 16 * kKS * 2;
+        constexpr int off = ((q % RG) * RH + decltype(M_)::value) * 16 * kKS * 2;
         dst[decltype(M_)::value] = __builtin_bit_cast(h8_t, lds_read128<off>(ad));
       });
     };
@@ -1681,12 +1696,12 @@ __global__ __launch_bounds__(512) void gemm_prefill16_f16_kernel(StreamArgs a) {
     __syncthreads();
     // the copy groups of steps ks0 - 3 .. ks0 - 1, as the steady state would have issued them
 #pragma unroll
-    for (int c = 4; c < kP16FCopies; ++c) copy_one(c, 0, 0, ks0, 0);
+    for (int c = 4; c < C::kCopies; ++c) copy_one(c, 0, 0, ks0, 0);
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
-      for (int c = 0; c < kP16FCopies; ++c) copy_one(c, ks0 + t, t, ks0 + 1 + t, 1 + t);
-    __asm__ volatile("s_waitcnt vmcnt(%0)" ::"n"(12) : "memory");   // activations and weights of step ks0
+      for (int c = 0; c < C::kCopies; ++c) copy_one(c, ks0 + t, t, ks0 + 1 + t, 1 + t);
+    __asm__ volatile("s_waitcnt vmcnt(%0)" ::"n"(4 + 2 * RG) : "memory");   // activations and weights of step ks0
     __builtin_amdgcn_s_barrier();
     read_a(lds0, IdxC<0>{}, aop[0]);
     read_b(0, IdxC<0>{});
@@ -1700,24 +1715,24 @@ __global__ __launch_bounds__(512) void gemm_prefill16_f16_kernel(StreamArgs a) {
     for (int ks = ks0; ks < ks1; ++ks) {
       const int stage1 = stage + 1 == kP16AStages ? 0 : stage + 1;
       const int wslot1 = wslot ^ 1;
-      const uint32_t At = lds0 + stage * kP16AStage;
-      static_for<0, 8>([&](auto Q_) __attribute__((always_inline)) {
+      const uint32_t At = lds0 + stage * C::kAStage;
+      static_for<0, C::kPhases>([&](auto Q_) __attribute__((always_inline)) {
         constexpr int q = decltype(Q_)::value;
-        constexpr int sl = q >> 2, cur = q & 1, nxt = cur ^ 1;
-        if constexpr (q < 7)
+        constexpr int sl = q / RG, cur = q & 1, nxt = cur ^ 1;
+        if constexpr (q < C::kPhases - 1)
           read_a(At, IdxC<q + 1>{}, aop[nxt]);
         else
-          read_a(lds0 + stage1 * kP16AStage, IdxC<0>{}, aop[nxt]);
+          read_a(lds0 + stage1 * C::kAStage, IdxC<0>{}, aop[nxt]);
         if constexpr (q == 2) read_b(wslot, IdxC<1>{});
-        if constexpr (q == 7) read_b(wslot1, IdxC<0>{});
+        if constexpr (q == C::kPhases - 1) read_b(wslot1, IdxC<0>{});
         __builtin_amdgcn_sched_barrier(0);
         static_for<0, 2 * RH>([&](auto I) __attribute__((always_inline)) {
           constexpr int i = decltype(I)::value;
           constexpr int ct = i / RH, m = i - ct * RH;
-          mfma16_inplace_v(acc[(q & 3) * RH + m][ct], aop[cur][m], __builtin_bit_cast(h8_t, bop[sl][ct]));
+          mfma16_inplace_v(acc[(q % RG) * RH + m][ct], aop[cur][m], __builtin_bit_cast(h8_t, bop[sl][ct]));
           __builtin_amdgcn_sched_barrier(0);
           // (weights into the slot whose last operands were read at phase 2 of this step)
-          if constexpr (q == 7) copy_one(i, ks + kP16FWSlots, wslot, ks + kP16AStages, stage);
+          if constexpr (q == C::kPhases - 1 && i < C::kCopies) copy_one(i, ks + kP16FWSlots, wslot, ks + kP16AStages, stage);
           __builtin_amdgcn_sched_barrier(0);
         });
         lds_wait();
@@ -1727,13 +1742,13 @@ __global__ __launch_bounds__(512) void gemm_prefill16_f16_kernel(StreamArgs a) {
           lds_landed(bop[1][0]);
           lds_landed(bop[1][1]);
         }
-        if constexpr (q == 7) {
+        if constexpr (q == C::kPhases - 1) {
           lds_landed(bop[0][0]);
           lds_landed(bop[0][1]);
         }
-        if constexpr (q == 6) {
-          // outstanding may stay: the four activation pieces of step ks + 2 (issued last in step ks - 1)
-          __asm__ volatile("s_waitcnt vmcnt(%0)" ::"n"(4) : "memory");
+        if constexpr (q == C::kPhases - 2) {
+          // outstanding may stay: the RG activation pieces of step ks + 2 (issued last in step ks - 1)
+          __asm__ volatile("s_waitcnt vmcnt(%0)" ::"n"(RG) : "memory");
           __builtin_amdgcn_s_barrier();   // bare barrier: no fence, the copies in flight stay in flight
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -1742,7 +1757,7 @@ __global__ __launch_bounds__(512) void gemm_prefill16_f16_kernel(StreamArgs a) {
       wslot = wslot1;
     }
 
-    prefill16_finish_tile(a, acc, (ks0 == 0) && (ks1 == a.ksteps), m0, nt0, part, seg, wave, l16, g4);
+    prefill16_finish_tile<RG>(a, acc, (ks0 == 0) && (ks1 == a.ksteps), m0, nt0, part, seg, wave, l16, g4);
     if (whole_round) {
       ++round;
     } else {
@@ -1826,7 +1841,13 @@ struct Shape {
 Shape pick_shape(int64_t m) {
   // Up to two row blocks the side-by-side shape wins (few tiles: the 256-row shape would leave most of
   // its stream-K pieces short); beyond that the weights would be re-read too often.
-  if (m > 2 * kMaxMT * 32) return {8, 1, 1, 8};
+  // There, blocks of 192 rows where they leave at least a tenth fewer rows to pad to than blocks of 256 (321 .. 384,
+  // 513 .. 576, 1025 .. 1152 and 1281 .. 1344 rows).  Measured, us, 256 -> 192: 333 rows FP16 12288 x 4096 86 -> 70,
+  // 21504 x 7168 204 -> 181, tiled 78 -> 58 and 167 -> 131; 576 rows tiled 4096 x 16384 114 -> 94, 21504 x 7168
+  // 252 -> 198; 1152 rows tiled 153 -> 132 (12288 x 4096), 381 -> 352, FP16 7168 x 28672 596 -> 594.  With less to
+  // save it goes either way: 500 rows tiled 86 -> 80 (12288 x 4096) but 228 -> 242 (7168 x 28672), 1000 rows FP16
+  // 4096 x 16384 159 -> 191, tiled 314 -> 351 (21504 x 7168).
+  if (m > 2 * kMaxMT * 32) return {ceil_div(m, 192) * 192 * 10 <= ceil_div(m, 256) * 256 * 9 ? 6 : 8, 1, 1, 8};
   if (m > kMaxMT * 32) m = ceil_div(m, 2);
   const int need = (int)ceil_div(m, 32);
   return {need < 1 ? 1 : need, 2, 1, 4};
@@ -1879,29 +1900,37 @@ int launch_t(const StreamArgs& a, hipStream_t stream) {
 // Eight waves from five row tiles up (measured against four waves in one run, 144 rows: QKV 162-167 vs
 // 176-178 us, FFN1 210-218 vs 225-229, FFN2 219-221 vs 227-230; 112 rows 135-144 vs 151; level at 48 rows,
 // 3-7 % slower at 4 and 16 rows, where a wave has too few MFMAs per step to spread anything between).
-template <bool H16M>
+template <int RG, bool H16M>
 int launch_prefill16(const StreamArgs& a, hipStream_t stream) {
   static bool attr_done = false;
   if (!attr_done) {
-    FG_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_prefill16_kernel<H16M>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, kP16Lds));
+    FG_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_prefill16_kernel<RG, H16M>),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, P16Cfg<RG>::kLds));
     attr_done = true;
   }
-  hipLaunchKernelGGL((gemm_prefill16_kernel<H16M>), dim3(a.grid), dim3(512), kP16Lds, stream, a);
+  hipLaunchKernelGGL((gemm_prefill16_kernel<RG, H16M>), dim3(a.grid), dim3(512), P16Cfg<RG>::kLds, stream, a);
   FG_LAUNCH_CHECK();
   return FG_OK;
 }
 
+template <int RG>
 int launch_prefill16_f16(const StreamArgs& a, hipStream_t stream) {
   static bool attr_done = false;
   if (!attr_done) {
-    FG_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_prefill16_f16_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                               kP16FLds));
+    FG_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_prefill16_f16_kernel<RG>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                               P16FCfg<RG>::kLds));
     attr_done = true;
   }
-  hipLaunchKernelGGL(gemm_prefill16_f16_kernel, dim3(a.grid), dim3(512), kP16FLds, stream, a);
+  hipLaunchKernelGGL(gemm_prefill16_f16_kernel<RG>, dim3(a.grid), dim3(512), P16FCfg<RG>::kLds, stream, a);
   FG_LAUNCH_CHECK();
   return FG_OK;
+}
+
+template <int RG>
+int launch_prefill16_any(const StreamArgs& a, int dtype, hipStream_t stream) {
+  return dtype == FG_F16               ? launch_prefill16_f16<RG>(a, stream)
+         : dtype == FG_Q4G64_H16_TILED ? launch_prefill16<RG, true>(a, stream)
+                                       : launch_prefill16<RG, false>(a, stream);
 }
 
 template <int MT16, bool H16M>
@@ -1935,7 +1964,8 @@ size_t gemm_stream_workspace(int64_t n, int64_t k, int64_t m) {
   (void)n;
   (void)k;
   const Shape sh = pick_shape(m);
-  return (size_t)sh.grid() * 2 * sh.rows() * kBN * sizeof(float);
+  const int rows = sh.nw == 8 ? 256 : sh.rows();   // blocks of 192 rows need less, but are a choice among equals here
+  return (size_t)sh.grid() * 2 * rows * kBN * sizeof(float);
 }
 
 int gemm_stream_launch(const LinearArgs& la, void* ws, size_t ws_bytes, hipStream_t stream) {
@@ -1972,9 +2002,7 @@ int gemm_stream_launch(const LinearArgs& la, void* ws, size_t ws_bytes, hipStrea
   if (sh.nw == 8) {   // prefill shape: GEMM and reduction of the last partial round are one profile record
     ProfScope prof(FG_K_GEMM_LARGE_M, stream);
     if (la.dtype != FG_Q4G64_TILED && la.dtype != FG_Q4G64_H16_TILED && la.dtype != FG_F16) return FG_ERR_UNSUPPORTED;
-    const int rc = la.dtype == FG_F16               ? launch_prefill16_f16(a, stream)
-                   : la.dtype == FG_Q4G64_H16_TILED ? launch_prefill16<true>(a, stream)
-                                                    : launch_prefill16<false>(a, stream);
+    const int rc = sh.mt == 6 ? launch_prefill16_any<3>(a, la.dtype, stream) : launch_prefill16_any<4>(a, la.dtype, stream);
     if (rc) return rc;
     if (rem_tiles > 0) {
       return launch_stream_finish(a, sh, rem_tiles, stream);

@@ -50,3 +50,18 @@ def test_linear_shared_contraction(m, n, k, fmt):
     got = B.fg_linear(mat, bias, x, residual=res, relu=True)
     assert_close(got.cpu().numpy(), ref.cpu().numpy(), "shared contraction m=%d n=%d k=%d %s" % (m, n, k, fmt))
     assert torch.equal(B.fg_linear(mat, bias, x, residual=res, relu=True), got)
+
+
+@pytest.mark.parametrize("fmt", sorted(FORMATS))
+@pytest.mark.parametrize("m,n,k", [
+    (321, 32800, 64),      # two blocks of 192 rows: whole rounds of one K step, a last column block of 32
+    (384, 33024, 128),     # both blocks full, two K steps
+    (385, 16416, 192),     # one row more: blocks of 256 again
+    (513, 22112, 256),     # three blocks, one row in the last
+    (576, 22112, 448),     # whole rounds and a shared rest
+    (577, 8224, 512),
+    (1152, 11040, 320),
+    (1344, 9248, 192),
+])
+def test_linear_blocks_of_192_rows(m, n, k, fmt):
+    test_linear_shared_contraction(m, n, k, fmt)
