@@ -156,6 +156,13 @@ def test_layernorm(rows, cols):
     assert_close(host(out), ref, "layernorm", rel=5e-4, mabs=4e-3)
 
 
+@pytest.mark.parametrize("rows,cols", [(256, 8), (257, 4096), (256, 2048), (3, 2056), (2, 4096), (256, 8192), (2, 8200),
+                                       (257, 12288), (300, 1024)])
+def test_layernorm_around_the_few_rows_line(rows, cols):
+    """One to sixteen waves per row, one and two pieces per lane, and the kernel for more rows."""
+    test_layernorm(rows, cols)
+
+
 # ------------------------------------------------------------------ fused dequant + GEMM
 def _linear_case(m, n, k, quant, bias, relu, residual, seed, std_w=0.02, std_x=1.0, tiled=False, meta_f16=False):
     w16 = _rand16((n, k), std_w, seed)
