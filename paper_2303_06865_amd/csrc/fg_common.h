@@ -148,6 +148,8 @@ __device__ __forceinline__ float dpp_f32(float v) {
 // quad_perm 1032 and 2301; lanes reversed inside 8 and inside 16: once the quads (the eights) are uniform, the
 // mirror brings the other quad's (the other eight's) value
 constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppHalfMirror = 0x141, kDppMirror = 0x140;
+// lanes of 16 rotated: once the eights (the quads of the eights) repeat, the other eight's (quad's) value at one's own place
+constexpr int kDppRor8 = 0x128, kDppRor4 = 0x124;
 
 template <class Op>
 __device__ __forceinline__ float row16_reduce(float v, Op op) {   // over each 16 lanes, result in all of them
@@ -177,8 +179,15 @@ struct OpAdd {
 __device__ __forceinline__ float wave_max(float v) {
   return xor32_reduce(xor16_reduce(row16_reduce(v, OpMax()), OpMax()), OpMax());
 }
+// The halves first, neighbouring lanes last.  The order is part of what LayerNorm returns: another one moves its mean
+// by a last bit, some of its FP16 results by an ulp and, behind the QKV projection, a few 4-bit codes of the cache by a
+// step, which in 12288-wide layers showed as single outputs off by 0.05 of their root mean square.
 __device__ __forceinline__ float wave_sum(float v) {
-  return xor32_reduce(xor16_reduce(row16_reduce(v, OpAdd()), OpAdd()), OpAdd());
+  v = xor16_reduce(xor32_reduce(v, OpAdd()), OpAdd());
+  v += dpp_f32<kDppRor8>(v);
+  v += dpp_f32<kDppRor4>(v);
+  v += dpp_f32<kDppXor2>(v);
+  return v + dpp_f32<kDppXor1>(v);
 }
 
 // Unpack one 32-bit word of eight 4-bit codes c0..c7 (c0 in the lowest nibble) into four FP16
