@@ -6,14 +6,12 @@
 
 namespace fg {
 
-__device__ __forceinline__ float block_sum_256(float v, float* red) {
+__device__ __forceinline__ float block_sum_256(float v, float* red) {   // red: four floats, used once per launch
   v = wave_sum(v);
   const int w = threadIdx.x >> 6;
   if ((threadIdx.x & 63) == 0) red[w] = v;
   __syncthreads();
-  const float t = red[0] + red[1] + red[2] + red[3];
-  __syncthreads();
-  return t;
+  return red[0] + red[1] + red[2] + red[3];
 }
 
 // One 256-thread block per row.  Mean first, then the centred second moment (both in binary32
@@ -22,7 +20,7 @@ __global__ __launch_bounds__(256) void layernorm_kernel(const half_t* __restrict
                                                         const half_t* __restrict__ gamma,
                                                         const half_t* __restrict__ beta, int cols,
                                                         float eps, half_t* __restrict__ out, int64_t ldo) {
-  __shared__ float red[4];
+  __shared__ float red[2][4];
   const half_t* xr = x + (int64_t)blockIdx.x * ldx;
   half_t* orow = out + (int64_t)blockIdx.x * ldo;
   const int nchunk = cols >> 3;
@@ -32,7 +30,7 @@ __global__ __launch_bounds__(256) void layernorm_kernel(const half_t* __restrict
 #pragma unroll
     for (int i = 0; i < 8; ++i) s += (float)v[i];
   }
-  const float mean = block_sum_256(s, red) / (float)cols;
+  const float mean = block_sum_256(s, red[0]) / (float)cols;
   float q = 0.f;
   for (int c = threadIdx.x; c < nchunk; c += 256) {
     const h8_t v = *reinterpret_cast<const h8_t*>(xr + c * 8);
@@ -42,7 +40,7 @@ __global__ __launch_bounds__(256) void layernorm_kernel(const half_t* __restrict
       q += d * d;
     }
   }
-  const float var = block_sum_256(q, red) / (float)cols;
+  const float var = block_sum_256(q, red[1]) / (float)cols;
   const float rstd = 1.0f / sqrtf(var + eps);
   for (int c = threadIdx.x; c < nchunk; c += 256) {
     const h8_t v = *reinterpret_cast<const h8_t*>(xr + c * 8);
@@ -57,21 +55,34 @@ __global__ __launch_bounds__(256) void layernorm_kernel(const half_t* __restrict
 
 // The same arithmetic in the same order for rows of up to 256 * 8 * NC elements, with the row held in
 // registers between the three phases (one read of x instead of three).
-template <int NC>
+// AHEAD, for few rows: one workgroup per row leaves CUs idle and the time is a chain of latencies (row in, two sums over
+// the workgroup, gamma and beta in, row out), so gamma and beta are on their way before the sums and a sum is one barrier.
+// (More waves per row were faster still, but cannot add in this order: see wave_sum.)
+template <int NC, bool AHEAD>
 __global__ __launch_bounds__(256) void layernorm_reg_kernel(const half_t* __restrict__ x, int64_t ldx,
                                                             const half_t* __restrict__ gamma,
                                                             const half_t* __restrict__ beta, int cols,
                                                             float eps, half_t* __restrict__ out, int64_t ldo) {
-  __shared__ float red[4];
+  __shared__ float red[2][4];
   const half_t* xr = x + (int64_t)blockIdx.x * ldx;
   half_t* orow = out + (int64_t)blockIdx.x * ldo;
   const int nchunk = cols >> 3;
-  h8_t v[NC];
+  h8_t v[NC], g[NC], b[NC];
+  auto load_gb = [&](int j) {
+    const int c = threadIdx.x + 256 * j;
+    g[j] = *reinterpret_cast<const h8_t*>(gamma + c * 8);
+    b[j] = *reinterpret_cast<const h8_t*>(beta + c * 8);
+  };
 #pragma unroll
   for (int j = 0; j < NC; ++j) {
     const int c = threadIdx.x + 256 * j;
     if (c < nchunk) v[j] = *reinterpret_cast<const h8_t*>(xr + c * 8);
   }
+  if (AHEAD) {
+#pragma unroll
+    for (int j = 0; j < NC; ++j)
+      if (threadIdx.x + 256 * j < nchunk) load_gb(j);
+  }
   float s = 0.f;
 #pragma unroll
   for (int j = 0; j < NC; ++j)
@@ -79,7 +90,7 @@ __global__ __launch_bounds__(256) void layernorm_reg_kernel(const half_t* __rest
 #pragma unroll
       for (int i = 0; i < 8; ++i) s += (float)v[j][i];
     }
-  const float mean = block_sum_256(s, red) / (float)cols;
+  const float mean = block_sum_256(s, red[0]) / (float)cols;
   float q = 0.f;
 #pragma unroll
   for (int j = 0; j < NC; ++j)
@@ -90,80 +101,13 @@ __global__ __launch_bounds__(256) void layernorm_reg_kernel(const half_t* __rest
         q += d * d;
       }
     }
-  const float var = block_sum_256(q, red) / (float)cols;
+  const float var = block_sum_256(q, red[1]) / (float)cols;
   const float rstd = 1.0f / sqrtf(var + eps);
 #pragma unroll
   for (int j = 0; j < NC; ++j) {
     const int c = threadIdx.x + 256 * j;
     if (c < nchunk) {
-      const h8_t g = *reinterpret_cast<const h8_t*>(gamma + c * 8);
-      const h8_t b = *reinterpret_cast<const h8_t*>(beta + c * 8);
-      h8_t o;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) o[i] = (half_t)(((float)v[j][i] - mean) * rstd * (float)g[i] + (float)b[i]);
-      *reinterpret_cast<h8_t*>(orow + c * 8) = o;
-    }
-  }
-}
-
-// Few rows: one workgroup per row leaves CUs idle, and the time is a chain of latencies (row in, two sums over the
-// workgroup, gamma and beta in, row out) plus the vector work of a lane.  So up to sixteen waves take a row, NC (one or
-// two) 16-byte pieces per lane; gamma and beta are on their way before the sums, and a sum is one barrier: each wave's
-// part to LDS, then every lane reads one part and the parts add up on DPP operands.
-template <int NW>
-__device__ __forceinline__ float block_sum_parts(float v, float* red) {   // red: NW floats, used once per launch
-  v = wave_sum(v);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-  __syncthreads();
-  float t = red[threadIdx.x & (NW - 1)];
-  t += dpp_f32<kDppXor1>(t);
-  t += dpp_f32<kDppXor2>(t);
-  if (NW >= 8) t += dpp_f32<kDppHalfMirror>(t);
-  if (NW >= 16) t += dpp_f32<kDppMirror>(t);
-  return t;
-}
-template <int NW, int NC>
-__global__ __launch_bounds__(NW * 64) void layernorm_fewrows_kernel(const half_t* __restrict__ x, int64_t ldx,
-                                                                    const half_t* __restrict__ gamma,
-                                                                    const half_t* __restrict__ beta, int cols,
-                                                                    float eps, half_t* __restrict__ out, int64_t ldo) {
-  __shared__ float red[2][NW];
-  const half_t* xr = x + (int64_t)blockIdx.x * ldx;
-  half_t* orow = out + (int64_t)blockIdx.x * ldo;
-  const int nchunk = cols >> 3;
-  h8_t v[NC], g[NC], b[NC];
-#pragma unroll
-  for (int j = 0; j < NC; ++j) {
-    const int c = threadIdx.x + NW * 64 * j;
-    const int cc = (c < nchunk ? c : nchunk - 1) * 8;   // past the end: the last piece again, never added or stored
-    v[j] = *reinterpret_cast<const h8_t*>(xr + cc);
-    g[j] = *reinterpret_cast<const h8_t*>(gamma + cc);
-    b[j] = *reinterpret_cast<const h8_t*>(beta + cc);
-  }
-  float s = 0.f;
-#pragma unroll
-  for (int j = 0; j < NC; ++j)
-    if (threadIdx.x + NW * 64 * j < nchunk) {
-#pragma unroll
-      for (int i = 0; i < 8; ++i) s += (float)v[j][i];
-    }
-  const float mean = block_sum_parts<NW>(s, red[0]) / (float)cols;
-  float q = 0.f;
-#pragma unroll
-  for (int j = 0; j < NC; ++j)
-    if (threadIdx.x + NW * 64 * j < nchunk) {
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const float d = (float)v[j][i] - mean;
-        q += d * d;
-      }
-    }
-  const float var = block_sum_parts<NW>(q, red[1]) / (float)cols;
-  const float rstd = 1.0f / sqrtf(var + eps);
-#pragma unroll
-  for (int j = 0; j < NC; ++j) {
-    const int c = threadIdx.x + NW * 64 * j;
-    if (c < nchunk) {
+      if (!AHEAD) load_gb(j);
       h8_t o;
 #pragma unroll
       for (int i = 0; i < 8; ++i) o[i] = (half_t)(((float)v[j][i] - mean) * rstd * (float)g[j][i] + (float)b[j][i]);
@@ -172,35 +116,31 @@ __global__ __launch_bounds__(NW * 64) void layernorm_fewrows_kernel(const half_t
   }
 }
 
-// The line is one workgroup per CU; there and below the wide workgroups win at every width, beyond they only cost
-// occupancy.  Back to back, four waves / this, us: 4 x 4096 3.07 / 2.42, 37 x 7168 3.46 / 3.00, 144 x 12288
-// 4.60 / 3.88, 256 x 12288 5.02 / 4.41; 333 x 7168 4.19 / 4.41, 512 x 4096 3.49 / 3.49, 1024 x 7168 6.51 / 7.74.
-constexpr int64_t kFewLnRows = 256;
+// Where the line lies: back to back, later / ahead, us: 4 x 4096 2.62 / 2.54, 37 x 7168 3.50 / 3.22, 144 x 12288 4.51 / 4.23,
+// 256 x 12288 4.88 / 4.57, 333 x 7168 4.10 / 3.98, 512 x 12288 6.22 / 5.95; 1000 x 4096 4.36 / 4.42, 1000 x 12288 9.77 / 10.19.
+constexpr int64_t kFewLnRows = 512;
 int layernorm_launch(const half_t* x, int64_t ldx, const half_t* g, const half_t* b, int64_t rows,
                      int64_t cols, float eps, half_t* out, int64_t ldo, hipStream_t stream) {
   if (rows == 0) return FG_OK;
   ProfScope prof(FG_K_LAYERNORM, stream);
   const dim3 grid((unsigned)rows), block(256);
-  if (rows <= kFewLnRows && cols <= 1024 * 8 * 2) {
-#define FG_LN_FEW(NW_, NC_) \
-  hipLaunchKernelGGL((layernorm_fewrows_kernel<NW_, NC_>), grid, dim3(64 * NW_), 0, stream, x, ldx, g, b, (int)cols, eps, out, ldo)
-    if (cols <= 256 * 8)
-      FG_LN_FEW(4, 1);
-    else if (cols <= 512 * 8)
-      FG_LN_FEW(8, 1);
-    else if (cols <= 1024 * 8)
-      FG_LN_FEW(16, 1);
-    else
-      FG_LN_FEW(16, 2);
-#undef FG_LN_FEW
-  } else if (cols <= 256 * 8 * 2)
-    hipLaunchKernelGGL(layernorm_reg_kernel<2>, grid, block, 0, stream, x, ldx, g, b, (int)cols, eps, out, ldo);
+  const bool few = rows <= kFewLnRows;
+#define FG_LN(NC_)                                                                                                      \
+  do {                                                                                                                  \
+    if (few)                                                                                                            \
+      hipLaunchKernelGGL((layernorm_reg_kernel<NC_, true>), grid, block, 0, stream, x, ldx, g, b, (int)cols, eps, out, ldo);  \
+    else                                                                                                                \
+      hipLaunchKernelGGL((layernorm_reg_kernel<NC_, false>), grid, block, 0, stream, x, ldx, g, b, (int)cols, eps, out, ldo); \
+  } while (0)
+  if (cols <= 256 * 8 * 2)
+    FG_LN(2);
   else if (cols <= 256 * 8 * 4)
-    hipLaunchKernelGGL(layernorm_reg_kernel<4>, grid, block, 0, stream, x, ldx, g, b, (int)cols, eps, out, ldo);
+    FG_LN(4);
   else if (cols <= 256 * 8 * 8)
-    hipLaunchKernelGGL(layernorm_reg_kernel<8>, grid, block, 0, stream, x, ldx, g, b, (int)cols, eps, out, ldo);
+    FG_LN(8);
   else
     hipLaunchKernelGGL(layernorm_kernel, grid, block, 0, stream, x, ldx, g, b, (int)cols, eps, out, ldo);
+#undef FG_LN
   FG_LAUNCH_CHECK();
   return FG_OK;
 }

@@ -159,7 +159,7 @@ def test_layernorm(rows, cols):
 @pytest.mark.parametrize("rows,cols", [(256, 8), (257, 4096), (256, 2048), (3, 2056), (2, 4096), (256, 8192), (2, 8200),
                                        (257, 12288), (300, 1024)])
 def test_layernorm_around_the_few_rows_line(rows, cols):
-    """One to sixteen waves per row, one and two pieces per lane, and the kernel for more rows."""
+    """Gamma and beta requested ahead of the sums or after them, one to eight pieces per lane."""
     test_layernorm(rows, cols)
 
 

@@ -55,8 +55,10 @@ def layernorm_in_order(x16, g16, b16, eps):
     return _fma((x16.astype(F) - mean) * rstd, g16.astype(F), b16.astype(F)).astype(np.float16)
 
 
-@pytest.mark.parametrize("rows,cols", [(257, 64), (257, 768), (300, 2056), (257, 4096), (300, 4104), (257, 7168), (257, 12288),
-                                       (300, 16384), (257, 16392), (1, 49152)])
+@pytest.mark.parametrize("rows,cols", [(513, 64), (513, 768), (600, 2056), (513, 4096), (600, 4104), (513, 7168), (513, 12288),
+                                       (600, 16384), (513, 16392), (1, 49152),
+                                       (1, 8), (256, 768), (200, 2048), (512, 4096), (100, 4104), (256, 8192), (37, 8200),
+                                       (144, 12288), (512, 16384)])
 def test_layernorm_sums_in_order(rows, cols):
     rng = np.random.default_rng(rows + cols)
     x = (rng.standard_normal((rows, cols)) * 3 + 0.7).astype(np.float16)
