@@ -471,12 +471,15 @@ __global__ __launch_bounds__(64 * block_waves(WPH)) void attn_decode_f16_kernel(
 //   22 chunks  32 heads 37 / 21 / 13.8 / 11.2           16   160 heads 28 / 17.5 / 12.2 / 10.9
 //   10         256 heads 19.7 / 13.3 / 11.2 / 10.0, 448 heads 20 / 15 / 14.3 / 16.8
 //   5          160 heads 12 / 9 / 7.5 / 7.0             FP16, 22 chunks, 32 heads 79 / 42 / 23.1 / 23.4
+static int waves_by_heads(int64_t heads, int chunks) {
+  int wph = heads >= 2048 ? 1 : (heads >= 1024 ? 2 : 4);
+  while (wph > 1 && chunks < wph) wph >>= 1;   // never more waves than chunks
+  return wph;
+}
 static int pick_waves_per_head(int64_t heads, int chunks, bool q4) {
   if (q4 && heads <= 256 && chunks >= 5) return 8;
   const int by_length = q4 ? (chunks >= 7 ? 4 : (chunks >= 5 ? 2 : 1)) : (chunks >= 4 ? 4 : (chunks >= 2 ? 2 : 1));
-  const int by_heads = heads >= 2048 ? 1 : (heads >= 1024 ? 2 : 4);   // never more waves than chunks for these
-  int wph = by_heads;
-  while (wph > 1 && chunks < wph) wph >>= 1;
+  const int wph = waves_by_heads(heads, chunks);
   return wph > by_length ? wph : by_length;
 }
 
@@ -577,12 +580,12 @@ int decode_attention_paged_launch(const fg_model_cfg& cfg, const half_t* q, int6
   a.n_pages = pages.n_pages;
   a.rows_bias = rows_bias;
   const int64_t heads = (int64_t)b * cfg.nh;
-  // as in the contiguous launch, with the longest sequence the page table can address standing in for the
-  // lengths, which only the device knows
+  // Only the device knows the lengths, and young sequences in a long table are the ordinary state of continuous
+  // batching: what the table could hold may lower the number of waves, never raise it (2 chunks, 96 x 80 heads: 31 us
+  // with one wave per head, 46 with four, 104 with eight).
   const int64_t longest = (int64_t)seqs.table_stride * FG_PAGE_ROWS;
-  const bool q4 = pages.dtype != FG_F16;
-  const int wph = pick_waves_per_head(heads, (int)ceil_div(longest, q4 ? 8192 / dh : 64), q4);
-  const dim3 grid((unsigned)ceil_div(heads * wph, block_waves(wph)));
+  const int wph = waves_by_heads(heads, (int)ceil_div(longest, pages.dtype == FG_F16 ? 64 : 8192 / dh));
+  const dim3 grid((unsigned)ceil_div(heads * wph, 4));
   const bool h16 = pages.dtype == FG_Q4G64_H16;
   ProfScope prof(FG_K_ATTN_DECODE, stream);
   if (pages.dtype == FG_F16) {
@@ -600,23 +603,18 @@ int decode_attention_paged_launch(const fg_model_cfg& cfg, const half_t* q, int6
     FG_LAUNCH_CHECK();
     return FG_OK;
   }
-#define FG_PAGED_LAUNCH(DH_, WPH_)                                                                                \
-  do {                                                                                                            \
-    const dim3 block(64 * block_waves(WPH_));                                                                     \
-    if (h16)                                                                                                      \
-      hipLaunchKernelGGL((attn_decode_q4_kernel<DH_, WPH_, true, true>), grid, block, 0, stream, a);              \
-    else                                                                                                          \
-      hipLaunchKernelGGL((attn_decode_q4_kernel<DH_, WPH_, false, true>), grid, block, 0, stream, a);             \
+#define FG_PAGED_LAUNCH(DH_, WPH_)                                                                          \
+  do {                                                                                                      \
+    if (h16)                                                                                                \
+      hipLaunchKernelGGL((attn_decode_q4_kernel<DH_, WPH_, true, true>), grid, dim3(256), 0, stream, a);    \
+    else                                                                                                    \
+      hipLaunchKernelGGL((attn_decode_q4_kernel<DH_, WPH_, false, true>), grid, dim3(256), 0, stream, a);   \
   } while (0)
-#define FG_PAGED_WPH(DH_)                                                                                         \
-  do {                                                                                                            \
-    if (wph == 1) FG_PAGED_LAUNCH(DH_, 1);                                                                        \
-    else if (wph == 2) FG_PAGED_LAUNCH(DH_, 2);                                                                   \
-    else if (wph == 4) FG_PAGED_LAUNCH(DH_, 4);                                                                   \
-    else FG_PAGED_LAUNCH(DH_, 8);                                                                                 \
-  } while (0)
-  if (dh == 128) FG_PAGED_WPH(128); else FG_PAGED_WPH(64);
-#undef FG_PAGED_WPH
+  if (dh == 128) {
+    if (wph == 1) FG_PAGED_LAUNCH(128, 1); else if (wph == 2) FG_PAGED_LAUNCH(128, 2); else FG_PAGED_LAUNCH(128, 4);
+  } else {
+    if (wph == 1) FG_PAGED_LAUNCH(64, 1); else if (wph == 2) FG_PAGED_LAUNCH(64, 2); else FG_PAGED_LAUNCH(64, 4);
+  }
 #undef FG_PAGED_LAUNCH
   FG_LAUNCH_CHECK();
   return FG_OK;

@@ -244,6 +244,36 @@ def test_decode_attention_paged_more_heads_than_wave_slots():
     assert_close(got, ref, "paged decode attention, 3720 heads")
 
 
+@pytest.mark.parametrize("kind", ["q4", "q4h", "f16"])
+@pytest.mark.parametrize("b,nh,dh,short", [
+    (23, 96, 128, 2),     # 2208 heads, two chunks: one wave per head
+    (26, 80, 64, 4),      # 2080 heads of 64
+    (2, 64, 128, 4),      # 128 heads, four chunks: four waves per head
+])
+def test_decode_attention_paged_long_table_does_not_split_short_sequences(b, nh, dh, short, kind):
+    """Sequences of at most `short` pages in a table of 40: the waves per head are those of the short table, which shows
+    in the bits, since another number of waves adds in another order."""
+    h1, n_pages = nh * dh, b * short
+    cfg = B.Cfg(h1, nh, 4 * h1, 1000, 64)
+    g = torch.Generator(device="cuda").manual_seed(b)
+    pages = B.KVPages(cfg, n_pages, kind == "q4h", zero=False, quantized=kind != "f16")
+    for codes, meta in ((pages.k_codes, pages.k_meta), (pages.v_codes, pages.v_meta)):
+        if kind == "f16":
+            codes.normal_(0.0, 1.0, generator=g)
+        else:
+            codes.random_(0, 256, generator=g)
+            meta.normal_(0.0, 0.3, generator=g).abs_()
+    table = torch.randperm(n_pages, device="cuda", generator=g).int().view(b, short)
+    longer = torch.full((b, 40), -1, dtype=torch.int32, device="cuda")
+    longer[:, :short] = table
+    rows = torch.randint(64 * (short - 1) + 1, 64 * short + 1, (b,), device="cuda", generator=g).int()
+    q = torch.empty((b, 3 * h1), dtype=torch.float16, device="cuda").normal_(0.0, 1.0, generator=g)
+    a = B.fg_decode_attention_paged(cfg, q, 3 * h1, b, pages, B.Ragged(table, None, rows), 0)
+    c = B.fg_decode_attention_paged(cfg, q, 3 * h1, b, pages, B.Ragged(longer, None, rows), 0)
+    torch.cuda.synchronize()
+    assert bool(torch.isfinite(a.float()).all()) and torch.equal(a, c)
+
+
 # ------------------------------------------------------------------ Top-K sparse attention over pages
 @pytest.mark.parametrize("meta_f16", [False, True])
 @pytest.mark.parametrize("nh,dh", [(2, 128), (3, 64)])
