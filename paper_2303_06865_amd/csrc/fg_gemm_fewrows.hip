@@ -72,7 +72,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_fewrows_kernel(FewArgs a) {
   const int n0 = blockIdx.x * (16 * CT);
   const int m0 = blockIdx.y * (4 * NP);
   // K = 64 mod 128: in the last step lanes kb = 2, 3 have no elements; they read those of kb - 2 (valid
-  // memory) and their activations are replaced by zeros
+  // memory), and zeros replace them on both sides of the product (an infinite weight times a zero would be a NaN)
   const int tail_step = (a.K & 64) ? a.steps - 1 : a.steps;
   const bool tail_lane = kb >= 2;
 
@@ -166,6 +166,17 @@ __global__ __launch_bounds__(NW * 64) void gemm_fewrows_kernel(FewArgs a) {
     for (int m = 0; m < MT; ++m)
 #pragma unroll
       for (int i = 0; i < 4; ++i) x[m][i] = lds_read128<0>(off + x_row[m] + (((4 * kb + i) ^ x_swz[m]) << 4));
+    if (step == tail_step) {   // wave-uniform
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct) {
+#pragma unroll
+        for (int i = 0; i < NB; ++i) b.w[ct][i] = tail_lane ? (u4_t){0u, 0u, 0u, 0u} : b.w[ct][i];
+        if constexpr (FMT == kFewQ4TiledH16)
+          b.pair16[ct] = tail_lane ? 0u : b.pair16[ct];
+        else if constexpr (Q4)
+          b.pair[ct] = tail_lane ? make_float2(0.f, 0.f) : b.pair[ct];
+      }
+    }
     bool waited = false;
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct) {

@@ -2,7 +2,9 @@
 four-row pieces, every count of column tiles per workgroup and of waves, ragged columns, contractions of one group, of
 an odd number of groups (the last step is half empty), shorter and longer than the steps the waves keep in flight."""
 import pytest
+import torch
 
+from paper_2303_06865_amd import binding as B
 from tests.test_gpu_kernels import _linear_case
 from tests.util import assert_close
 
@@ -55,3 +57,27 @@ def test_linear_blocks_of_rows(m, n, k, fmt):
     quant, tiled, h16 = FORMATS[fmt]
     got, ref = _linear_case(m, n, k, quant, True, True, True, seed=m + n + k, tiled=tiled, meta_f16=h16)
     assert_close(got, ref, "blocks of rows m=%d n=%d k=%d %s" % (m, n, k, fmt))
+
+
+@pytest.mark.parametrize("fmt", sorted(FORMATS))
+@pytest.mark.parametrize("m,n,k", [(1, 64, 64), (6, 96, 192), (16, 2304, 832), (31, 288, 1984)])
+def test_infinite_weight_in_the_half_empty_last_step(m, n, k, fmt):
+    """An infinite weight in the last group of an odd number of groups: infinity in its column (the activations are
+    positive), the other columns as they are.  The lanes that have no elements in that step must not bring it in."""
+    quant, tiled, h16 = FORMATS[fmt]
+    g = torch.Generator(device="cuda").manual_seed(m + n + k)
+    half = lambda *s: torch.empty(s, dtype=torch.float16, device="cuda").normal_(0.0, 1.0, generator=g)
+    w, x = half(n, k) * 0.05, half(m, k).abs() + 0.01
+    mat = B.Mat.from_f16(w, quant, meta_f16=h16)
+    if quant:
+        ref = B.fg_dequantize_groupwise(*B.fg_quantize_groupwise(w, meta_f16=h16)).view(n, k).half().float()
+        mat.meta.view(n, k // 64, 2)[5, -1] = torch.tensor([float("inf"), 0.0])   # {min, scale}: the whole group
+        mat = mat.tiled() if tiled else mat
+    else:
+        ref = w.float().clone()
+        mat.data[5, k - 7] = float("inf")
+    out = B.fg_linear(mat, None, x).float()
+    want = x.float() @ ref.t()
+    assert bool((out[:, 5] == float("inf")).all())
+    keep = torch.arange(n) != 5
+    assert_close(out[:, keep].cpu().numpy(), want[:, keep].cpu().numpy(), "beside an infinite column, %s" % fmt)
