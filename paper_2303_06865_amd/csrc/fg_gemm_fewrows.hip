@@ -123,6 +123,10 @@ __global__ __launch_bounds__(NW * 64) void gemm_fewrows_kernel(FewArgs a) {
       c = tail ? c & 7 : c;
       __builtin_amdgcn_global_load_lds((gptr_t)(xp[p] + xo + 8 * c), (lptr_t)(ring + (d * NP + p) * 1024), 16, 0, 0);
     }
+    // compute() takes the arrival of a weight register for the arrival of these copies: no weight load before them
+    __builtin_amdgcn_sched_barrier(0);
+    __asm__ volatile("; activation copies issued" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
     const bool back = tail && tail_lane;
     const int64_t wo = (int64_t)step * kWStep - (back ? kWTail : 0);
     const int64_t mo = (int64_t)step * kMStep - (back ? kMTail : 0);
