@@ -38,9 +38,14 @@ __device__ __forceinline__ TileParts tile_parts(int64_t total, int parts, int ks
 // workgroup: its pipeline does not fill and its partial sums cost more than the steps.  Measured with the reduction pass,
 // 768 x 3072 4-bit weights at 33 / 144 / 600 rows, at least 1 / 3 / 6 / 12 steps (us): 14.5 / 10.7 / 11.3 / 14.3,
 // 23.5 / 16.8 / 17.2 / 21.2, 41.3 / 29.7 / 28.8 / 31.9 (and 49.6 / 56.5 / - with ranges of less than one step).
+// A tile of up to five steps is one range, with no partial sums at all, if there are 32 of them or no more than three
+// steps (fewer of four are halved): us with ranges of at least 1 / 2 / 3 steps, tiled, 8192 columns x 333 rows, K = 64
+// 12.9 / 20.5 / 34.7, K = 128 24.4 / 14.1 / 28.4; with 2 / 3 / 4, K = 256, 16384 x 512 38 / 44 / 23, 768 x 144 (three
+// tiles) 11.7 / 17.9 / 18.4; with 3 / 5, K = 320, 16384 x 512 47 / 24, 2048 x 300 (16 tiles) 18.1 / 21.5.
 constexpr int kMinPartSteps = 3;
-static inline int work_parts(int64_t total, int grid) {
-  const int64_t p = total / kMinPartSteps;
+static inline int work_parts(int64_t total, int ksteps, int grid) {
+  const bool whole = ksteps <= kMinPartSteps || (ksteps <= 5 && total / ksteps >= 32);
+  const int64_t p = total / (whole ? ksteps : (ksteps == 4 ? 2 : kMinPartSteps));
   return p < 1 ? 1 : p < grid ? (int)p : grid;
 }
 

@@ -385,7 +385,7 @@ int gemm_f16w_launch(const LinearArgs& la, void* ws, size_t ws_bytes, hipStream_
   a.rounds = a.n_tiles / kGrid;
   const int64_t rem_tiles = a.n_tiles - (int64_t)a.rounds * kGrid;
   a.rem_work = rem_tiles * a.ksteps;
-  a.parts = work_parts(a.rem_work, kGrid);
+  a.parts = work_parts(a.rem_work, a.ksteps, kGrid);
   a.bias = la.bias;
   a.residual = la.residual;
   a.ldr = la.ldr;

@@ -1988,7 +1988,7 @@ int gemm_stream_launch(const LinearArgs& la, void* ws, size_t ws_bytes, hipStrea
   a.rounds = (int)(tiles / a.grid);
   const int64_t rem_tiles = tiles - (int64_t)a.rounds * a.grid;
   a.rem_work = rem_tiles * a.ksteps;
-  a.parts = work_parts(a.rem_work, a.grid);
+  a.parts = work_parts(a.rem_work, a.ksteps, a.grid);
   a.bias = la.bias;
   a.residual = la.residual;
   a.ldr = la.ldr;

@@ -14,7 +14,14 @@ FORMATS = {"f16": (False, False, False), "q4t": (True, True, False), "q4h": (Tru
 
 CASES = [
     # m, n, k
-    (1025, 32, 64),        # 5 units in all: one range over five tiles
+    (1025, 32, 64),        # tiles of one K step, a range each
+    (1300, 8224, 64),
+    (1025, 4128, 128),     # of two
+    (700, 16416, 128),
+    (1100, 2080, 256),     # of four
+    (500, 2080, 256),      # ... halved where there are few tiles
+    (1100, 2080, 320),     # of five
+    (500, 2080, 320),      # ... in ranges of three or more, across tiles
     (1040, 768, 192),      # 45 units, 15 ranges over 15 tiles
     (1100, 1056, 448),     # a last column block of one 32-column tile, a last row block of 76 rows
     (1281, 288, 640),      # one row in the last block
