@@ -378,11 +378,16 @@ int launch_few_fmt(const FewArgs& a, hipStream_t stream) {
 
 }  // namespace
 
-// Which calls this kernel takes.  Up to 16 rows all of them; up to 32 rows those whose matrix is small enough for the
-// activations of its many workgroups not to cost more than the wider tiles' partial sums.  Measured at 32 rows against
-// the kernel that otherwise runs (us): tiled 28672 x 7168 43 vs 48, 7168 x 28672 49 vs 56, 36864 x 12288 84 vs 76,
-// 12288 x 49152 101 vs 98; FP16 21504 x 7168 68 vs 69, 12288 x 12288 58 vs 70, 7168 x 28672 100 vs 97, 50272 x 4096
-// 102 vs 96; canonical always (46 vs 135 and more).
+// Which calls this kernel takes.  Up to 16 rows all of them but FP16 weights of few columns and a long contraction; up
+// to 32 rows those whose matrix is small enough for the activations of its many workgroups not to cost more than the
+// wider tiles' partial sums.  Measured at 32 rows against the kernel that otherwise runs (us): tiled 28672 x 7168 43 vs 48,
+// 7168 x 28672 49 vs 56, 36864 x 12288 84 vs 76, 12288 x 49152 101 vs 98; FP16 21504 x 7168 68 vs 69, 12288 x 12288
+// 58 vs 70, 7168 x 28672 100 vs 97, 50272 x 4096 102 vs 96; canonical always (46 vs 135 and more).
+// FP16 weights, few columns, long contraction: a workgroup's time grows with the contraction and too few of them read.
+//   columns x contraction, this kernel vs the one that splits it, us: 1 row 1280 x 16384 18.6 vs 19.2, x 20480 23.8 vs
+//   21.1; 8 rows 2560 x 20480 31 vs 34, 2048 x 20480 30 vs 25; 16 rows 3072 x 16384 31 vs 34, 2048 x 16384 29 vs 23;
+//   24 rows 3072 x 12288 27 vs 30, 2560 x 12288 26 vs 23.  (Up to 8192 deep it is level or better: 640 x 8192, 16 rows,
+//   12 vs 12.)
 // More rows, in blocks of 32 that each read the matrix: as long as matrix x blocks is small, the other kernels leave most
 // of the chip without work, or split the contraction into partial sums.  The line is where both take the same time, us:
 //   tiled, 110 M    768 x 768 x 128 rows 4.6 vs 12.4; 2304 x 768 x 1000 22 vs 32; 2048 x 2048 x 640 21 vs 43;
@@ -391,22 +396,52 @@ int launch_few_fmt(const FewArgs& a, hipStream_t stream) {
 //   FP16, 34 M      2048 x 2048 x 128 8.1 vs 13; 4096 x 4096 x 64 15.9 vs 15.7, x 96 27 vs 19
 //   FP16 beyond 128 rows, 70 M   2304 x 768 x 320 10 vs 18; 2048 x 2048 x 450 22 vs 39; 6144 x 2048 x 144 24 vs 30,
 //                   x 192 29 vs 26
-//   canonical, 600 M   12288 x 4096 x 64 30 vs 343, x 320 119 vs 161, x 512 175 vs 121; 7168 x 7168 x 320 118 vs 184;
-//                   7168 x 28672 x 33 85 vs 325; 36864 x 12288 x 33 201 vs 183
+//   canonical, 600 M   7168 x 7168 x 320 118 vs 184, x 384 level; 4096 x 16384 x 320 0.62 of the other's time; 7168 x
+//                   28672 x 33 85 vs 325; 36864 x 12288 x 33 201 vs 183.  From 161 rows the wider matrices lose earlier:
+//                   12288 x 4096 x 320 (503 M) 119 vs 161, x 333 (553 M) 128 vs 113; 33000 x 1024 x 320 (337 M) 0.86 of
+//                   the other's time, x 384 (405 M) 124 vs 105; 16384 x 4096 x 161 (402 M) 92 vs 73
 //   canonical beyond 512 rows, 300 M   2048 x 2048 x 1000 36 vs 87; 6144 x 2048 x 640 66 vs 87, x 1000 98 vs 89
+// and, where the contraction is short, as long as columns x blocks is: then a workgroup is little more than its start and
+// its epilogue, and the wider tiles have fewer of them.
+//   tiled           16384 x 64 x 128 rows (65536) 13.9 vs 14.8, x 200 (114688) 23 vs 14.7; 4096 x 256 x 1000 (131072)
+//                   31 vs 39; 8192 x 768 x 512 (131072) 32 vs 38; 16384 x 768 x 192 (98304) 25 vs 27, x 256 (131072) 32 vs
+//                   31; 50272 x 64 x 32 14.4 vs 8.6, x 256 x 32 16.1 vs 17.6
+//   FP16            up to 128 rows the narrow tiles come without remainder where 4096 divides the columns: 4096 x 768 x
+//                   64 (8192) 5.0 vs 5.6, x 100 (16384) 6.5 vs 6.3, 4096 x 64 x 64 3.5 vs 3.0; elsewhere 6144 x 1024 x
+//                   128 (24576) 12 vs 15, 28672 x 1024 x 40 (57344) 33 vs 26.  Beyond 128 rows 8192 x 768 x 256
+//                   (65536) 22 vs 25; 4096 x 512 x 1000 (131072) 33 vs 38; 16384 x 512 x 200 (114688) 32 vs 28
+//   canonical       16384 x 64 x 128 (65536) 13.7 vs 17.7, x 200 (114688) 23 vs 18; 50272 x 192 x 128 (201088) 50 vs 63,
+//                   x 200 (351904) 82 vs 76; 50272 x 384 x 320 (502720) 104 vs 130, x 512 164 vs 124; 16384 x 512 x 512
+//                   (262144) 61 vs 28; beyond 512 rows 4096 x 64 x 1000 (131072) 26 vs 29, 16384 x 256 x 1000 116 vs 43
+// (FP16 columns that 32 does not divide are outside the FP16 exceptions: the kernel they would fall to is the slow one.)
 bool gemm_fewrows_takes(int dtype, int64_t n, int64_t k, int64_t m) {
   if (m < 1 || m > 1024 || k % kGroup != 0) return false;
+  const bool f16 = dtype == FG_F16, streams = n % 32 == 0;
+  if (f16 && streams && k > 8192 && k > n * (m <= 4 ? 10 : (m <= 8 ? 8 : (m <= 16 ? 6 : 4)))) return false;
   if (m <= 16) return true;
-  const int64_t size = n * k;
+  const int64_t size = n * k, blocks = ceil_div(m, 32), wide = n * blocks;
   if (m <= 32) {
     if (dtype == FG_Q4G64) return true;
-    if (dtype == FG_F16) return size <= 160000000 && n <= 32768;
-    return size <= 220000000;
+    if (f16) return size <= 160000000 && n <= 32768;
+    return size <= 220000000 && (k >= 256 || n <= 32768);
   }
-  const int64_t line = dtype == FG_Q4G64 ? (m <= 512 ? 600000000 : 300000000)
-                       : dtype == FG_F16 ? (m <= 128 ? 34000000 : 70000000)
-                                         : 110000000;
-  return size <= line / ceil_div(m, 32);
+  if (dtype == FG_Q4G64) {
+    const int64_t line = m <= 160                ? 600000000
+                         : m > 512               ? 300000000
+                         : n <= 10240            ? 600000000
+                         : n < 16384             ? 510000000
+                                                 : 340000000;
+    if (size > line / blocks) return false;
+    if (m <= 512 && k < 192) return wide <= 81920;
+    return (m <= 320 && k >= 256) || wide <= 204800;
+  }
+  if (f16) {
+    if (size > (m <= 128 ? 34000000 : 70000000) / blocks) return false;
+    if (!streams) return true;
+    if (m > 128) return wide <= (k < 256 || n > 8192 ? 65536 : 131072);
+    return n % 4096 == 0 ? wide <= 8192 && k >= 192 : wide <= 24576;
+  }
+  return size <= 110000000 / blocks && wide <= (k < 256 ? 65536 : (n <= 8192 ? 131072 : 98304));
 }
 
 int gemm_fewrows_launch(const LinearArgs& la, hipStream_t stream) {

@@ -27,8 +27,10 @@ CASES = [
     (12, 12288, 64, False, False, True),     # three
     (16, 16384, 192, True, False, True),     # four
     (29, 12256, 128, False, False, True),    # three, ragged
-    (2, 128, 8256, True, False, True),       # 65 steps: sixteen waves (tiled), eight (canonical, FP16)
-    (13, 64, 16448, True, False, True),      # 129 steps: sixteen waves on FP16 weights too
+    (2, 128, 8256, True, False, True),       # 65 steps: sixteen waves (tiled), eight (canonical); FP16: not this kernel
+    (2, 832, 8256, True, False, True),       # ... this one again, with eight
+    (13, 64, 16448, True, False, True),      # 129 steps
+    (3, 1664, 16448, True, False, True),     # ... sixteen waves on FP16 weights too
     (7, 6144, 8256, True, False, False),     # sixteen waves, two column tiles (tiled)
 ]
 

@@ -46,7 +46,10 @@ CASES = [
 @pytest.mark.parametrize("fmt", sorted(FORMATS))
 @pytest.mark.parametrize("m,n,k", CASES)
 def test_linear_shared_contraction(m, n, k, fmt):
-    quant, tiled, h16 = FORMATS[fmt]
+    _check(m, n, k, *FORMATS[fmt])
+
+
+def _check(m, n, k, quant, tiled, h16):
     g = torch.Generator(device="cuda").manual_seed(m + n + k)
     half = lambda *s: torch.empty(s, dtype=torch.float16, device="cuda").normal_(0.0, 1.0, generator=g)
     w, x, bias, res = half(n, k) * 0.05, half(m, k), half(n), half(m, n)
@@ -55,7 +58,7 @@ def test_linear_shared_contraction(m, n, k, fmt):
         w = B.fg_dequantize_groupwise(*B.fg_quantize_groupwise(w, meta_f16=h16)).view(n, k).half()
     ref = torch.relu(x.float() @ w.float().t() + bias.float()) + res.float()
     got = B.fg_linear(mat, bias, x, residual=res, relu=True)
-    assert_close(got.cpu().numpy(), ref.cpu().numpy(), "shared contraction m=%d n=%d k=%d %s" % (m, n, k, fmt))
+    assert_close(got.cpu().numpy(), ref.cpu().numpy(), "shared contraction m=%d n=%d k=%d %s" % (m, n, k, (quant, tiled, h16)))
     assert torch.equal(B.fg_linear(mat, bias, x, residual=res, relu=True), got)
 
 
@@ -72,3 +75,18 @@ def test_linear_shared_contraction(m, n, k, fmt):
 ])
 def test_linear_blocks_of_192_rows(m, n, k, fmt):
     test_linear_shared_contraction(m, n, k, fmt)
+
+
+# Both sides of the lines between blocks of 32 rows over whole contractions and the kernels that take the rest.
+@pytest.mark.parametrize("fmt,m,n,k", [
+    ("f16", 1, 1024, 10304), ("f16", 1, 1056, 10304), ("f16", 8, 1280, 10304), ("f16", 8, 1312, 10304), ("f16", 16, 1696, 10304),
+    ("f16", 16, 1728, 10304), ("f16", 24, 2560, 10304), ("f16", 24, 2592, 10304), ("f16", 40, 320, 8256), ("f16", 7, 200, 9280),
+    ("q4t", 17, 32768, 192), ("q4h", 32, 32800, 192), ("q4t", 33, 32768, 192), ("q4t", 64, 32800, 192), ("q4h", 512, 8192, 256),
+    ("q4t", 513, 8192, 256), ("q4t", 33, 49152, 256), ("q4t", 40, 49184, 256),
+    ("f16", 33, 4096, 192), ("f16", 50, 4096, 128), ("f16", 65, 4096, 256), ("f16", 128, 6144, 128), ("f16", 100, 6176, 128),
+    ("f16", 129, 13088, 192), ("f16", 130, 13120, 192), ("f16", 512, 8192, 256), ("f16", 513, 8192, 256),
+    ("q4", 161, 13648, 128), ("q4", 161, 13664, 128), ("q4", 330, 18608, 256), ("q4", 330, 18632, 256), ("q4", 320, 18632, 256),
+    ("q4", 161, 16384, 3456), ("q4", 161, 16384, 3520), ("q4", 321, 12288, 3712), ("q4", 321, 12288, 3840),
+])
+def test_linear_around_the_few_rows_lines(fmt, m, n, k):
+    _check(m, n, k, *dict(FORMATS, q4=(True, False, False))[fmt])
