@@ -201,28 +201,31 @@ __global__ __launch_bounds__(256) void embed_ragged_kernel(const half_t* __restr
 
 // Greedy token: argmax over a row of binary32 logits, lowest index on ties.
 // Row r's result goes to out[r * out_stride], or to out[out_index[r]] when out_index is given.
-// One workgroup per row, so with few rows the time is that of one CU taking in a row: sixteen waves with
-// sixteen 16-byte loads each in flight (rows of up to 65536 in one go): 7.0 us for 4 rows of 50272 logits and 9.2 us
-// for 128 of them (with four loads each 8.7 and 10.1; 256 threads with one 4-byte load each 59 and 64).  VEC: the
-// rows start on 16-byte boundaries.
-constexpr int kArgmaxThreads = 1024;
-template <bool VEC>
-__global__ __launch_bounds__(kArgmaxThreads) void argmax_kernel(const float* __restrict__ logits, int64_t cols,
-                                                                int32_t* __restrict__ out, int64_t out_stride,
-                                                                const int32_t* __restrict__ out_index) {
-  constexpr int NW = kArgmaxThreads / 64, kW = VEC ? 4 : 1, kLoads = 16;
+// One workgroup of T threads per row, kLoads pieces of it in flight per thread (a piece is 16 bytes; VEC == false, for
+// rows that do not start on 16-byte boundaries: one element).  With few rows the time is that of one CU taking in a row,
+// so it has sixteen waves, and as many loads as the row is long; what is loaded beyond the row's end is lost, and many
+// rows pay for it.  LM head (64 wide) and argmax together, us, threads x loads 256 x 1 / 1024 x 1 / 1024 x 4 / 1024 x 16:
+// 4 rows of 1000 logits 8.7 / 8.9 / 9.2 / 10.9, 2000 rows 39 / 43 / 45 / 67; 4 rows of 8192 12.0 / 10.0 / 10.4 / 13.7,
+// 2000 rows 39 / 41 / 43 / 78; 4 rows of 50272 34 / 18.9 / 16.8 / 18.1, 128 rows 69 / 54 / 52 / 53, 2000 rows 211 / 221 /
+// 220 / 221; 300 rows of 256000 305 / 209 / 212 / 203, 512 rows 325 / 274 / 279 / 267.  (256 threads with one 4-byte load
+// each: 59 us for the argmax alone of 4 rows of 50272.)
+template <bool VEC, int T, int kLoads>
+__global__ __launch_bounds__(T) void argmax_kernel(const float* __restrict__ logits, int64_t cols,
+                                                   int32_t* __restrict__ out, int64_t out_stride,
+                                                   const int32_t* __restrict__ out_index) {
+  constexpr int NW = T / 64, kW = VEC ? 4 : 1;
   __shared__ float bv[NW];
   __shared__ int bi[NW];
   const float* r = logits + (int64_t)blockIdx.x * cols;
   float best = -INFINITY;
   int idx = 0x7fffffff;
   const uint32_t n = (uint32_t)(cols / kW);   // (VEC is only taken where cols is a multiple of 4)
-  for (uint32_t c = threadIdx.x; c < n; c += kLoads * kArgmaxThreads) {
+  for (uint32_t c = threadIdx.x; c < n; c += kLoads * T) {
     float v[kLoads][kW];
     uint32_t at[kLoads];
 #pragma unroll
     for (int j = 0; j < kLoads; ++j) {
-      at[j] = c + j * kArgmaxThreads;
+      at[j] = c + j * T;
       at[j] = (at[j] < n ? at[j] : n - 1) * kW;   // past the end: the last piece again, which changes nothing
       if constexpr (VEC)
         *reinterpret_cast<float4*>(v[j]) = *reinterpret_cast<const float4*>(r + at[j]);
@@ -262,10 +265,10 @@ __global__ __launch_bounds__(kArgmaxThreads) void argmax_kernel(const float* __r
     bi[threadIdx.x >> 6] = idx;
   }
   __syncthreads();
-  static_assert(NW == 16, "one DPP row merges the waves");
+  static_assert(NW <= 16 && 16 % NW == 0, "one DPP row merges the waves");
   if (threadIdx.x < 64) {
-    best = bv[threadIdx.x & 15];
-    idx = bi[threadIdx.x & 15];
+    best = bv[threadIdx.x & (NW - 1)];
+    idx = bi[threadIdx.x & (NW - 1)];
     merge_row16();
     if (threadIdx.x == 0) {
       const int64_t dst = out_index ? (int64_t)out_index[blockIdx.x] : (int64_t)blockIdx.x * out_stride;
@@ -278,11 +281,27 @@ int argmax_launch(const float* logits, int64_t rows, int64_t cols, int32_t* out,
                   hipStream_t stream, const int32_t* out_index) {
   if (rows == 0) return FG_OK;
   ProfScope prof(FG_K_ARGMAX, stream);
-  const dim3 grid((unsigned)rows), block(kArgmaxThreads);
-  if (cols % 4 == 0 && (reinterpret_cast<uintptr_t>(logits) & 15u) == 0)
-    hipLaunchKernelGGL(argmax_kernel<true>, grid, block, 0, stream, logits, cols, out, out_stride, out_index);
+  const bool vec = cols % 4 == 0 && (reinterpret_cast<uintptr_t>(logits) & 15u) == 0;
+#define FG_ARGMAX(T_, LOADS_)                                                                                            \
+  do {                                                                                                                   \
+    if (vec)                                                                                                             \
+      hipLaunchKernelGGL((argmax_kernel<true, T_, LOADS_>), dim3((unsigned)rows), dim3(T_), 0, stream, logits, cols, out,  \
+                         out_stride, out_index);                                                                         \
+    else                                                                                                                 \
+      hipLaunchKernelGGL((argmax_kernel<false, T_, LOADS_>), dim3((unsigned)rows), dim3(T_), 0, stream, logits, cols, out, \
+                         out_stride, out_index);                                                                         \
+  } while (0)
+  // pieces of a row: 16 bytes, or one element
+  const int64_t pieces = vec ? cols / 4 : cols;
+  if (pieces <= 256)
+    FG_ARGMAX(256, 1);
+  else if (pieces <= 2048)
+    FG_ARGMAX(1024, 1);
+  else if (pieces <= 16384)
+    FG_ARGMAX(1024, 4);
   else
-    hipLaunchKernelGGL(argmax_kernel<false>, grid, block, 0, stream, logits, cols, out, out_stride, out_index);
+    FG_ARGMAX(1024, 16);
+#undef FG_ARGMAX
   FG_LAUNCH_CHECK();
   return FG_OK;
 }

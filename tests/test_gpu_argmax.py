@@ -1,5 +1,5 @@
-"""Greedy token over rows of logits (csrc/fg_norm.hip: argmax_kernel): widths around its passes of 1024 16-byte pieces,
-widths and addresses that it has to read element by element, ties between far columns."""
+"""Greedy token over rows of logits (csrc/fg_norm.hip: argmax_kernel): widths around what its threads
+take in one pass, widths and addresses that it has to read element by element, ties between far columns."""
 import ctypes as C
 
 import numpy as np
@@ -13,7 +13,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("offset", [0, 1])
-@pytest.mark.parametrize("vocab", [8, 1000, 4096, 4104, 16384, 16392, 50272])
+@pytest.mark.parametrize("vocab", [8, 256, 264, 1000, 1024, 1032, 2048, 2056, 4096, 4104, 8192, 8200, 16384, 16392, 50272, 65536,
+                                   65544, 131080])
 def test_argmax_is_the_lowest_index_of_the_maximum(vocab, offset):
     """Every embedding row that attains the largest logit occurs again at other columns, the last one among them; with
     offset 1 the logits start 4 bytes off a 16-byte boundary."""
