@@ -1838,7 +1838,7 @@ struct Shape {
   // per CU, which doubles the bytes in flight of what is then a pure weight streamer.
   int grid() const { return (wm == 1 && mt == 1) ? 512 : 256; }
 };
-Shape pick_shape(int64_t m) {
+Shape pick_shape(int64_t m, int dtype, int64_t n, int64_t k) {
   // Up to two row blocks the side-by-side shape wins (few tiles: the 256-row shape would leave most of
   // its stream-K pieces short); beyond that the weights would be re-read too often.
   // There, blocks of 192 rows where they leave at least a tenth fewer rows to pad to than blocks of 256 (321 .. 384,
@@ -1847,7 +1847,15 @@ Shape pick_shape(int64_t m) {
   // 252 -> 198; 1152 rows tiled 153 -> 132 (12288 x 4096), 381 -> 352, FP16 7168 x 28672 596 -> 594.  With less to
   // save it goes either way: 500 rows tiled 86 -> 80 (12288 x 4096) but 228 -> 242 (7168 x 28672), 1000 rows FP16
   // 4096 x 16384 159 -> 191, tiled 314 -> 351 (21504 x 7168).
-  if (m > 2 * kMaxMT * 32) return {ceil_div(m, 192) * 192 * 10 <= ceil_div(m, 256) * 256 * 9 ? 6 : 8, 1, 1, 8};
+  // FP16 weights cost a block of 192 rows as much LDS traffic as one of 256; where all tiles are cut along a long
+  // contraction that is what counts from seven blocks up: 1290 rows FP16 4096 x 16384 236 -> 252, 7168 x 28672 667 -> 699,
+  // 8192 x 8192 211 -> 252, 12288 x 12288 397 -> 406; but 6144 x 6144 162 -> 134, 2048 x 16384 139 -> 134, 21504 x 7168
+  // 450 -> 413, and 1152 rows FP16 4096 x 16384 221 -> 192, 12288 x 12288 460 -> 328.
+  if (m > 2 * kMaxMT * 32) {
+    const bool fewer = ceil_div(m, 192) * 192 * 10 <= ceil_div(m, 256) * 256 * 9;
+    const bool split_f16 = dtype == FG_F16 && m > 1152 && n >= 4096 && n <= 12288 && k >= 7168;
+    return {fewer && !split_f16 ? 6 : 8, 1, 1, 8};
+  }
   if (m > kMaxMT * 32) m = ceil_div(m, 2);
   const int need = (int)ceil_div(m, 32);
   return {need < 1 ? 1 : need, 2, 1, 4};
@@ -1961,16 +1969,14 @@ int launch_dec16(const StreamArgs& a, hipStream_t stream) {
 }  // namespace
 
 size_t gemm_stream_workspace(int64_t n, int64_t k, int64_t m) {
-  (void)n;
-  (void)k;
-  const Shape sh = pick_shape(m);
+  const Shape sh = pick_shape(m, FG_Q4G64_TILED, n, k);
   const int rows = sh.nw == 8 ? 256 : sh.rows();   // blocks of 192 rows need less, but are a choice among equals here
   return (size_t)sh.grid() * 2 * rows * kBN * sizeof(float);
 }
 
 int gemm_stream_launch(const LinearArgs& la, void* ws, size_t ws_bytes, hipStream_t stream) {
   if (la.m == 0 || la.n == 0) return FG_OK;
-  const Shape sh = pick_shape(la.m);
+  const Shape sh = pick_shape(la.m, la.dtype, la.n, la.k);
   StreamArgs a;
   a.w = reinterpret_cast<const uint8_t*>(la.w_data);
   a.meta = reinterpret_cast<const float2*>(la.w_meta);

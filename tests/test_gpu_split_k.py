@@ -72,6 +72,11 @@ def _check(m, n, k, quant, tiled, h16):
     (577, 8224, 512),
     (1152, 11040, 320),
     (1344, 9248, 192),
+    (1281, 4096, 7168),    # FP16: blocks of 256 rows here, and of 192 in the next four
+    (1281, 4064, 7168),
+    (1281, 4096, 7104),
+    (1344, 12320, 7168),
+    (1152, 4096, 7168),
 ])
 def test_linear_blocks_of_192_rows(m, n, k, fmt):
     test_linear_shared_contraction(m, n, k, fmt)
