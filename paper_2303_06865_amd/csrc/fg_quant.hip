@@ -85,14 +85,17 @@ __device__ __forceinline__ void quantize_group_8lanes(const h8_t v, uint32_t& pa
 // and its 32 pairs are one contiguous piece of the result, so the tiled order costs no second pass.  A 28672 x 7168
 // matrix into tiles: 96 us, 5.6 TB/s of its 539 MB (quantizer with one load in flight 121 us, then 54 us of
 // fg_pack_weights: 166 back to back).
-template <bool H16, bool TILED>
+// J = loads of a wave, 8 J groups.  One where there are few groups: the loads overlap, the arithmetic behind them is four
+// times as long (768 x 768 canonical 3.67 -> 2.79 us, 100 x 4096 3.55 -> 2.66).
+template <bool H16, bool TILED, int J>
 __global__ __launch_bounds__(256) void quantize_rows_kernel(const half_t* __restrict__ x, int64_t n_groups,
                                                             uint32_t groups_per_row,
                                                             uint32_t* __restrict__ codes,
                                                             void* __restrict__ meta) {
+  static_assert(!TILED || J == 4, "a tile has 32 rows");
   const int lane = threadIdx.x & 63, sub = lane & 7, lg = lane >> 3;
   const uint32_t piece = blockIdx.x * 4u + (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t g0 = (int64_t)piece * 32;   // first group of the piece, in the order of the result
+  const int64_t g0 = (int64_t)piece * (8 * J);   // first group of the piece, in the order of the result
   if (g0 >= n_groups) return;
   const half_t* src = x + g0 * kGroup;
   int64_t step = kGroup;                    // elements between consecutive groups of the piece
@@ -101,17 +104,17 @@ __global__ __launch_bounds__(256) void quantize_rows_kernel(const half_t* __rest
     step = (int64_t)groups_per_row * kGroup;
     src = x + (int64_t)rb * 32 * step + (int64_t)kt * kGroup;
   }
-  const int valid = TILED || n_groups - g0 >= 32 ? 32 : (int)(n_groups - g0);
-  h8_t v[4];
+  const int valid = TILED || n_groups - g0 >= 8 * J ? 8 * J : (int)(n_groups - g0);
+  h8_t v[J];
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
+  for (int j = 0; j < J; ++j) {
     const int gi = j * 8 + lg;
     v[j] = *reinterpret_cast<const h8_t*>(src + (gi < valid ? gi : valid - 1) * step + sub * 8);
   }
   uint32_t* dst = codes + g0 * 8;
   float my_mn = 0.f, my_sc = 0.f;
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
+  for (int j = 0; j < J; ++j) {
     const int gi = j * 8 + lg;
     uint32_t p;
     float mn, sc;
@@ -121,7 +124,7 @@ __global__ __launch_bounds__(256) void quantize_rows_kernel(const half_t* __rest
     if (gi < valid) dst[TILED ? 4 * (32 * (sub >> 2) + gi) + (sub & 3) : gi * 8 + sub] = p;
   }
   const int gm = sub * 8 + lg;
-  if (sub < 4 && gm < valid) {
+  if (sub < J && gm < valid) {
     if (H16)
       reinterpret_cast<h2_t*>(meta)[g0 + gm] = (h2_t){(half_t)my_mn, (half_t)my_sc};
     else
@@ -358,20 +361,29 @@ static int quantize_launch(bool h16, bool tiled, const void* x_f16, int64_t rows
                            void* meta_out, hipStream_t st) {
   const half_t* x = reinterpret_cast<const half_t*>(x_f16);
   uint32_t* codes = reinterpret_cast<uint32_t*>(codes_out);
-  const int64_t gpr = cols / kGroup, groups = rows * gpr, blocks = ceil_div(groups, 128);
+  const int64_t gpr = cols / kGroup, groups = rows * gpr;
+  // The line (J = 4 / 1, us): 4096 x 4096 (262144 groups) 11.0 / 10.6, 8192 x 4096 18.8 / 17.7, FP16 pairs 19.2 / 18.7;
+  // 12288 x 4096 with FP16 pairs 25.8 / 26.3.
+  const int j = !tiled && groups <= 524288 ? 1 : 4;
+  const int64_t blocks = ceil_div(groups, 32 * j);
   if (blocks > 0x1fffffff || gpr > 0x7fffffff) return FG_ERR_SHAPE;   // piece numbers are 32-bit
   const dim3 grid((unsigned)blocks);
   ProfScope prof(FG_K_QUANTIZE, st);
-#define FG_QUANTIZE(H16_, TILED_) \
-  hipLaunchKernelGGL((quantize_rows_kernel<H16_, TILED_>), grid, dim3(256), 0, st, x, groups, (uint32_t)gpr, codes, meta_out)
-  if (h16 && tiled)
-    FG_QUANTIZE(true, true);
-  else if (h16)
-    FG_QUANTIZE(true, false);
-  else if (tiled)
-    FG_QUANTIZE(false, true);
+#define FG_QUANTIZE(TILED_, J_)                                                                                            \
+  do {                                                                                                                     \
+    if (h16)                                                                                                               \
+      hipLaunchKernelGGL((quantize_rows_kernel<true, TILED_, J_>), grid, dim3(256), 0, st, x, groups, (uint32_t)gpr, codes,  \
+                         meta_out);                                                                                        \
+    else                                                                                                                   \
+      hipLaunchKernelGGL((quantize_rows_kernel<false, TILED_, J_>), grid, dim3(256), 0, st, x, groups, (uint32_t)gpr, codes, \
+                         meta_out);                                                                                        \
+  } while (0)
+  if (tiled)
+    FG_QUANTIZE(true, 4);
+  else if (j == 1)
+    FG_QUANTIZE(false, 1);
   else
-    FG_QUANTIZE(false, false);
+    FG_QUANTIZE(false, 4);
 #undef FG_QUANTIZE
   FG_LAUNCH_CHECK();
   return FG_OK;

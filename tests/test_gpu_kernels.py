@@ -128,6 +128,20 @@ def test_quantize_tiled_is_quantize_then_tile(rows, cols, meta_f16):
     assert host(m.meta).tobytes() == host(two.meta).tobytes()
 
 
+@pytest.mark.parametrize("meta_f16", [False, True])
+@pytest.mark.parametrize("groups", [524288, 524289, 524300, 700001])
+def test_quantize_one_and_four_loads_per_wave(groups, meta_f16):
+    """A matrix on either side of the line between the two launches, against its halves, which are below it."""
+    g = torch.Generator(device="cuda").manual_seed(groups)
+    x = torch.empty((groups, 64), dtype=torch.float16, device="cuda").normal_(0.0, 0.02, generator=g)
+    x[1, 3], x[7, 5], x[groups - 1, 63] = float("inf"), float("nan"), -float("inf")
+    codes, meta = B.fg_quantize_groupwise(x, meta_f16=meta_f16)
+    half = [B.fg_quantize_groupwise(p.contiguous(), meta_f16=meta_f16) for p in x.split(groups // 2 + 1)]
+    torch.cuda.synchronize()
+    assert torch.equal(codes, torch.cat([h[0] for h in half]))
+    assert host(meta).tobytes() == torch.cat([h[1] for h in half]).cpu().numpy().tobytes()
+
+
 def test_quantize_empty_input_is_a_noop():
     x = torch.empty((0, 128), dtype=torch.float16, device="cuda")
     codes, meta = B.fg_quantize_groupwise(x)
