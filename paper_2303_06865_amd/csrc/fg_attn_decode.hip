@@ -466,7 +466,8 @@ __global__ __launch_bounds__(64 * block_waves(WPH)) void attn_decode_f16_kernel(
 //   5          96 x 144 127 / 119 / 136 / 268           4    32 x 128 30.0 / 31.5 / 33.5 / 67
 //   2          96 x 80 31 / 33 / 46 / 104
 //   FP16 cache 2 chunks 96 x 80 74 / 70 / 83; 4 chunks 32 x 128 81 / 78 / 76; 5 chunks 96 x 144 355 / 348 / 336;
-//              12 chunks 56 x 37 171 / 150 / 140 / 145
+//              12 chunks 56 x 37 171 / 150 / 140 / 145; by rows, 56 x 512 heads, 1 / 2 waves: 65 173 / 183, 80 201 / 198,
+//              128 (56 x 256) 172 / 160
 // and where the heads are too few for the chip
 //   22 chunks  32 heads 37 / 21 / 13.8 / 11.2           16   160 heads 28 / 17.5 / 12.2 / 10.9
 //   10         256 heads 19.7 / 13.3 / 11.2 / 10.0, 448 heads 20 / 15 / 14.3 / 16.8
@@ -476,9 +477,10 @@ static int waves_by_heads(int64_t heads, int chunks) {
   while (wph > 1 && chunks < wph) wph >>= 1;   // never more waves than chunks
   return wph;
 }
-static int pick_waves_per_head(int64_t heads, int chunks, bool q4) {
+static int pick_waves_per_head(int64_t heads, int rows, int dh, bool q4) {
+  const int chunks = (int)ceil_div(rows, q4 ? 8192 / dh : 64);
   if (q4 && heads <= 256 && chunks >= 5) return 8;
-  const int by_length = q4 ? (chunks >= 7 ? 4 : (chunks >= 5 ? 2 : 1)) : (chunks >= 4 ? 4 : (chunks >= 2 ? 2 : 1));
+  const int by_length = q4 ? (chunks >= 7 ? 4 : (chunks >= 5 ? 2 : 1)) : (chunks >= 4 ? 4 : (rows >= 80 ? 2 : 1));
   const int wph = waves_by_heads(heads, chunks);
   return wph > by_length ? wph : by_length;
 }
@@ -507,7 +509,7 @@ int decode_attention_launch(const fg_model_cfg& cfg, const half_t* q, int64_t q_
   const int64_t heads = (int64_t)b * cfg.nh;
   const bool q4 = kv.dtype == FG_Q4G64 || kv.dtype == FG_Q4G64_H16;
   const bool h16 = kv.dtype == FG_Q4G64_H16;
-  const int wph = pick_waves_per_head(heads, (int)ceil_div(rows, q4 ? 8192 / dh : 64), q4);
+  const int wph = pick_waves_per_head(heads, rows, dh, q4);
   const dim3 grid((unsigned)ceil_div(heads * wph, block_waves(wph)));
   ProfScope prof(FG_K_ATTN_DECODE, stream);
 #define FG_ATTN_LAUNCH(DH_, ...)                                                                      \

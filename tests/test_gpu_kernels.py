@@ -421,7 +421,9 @@ def test_decode_attention_many_heads(b, nh, dh, rows, quant):
 @pytest.mark.parametrize("b,nh,dh,rows,quant", [
     (41, 51, 128, 330, True),     # 2091 heads of six chunks: two waves per head
     (41, 51, 128, 450, True),     # ... of eight: four
-    (41, 51, 64, 130, False),     # FP16 cache, three chunks: two waves per head
+    (41, 51, 64, 79, False),      # FP16 cache, little more than one chunk: one wave per head
+    (41, 51, 128, 80, False),     # ... two
+    (41, 51, 64, 130, False),     # three chunks: two waves per head
     (41, 51, 64, 200, False),     # four chunks: four
     (17, 15, 128, 260, True),     # 255 heads of five chunks: eight waves per head
     (16, 16, 64, 1030, True),     # 256 heads of nine chunks, one of them for a single wave
