@@ -1,8 +1,8 @@
 // Fused dequant + GEMM for the decode-phase projections (Section 3: t.wQ, t.wK, t.wV, .wO, .w1, .w2
 // with the weights stored as in Section 5), for a small number of activation rows M (the block
 // of sequences in a decode step), on weights in the CANONICAL row-major 4-bit format, and on FP16
-// weights whose shape the streaming kernels do not take (N % 32 != 0), from 33 rows up (fewer rows:
-// fg_gemm_fewrows.hip).  Tiled 4-bit weights and the common FP16 cases go through fg_gemm_stream.hip,
+// weights whose shape the streaming kernels do not take (N % 32 != 0), beyond the lines of
+// gemm_fewrows_takes (4-bit from 33 rows up, FP16 from 17).  Tiled 4-bit weights and the common FP16 cases go through fg_gemm_stream.hip,
 // which is faster: in the canonical format the 32 bytes a lane pair needs per K step lie K/2 bytes
 // apart from row to row.
 //
@@ -335,10 +335,8 @@ int launch_t(const SmallArgs& a, hipStream_t stream) {
 
 template <bool Q4>
 int launch_q(int mt, const SmallArgs& a, hipStream_t stream) {
-  if constexpr (!Q4) {   // 4-bit weights come here from 33 rows up (gemm_fewrows_takes)
-    if (mt == 1) return launch_t<1, Q4>(a, stream);
+  if constexpr (!Q4)   // 4-bit weights come here from 33 rows up, FP16 weights from 17 (gemm_fewrows_takes)
     if (mt == 2) return launch_t<2, Q4>(a, stream);
-  }
   switch (mt) {
     case 3: return launch_t<3, Q4>(a, stream);
     case 4: return launch_t<4, Q4>(a, stream);

@@ -138,9 +138,9 @@ static bool use_f16w(int dtype, int64_t n, int64_t k, int64_t m) {
 }
 
 // A few rows: the kernel that splits nothing over workgroups, on every weight format.  (FG_F16W_COLS in the
-// environment asks for the narrow-tile kernel on FP16 weights: gemm_f16w_pick_cols.)
+// environment asks for the narrow-tile kernel where it takes the call: gemm_f16w_pick_cols.)
 static bool use_fewrows(int dtype, int64_t n, int64_t k, int64_t m) {
-  return gemm_fewrows_takes(dtype, n, k, m) && !(dtype == FG_F16 && gemm_f16w_forced(n));
+  return gemm_fewrows_takes(dtype, n, k, m) && !(use_f16w(dtype, n, k, m) && gemm_f16w_forced(n));
 }
 
 // What a call asks of its caller (and is refused without) is that of the kernels that split the contraction, also where

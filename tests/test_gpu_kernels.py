@@ -255,6 +255,14 @@ def test_linear_f16_weights_narrow_tiles(m, n, k, bias, relu, residual, cols, mo
     assert_close(got, ref, "linear f16w m=%d n=%d k=%d cols=%d" % (m, n, k, cols))
 
 
+@pytest.mark.parametrize("m,n", [(4, 48), (16, 1008), (29, 80)])
+def test_linear_f16_weights_narrow_tiles_asked_for_in_vain(m, n, monkeypatch):
+    """FG_F16W_COLS where 32 does not divide the columns, which the narrow-tile streamer does not take."""
+    monkeypatch.setenv("FG_F16W_COLS", "1")
+    got, ref = _linear_case(m, n, 320, False, True, False, True, seed=m + n)
+    assert_close(got, ref, "linear f16w in vain m=%d n=%d" % (m, n))
+
+
 @pytest.mark.parametrize("quant", [True, False])
 @pytest.mark.parametrize("m,n,k,bias,relu,residual", [
     (600, 768, 768, True, False, True),
