@@ -16,15 +16,15 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("vocab", [8, 256, 264, 1000, 1024, 1032, 2048, 2056, 4096, 4104, 8192, 8200, 16384, 16392, 50272, 65536,
                                    65544, 131080])
 def test_argmax_is_the_lowest_index_of_the_maximum(vocab, offset):
-    """Every embedding row that attains the largest logit occurs again at other columns, the last one among them; with
+    """Every embedding row that attains the largest logit occurs at three columns, one near the end; with
     offset 1 the logits start 4 bytes off a 16-byte boundary."""
-    rows, h1 = 5, 64
+    rows, h1 = 5 if vocab >= 1000 else 1, 64   # (few columns hold the three of one row)
     cfg = B.Cfg(h1, 1, 64, vocab, 8)
     g = torch.Generator(device="cuda").manual_seed(vocab)
     half = lambda *s: torch.empty(s, dtype=torch.float16, device="cuda").normal_(0.0, 1.0, generator=g)
     x, gamma, beta, emb = half(rows, h1), half(h1), half(h1), half(vocab, h1)
     for r in range(rows):                     # the row's strongest embedding, at three columns
-        at = [(7 * r + 3) % vocab, (vocab // 2 + r) % vocab, vocab - 1 - r % 3]
+        at = [7 * r + 3, vocab // 2 + r, vocab - 1 - r]
         y = torch.nn.functional.layer_norm(x[r].float(), (h1,), gamma.float(), beta.float())
         emb[at] = (3.0 * y.sign()).half()
     buf = torch.empty(rows * vocab + 1, dtype=torch.float32, device="cuda")
@@ -38,5 +38,5 @@ def test_argmax_is_the_lowest_index_of_the_maximum(vocab, offset):
     assert rc == 0
     torch.cuda.synchronize()
     lg = host(logits)
-    assert (lg == lg.max(axis=1, keepdims=True)).sum(axis=1).min() >= 1
+    assert (lg == lg.max(axis=1, keepdims=True)).sum(axis=1).min() == 3   # the ties are there
     assert np.array_equal(host(ids), np.argmax(lg, axis=1).astype(np.int32))

@@ -82,6 +82,19 @@ def test_linear_blocks_of_192_rows(m, n, k, fmt):
     test_linear_shared_contraction(m, n, k, fmt)
 
 
+# Canonical 4-bit weights past the lines of the few-rows kernel, and FP16 weights whose columns 32 does not divide, which
+# neither streaming kernel takes: every row tile count, ragged columns, contractions that end inside a step of 128.
+@pytest.mark.parametrize("fmt,m,n,k", [
+    ("q4", 33, 36864, 12288), ("q4", 64, 33800, 8896), ("q4", 96, 20488, 9792), ("q4", 128, 16392, 9280),
+    ("q4", 144, 12872, 9664), ("q4", 160, 12296, 9792), ("q4", 300, 8200, 7360), ("q4", 512, 6152, 6208),
+    ("q4", 600, 4104, 3904), ("q4", 1000, 3080, 3072),
+    ("f16", 20, 32776, 128), ("f16", 32, 32792, 192), ("f16", 50, 5000, 3456), ("f16", 64, 5000, 3456), ("f16", 100, 3016, 2880),
+    ("f16", 128, 3016, 2880), ("f16", 144, 4104, 3520), ("f16", 300, 2056, 3456), ("f16", 512, 1544, 2880), ("f16", 600, 1032, 3648),
+])
+def test_linear_small_and_large_m_past_the_few_rows_lines(fmt, m, n, k):
+    _check(m, n, k, fmt == "q4", False, False)
+
+
 # Both sides of the lines between blocks of 32 rows over whole contractions and the kernels that take the rest.
 @pytest.mark.parametrize("fmt,m,n,k", [
     ("f16", 1, 1024, 10304), ("f16", 1, 1056, 10304), ("f16", 8, 1280, 10304), ("f16", 8, 1312, 10304), ("f16", 16, 1696, 10304),

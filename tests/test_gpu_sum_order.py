@@ -1,10 +1,11 @@
 """The order of additions that results downstream depend on: LayerNorm's sums, bit for bit, at every width that its launch
-rules tell apart.
+rules tell apart; and a 12288-wide decode layer on an FP16 cache, where no 4-bit code can move.
 
 A projection behind a LayerNorm whose sums run in another order differs by last bits, and where its output is quantized
 into the cache a last bit can be a whole code step; so the order is held fixed here, not only the value."""
 import numpy as np
 import pytest
+import torch
 
 from paper_2303_06865_amd import binding as B
 from tests.util import dev, host
@@ -66,3 +67,38 @@ def test_layernorm_sums_in_order(rows, cols):
     out = host(B.fg_layernorm(dev(x), dev(g), dev(b), 1e-5))
     assert np.array_equal(out.view(np.uint16), layernorm_in_order(x, g, b, 1e-5).view(np.uint16))
 
+
+def test_decode_layer_175b_wide_f16_cache():
+    """144 sequences, tiled 4-bit weights, against binary32 with an FP16 rounding wherever the layer stores FP16.  Seven
+    stored tensors lie in a row.  If a last bit of a sum turned every one of their roundings over, they would add up to
+    sqrt(7) 2^-11 = 1.3e-3 in the 2-norm; half of that, and single values within 1e-2 of the root mean square, are far
+    from what a moved code of a 4-bit cache does (up to 0.06)."""
+    b, nh, dh, t = 144, 96, 128, 130
+    h1, h2 = nh * dh, 4 * nh * dh
+    cfg = B.Cfg(h1, nh, h2, 1000, 4096)
+    g = torch.Generator(device="cuda").manual_seed(12)
+    half = lambda shape, std=1.0: torch.empty(shape, dtype=torch.float16, device="cuda").normal_(0.0, std, generator=g)
+    mats, dense = [], []
+    for n, k in ((3 * h1, h1), (h1, h1), (h2, h1), (h1, h2)):
+        w = half((n, k), 0.02)
+        mats.append(B.Mat.from_f16(w, True, tiled=True))
+        dense.append(B.fg_dequantize_groupwise(*B.fg_quantize_groupwise(w)).view(n, k).half())
+    ones, zeros = torch.ones(h1, dtype=torch.float16, device="cuda"), torch.zeros(h1, dtype=torch.float16, device="cuda")
+    kv = B.KVCache(cfg, b, t + 2, False, zero=False)
+    for c in (kv.k_codes, kv.v_codes):
+        c.normal_(0.0, 1.0, generator=g)
+    x = half((b, h1))
+    r16 = lambda a: a.half().float()
+    lin = lambda a, w: a @ w.float().t()
+    norm = lambda a: r16(torch.nn.functional.layer_norm(a.double(), (h1,), eps=1e-5))
+    q, k, v = r16(lin(norm(x.float()), dense[0])).view(b, 3, nh, dh).unbind(1)
+    rows = lambda c, new: torch.cat([c.view(b, nh, t + 2, dh)[:, :, :t].float(), new[:, :, None]], 2)
+    kk, vv = rows(kv.k_codes, k), rows(kv.v_codes, v)
+    p = torch.softmax((kk * q[:, :, None]).sum(-1) / dh ** 0.5, -1)
+    o = r16((p[..., None] * vv).sum(2).reshape(b, h1))
+    x1 = r16(lin(o, dense[1]) + x.float())
+    want = r16(lin(r16(torch.relu(lin(norm(x1), dense[2]))), dense[3]) + x1)
+    got = B.fg_decode_layer(cfg, B.LayerWeights(*mats, ones, zeros, ones, zeros), x, t, kv).float()
+    d, rms = (got - want).abs(), want.square().mean().sqrt()
+    assert float(d.norm() / want.norm()) <= 6.3e-4
+    assert float(d.max() / rms) <= 1e-2

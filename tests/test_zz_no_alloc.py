@@ -28,7 +28,10 @@ def _case(m, n, k, seed, wdtype):
 def test_static_scratch_linear_matches_workspace_linear_twice_in_a_row(wdtype):
     # first a projection whose partial sums fill most of the scratch (144 rows, split contraction), then a
     # smaller one with a ragged row count that finds the first call's partial sums still in place
-    for (m, n, k, seed) in ((144, 4096, 12288, 1), (37, 1024, 2048, 2)):
+    # (those of `split` are beyond what one pass over the whole contraction takes in that format)
+    split = {"q4t": ((144, 4096, 12288, 1), (33, 12832, 4416, 3)), "f16": ((144, 4096, 12288, 1), (37, 4096, 4416, 3)),
+             "q4": ((144, 12872, 9664, 1), (100, 15368, 9792, 3))}[wdtype]
+    for (m, n, k, seed) in ((144, 4096, 12288, 1), (37, 1024, 2048, 2)) + split:
         mat, bias, x, res = _case(m, n, k, seed, wdtype)
         need = B.lib().fg_linear_workspace_bytes(C.byref(mat.c), m)
         assert need <= B.lib().fg_linear_static_scratch_bytes()
