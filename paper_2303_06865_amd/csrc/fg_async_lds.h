@@ -50,7 +50,8 @@ static inline int work_parts(int64_t total, int ksteps, int grid) {
 }
 
 // Sum, in ascending K order, of what ranges lo .. hi left of a tile: v[i] = float4 number `at + i * step` of each
-// range's slot (2 slots of slot4 float4s per range).  The loads of eight ranges are in flight together.
+// range's slot (2 slots of slot4 float4s per range).  The loads of eight ranges are in flight together, of four with two
+// items.
 template <int ITEMS>
 __device__ __forceinline__ void sum_parts(const float4* partial, int64_t slot4, const TileParts& tp, int64_t at, int64_t step,
                                           float4 (&v)[ITEMS]) {

@@ -1,8 +1,8 @@
 // Decode-phase attention over the stored KV cache (Section 3, decode: softmax(tQ.K^T/sqrt(h)).V),
 // with the cache read in its storage format of Section 5 and dequantized in registers.
 //
-// WPH = 1, 2, 4 or (4-bit caches) 8 waves per (sequence, head), four waves per workgroup (eight where they
-// share a head).  The rows of that head's K and V are one contiguous byte stream in the cache, read 16 bytes
+// WPH = 1, 2, 4 or (4-bit caches that are not paged) 8 waves per (sequence, head), four waves per workgroup (eight
+// where they share a head).  The rows of that head's K and V are one contiguous byte stream in the cache, read 16 bytes
 // per lane (1 KiB per wave load).
 // The waves of a head take 4 KiB chunks of the stream round-robin, keep a running (max, sum, output)
 // triple each, and the triples are merged through LDS at the end (log-sum-exp merge); with one wave
@@ -44,11 +44,11 @@ struct AttnArgs {
   int table_stride, n_seqs, n_pages, rows_bias;
 };
 
-// Merge the WPH per-wave triples of each head of the block and write the outputs.  o_w already
-// includes the per-group constant term.  out0 = output row of the block's first head.
 // waves of a workgroup: four, or all of one head where more than four share it
 constexpr int block_waves(int wph) { return wph > 4 ? wph : 4; }
 
+// Merge the WPH per-wave triples of each head of the block and write the outputs.  o_w already
+// includes the per-group constant term.  out0 = output row of the block's first head.
 template <int DH, int WPH>
 __device__ __forceinline__ void merge_and_store(const float* sm_m, const float* sm_l, const float* sm_o, half_t* out0,
                                                 int heads_valid) {

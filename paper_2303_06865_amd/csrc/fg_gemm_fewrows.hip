@@ -9,8 +9,9 @@
 //   * A workgroup owns 16 CT output columns over the WHOLE contraction; its NW waves take NW ranges of it and meet
 //     once in LDS: no partial sums in memory and no reduction pass (which took as long as the contraction: 8-23 us
 //     behind 10-15 us on the OPT-6.7B shapes, 39 us on a 768-wide layer).
-//   * Weights go straight to registers, 16 bytes per lane and load, two steps of 128 ahead, without a barrier in
-//     the loop.  A lane holds 32 consecutive codes of one column (the 16 bytes that every 4-bit layout stores
+//   * Weights go straight to registers, 16 bytes per lane and load, two steps of 128 on their way at a time, without a
+//     barrier in the loop.  (The compiler's one wait per pair of steps is for everything in flight, the step requested
+//     last among it, so every pair exposes a memory latency.)  A lane holds 32 consecutive codes of one column (the 16 bytes that every 4-bit layout stores
 //     together), so a step is four MFMAs per column tile, the i-th taking elements 8 i .. 8 i + 7 of every lane's
 //     32: lane (row, kb) of the activation operand holds k = 128 step + 32 kb + 8 i.  (One 4-byte load per MFMA,
 //     with k in its natural order, was up to twice as slow: the loads are bound by their number.)
@@ -232,7 +233,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_fewrows_kernel(FewArgs a) {
   };
 
   // Two steps in flight, none loaded twice (a 768-wide contraction is one step per wave).  The steady loop has
-  // no condition around its loads, so that the compiler's wait counts leave the younger step in flight.
+  // no condition around its loads.
   int s = a.steps * wave / NW;
   const int s1 = a.steps * (wave + 1) / NW;
   Buf b0, b1;
@@ -256,7 +257,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_fewrows_kernel(FewArgs a) {
   if (left == 3) compute(b0, 0, s + 2);
 
   // ---- the waves' sums meet in LDS (over the rings: every copy has landed and been read); thread t finishes
-  // item t, t + 512, ... of (row tile, column tile, lane)
+  // items t, t + 64 NW, ... of (row tile, column tile, lane)
   __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   float4(*red)[MT * CT][64] = reinterpret_cast<float4(*)[MT * CT][64]>(smem);
