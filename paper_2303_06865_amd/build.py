@@ -16,6 +16,7 @@ SOURCES = [
     "fg_quant.hip",
     "fg_norm.hip",
     "fg_gemm_fewrows.hip",
+    "fg_gemm_fewrows_ln.hip",
     "fg_gemm_small_m.hip",
     "fg_gemm_large_m.hip",
     "fg_gemm_stream.hip",

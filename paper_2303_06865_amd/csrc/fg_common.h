@@ -79,6 +79,11 @@ int linear_launch(const LinearArgs& a, void* ws, size_t ws_bytes, hipStream_t st
 // a few rows, any weight format (csrc/fg_gemm_fewrows.hip); needs no workspace
 bool gemm_fewrows_takes(int dtype, int64_t n, int64_t k, int64_t m);
 int gemm_fewrows_launch(const LinearArgs& a, hipStream_t stream);
+// ... of LayerNorm(a.x), with FP16 results and no residual (csrc/fg_gemm_fewrows_ln.hip; ct: column tiles per workgroup)
+bool gemm_ln_fewrows_takes(int dtype, int64_t n, int64_t k, int64_t m);
+int gemm_ln_fewrows_launch(const LinearArgs& a, const half_t* gamma, const half_t* beta, float eps, hipStream_t stream);
+bool gemm_fewrows_ln_takes(int dtype, int64_t n, int64_t k, int64_t m, int ct);
+int gemm_fewrows_ln_launch(const LinearArgs& a, const half_t* gamma, const half_t* beta, float eps, int ct, hipStream_t stream);
 // small-M (decode) and large-M (prefill) kernels behind linear_launch
 size_t gemm_small_m_workspace(int dtype, int64_t n, int64_t k, int64_t m);
 int gemm_small_m_launch(const LinearArgs& a, void* ws, size_t ws_bytes, hipStream_t stream);

@@ -445,6 +445,16 @@ bool gemm_fewrows_takes(int dtype, int64_t n, int64_t k, int64_t m) {
   return size <= 110000000 / blocks && wide <= (k < 256 ? 65536 : (n <= 8192 ? 131072 : 98304));
 }
 
+bool gemm_ln_fewrows_takes(int dtype, int64_t n, int64_t k, int64_t m) {
+  return gemm_fewrows_takes(dtype, n, k, m) &&
+         gemm_fewrows_ln_takes(dtype, n, k, m, pick_ct(dtype == FG_F16 ? kFewF16 : kFewQ4, n, m));
+}
+
+int gemm_ln_fewrows_launch(const LinearArgs& la, const half_t* gamma, const half_t* beta, float eps, hipStream_t stream) {
+  ProfScope prof(FG_K_GEMM_SMALL_M, stream);
+  return gemm_fewrows_ln_launch(la, gamma, beta, eps, pick_ct(la.dtype == FG_F16 ? kFewF16 : kFewQ4, la.n, la.m), stream);
+}
+
 int gemm_fewrows_launch(const LinearArgs& la, hipStream_t stream) {
   if (la.m == 0 || la.n == 0) return FG_OK;
   const FewArgs a = make_few(la);

@@ -182,6 +182,20 @@ static LinearArgs make_linear(const fg_mat& w, const void* bias, const half_t* x
   return a;
 }
 
+// A projection of LayerNorm(a.x): in one launch where a kernel takes the LayerNorm in, else by way of y [m, k].
+static int ln_linear_launch(LinearArgs a, const void* gamma, const void* beta, float eps, half_t* y, void* ws, size_t ws_bytes,
+                            hipStream_t stream) {
+  const half_t* g = reinterpret_cast<const half_t*>(gamma);
+  const half_t* b = reinterpret_cast<const half_t*>(beta);
+  if (use_fewrows(a.dtype, a.n, a.k, a.m) && gemm_ln_fewrows_takes(a.dtype, a.n, a.k, a.m))
+    return gemm_ln_fewrows_launch(a, g, b, eps, stream);
+  const int rc = layernorm_launch(a.x, a.ldx, g, b, a.m, a.k, eps, y, a.k, stream);
+  if (rc) return rc;
+  a.x = y;
+  a.ldx = a.k;
+  return linear_launch(a, ws, ws_bytes, stream);
+}
+
 // ---------------------------------------------------------------- one layer
 // Row stride of the FFN hidden buffer: h2 plus one 128-byte line.  With rows exactly h2 * 2 bytes apart
 // (96 KiB at h2 = 49152) the 256 rows of an activation tile that a K step of the second FFN projection
@@ -244,11 +258,8 @@ static int run_layer(const fg_model_cfg& c, const fg_layer_weights& w, const hal
   // the row count, so a buffer sized for more rows need not be large enough
   if (L.total > ws_bytes) return FG_ERR_WORKSPACE;
   int rc;
-  if ((rc = layernorm_launch(x_in, h1, reinterpret_cast<const half_t*>(w.ln1_g),
-                             reinterpret_cast<const half_t*>(w.ln1_b), rows, h1, c.ln_eps, L.y, h1, st)))
-    return rc;
-  if ((rc = linear_launch(make_linear(w.wqkv, w.bqkv, L.y, h1, rows, nullptr, 0, 0, L.qkv, 3 * h1), L.gemm,
-                          L.gemm_bytes, st)))
+  if ((rc = ln_linear_launch(make_linear(w.wqkv, w.bqkv, x_in, h1, rows, nullptr, 0, 0, L.qkv, 3 * h1), w.ln1_g, w.ln1_b,
+                             c.ln_eps, L.y, L.gemm, L.gemm_bytes, st)))
     return rc;
   if (paged) {
     if (prefill) {
@@ -282,11 +293,8 @@ static int run_layer(const fg_model_cfg& c, const fg_layer_weights& w, const hal
   if ((rc = linear_launch(make_linear(w.wo, w.bo, L.o, h1, rows, x_in, h1, 0, L.x1, h1), L.gemm, L.gemm_bytes,
                           st)))
     return rc;
-  if ((rc = layernorm_launch(L.x1, h1, reinterpret_cast<const half_t*>(w.ln2_g),
-                             reinterpret_cast<const half_t*>(w.ln2_b), rows, h1, c.ln_eps, L.y, h1, st)))
-    return rc;
-  if ((rc = linear_launch(make_linear(w.w1, w.b1, L.y, h1, rows, nullptr, 0, 1, L.act, act_stride(c)), L.gemm,
-                          L.gemm_bytes, st)))
+  if ((rc = ln_linear_launch(make_linear(w.w1, w.b1, L.x1, h1, rows, nullptr, 0, 1, L.act, act_stride(c)), w.ln2_g, w.ln2_b,
+                             c.ln_eps, L.y, L.gemm, L.gemm_bytes, st)))
     return rc;
   return linear_launch(make_linear(w.w2, w.b2, L.act, act_stride(c), rows, L.x1, h1, 0, x_out, h1), L.gemm, L.gemm_bytes,
                        st);
