@@ -21,6 +21,7 @@
 //             accumulated per lane over its 32 head dimensions with FP16->FP32 mixed FMAs on the
 //             nibbles taken in place as FP16 subnormals, the second is one scalar per group.
 #include "fg_attn_common.h"
+#include "fg_quantize_group.h"
 
 namespace fg {
 
@@ -34,6 +35,9 @@ struct AttnArgs {
   const void* k_meta;   // float2 or (H16) FP16 pairs
   const void* v_meta;
   half_t* out;       // [b, nh*dh]
+  // the token's own key and value rows (APPEND kernels), at the row stride of q; they become cache row rows - 1
+  const half_t* k_new;
+  const half_t* v_new;
   int nh, cap, rows, batch_offset;
   int n_heads;       // b * nh
   float scale;       // 1/sqrt(dh)
@@ -75,8 +79,14 @@ __device__ __forceinline__ void merge_and_store(const float* sm_m, const float* 
 // PAGED: the head's stream is cut into pages of 64 rows (FG_PAGE_ROWS) found through the sequence's
 // row of the page table, and every sequence has its own length.  A wave keeps 64 consecutive table
 // entries in one register (one per lane) and picks the page of a chunk with a lane read.
-template <int DH, int WPH, bool H16, bool PAGED = false>
+//
+// APPEND: the last cache row is the token's own.  The wave that has the last chunk quantizes it, stores it in the cache and
+// puts it in the place of what it loaded from there: a launch less than appending first (2.6 us at 4 sequences x 12 heads,
+// 3.7 at 1 x 32, 5.9 at 144 x 96), for some 60 instructions in one wave per head.  (Not over pages: there two rows of a
+// call may belong to one sequence, and the second has to see the first.)
+template <int DH, int WPH, bool H16, bool PAGED = false, bool APPEND = false>
 __global__ __launch_bounds__(64 * block_waves(WPH), WPH > 4 ? WPH / 4 : 3) void attn_decode_q4_kernel(AttnArgs a) {
+  static_assert(!(PAGED && APPEND), "rows of one sequence may meet in a paged call");
   using meta_t = typename MetaRaw<H16>::type;
   constexpr int GPR = DH / 64;       // quantization groups per row of this head
   constexpr int NS = 2 / GPR;        // scores per lane per chunk (lane owns groups 2L, 2L+1)
@@ -84,6 +94,9 @@ __global__ __launch_bounds__(64 * block_waves(WPH), WPH > 4 ? WPH / 4 : 3) void 
   __shared__ __attribute__((aligned(16))) half_t sm_q[HPB * DH];
   __shared__ float sm_m[NW], sm_l[NW];
   __shared__ float sm_o[WPH > 1 ? NW * DH : 1];
+  // APPEND: codes and pairs of the new key row's groups, then of the new value row's
+  __shared__ __attribute__((aligned(16))) uint32_t sm_new[APPEND ? HPB : 1][2 * GPR][8];
+  __shared__ meta_t sm_new_meta[APPEND ? HPB : 1][2 * GPR];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -172,11 +185,62 @@ __global__ __launch_bounds__(64 * block_waves(WPH), WPH > 4 ? WPH / 4 : 3) void 
   Buf b0, b1;
   if (part < n_chunks) load(b0, part);
 
+  // (wave-uniform; eight lanes per group, lanes beyond the new row's groups repeat them)
+  const bool appends = APPEND && part == (n_chunks - 1) % WPH;
+  const int new_group = (lane >> 3) & (2 * GPR - 1);   // K groups, then V groups
+  h8_t new_v;
+  if (APPEND && appends)
+    new_v = *reinterpret_cast<const h8_t*>((new_group < GPR ? a.k_new : a.v_new) + (int64_t)seq * a.q_stride + head * DH +
+                                           (new_group & (GPR - 1)) * kGroup + (lane & 7) * 8);
+
   half_t* my_q = sm_q + hl * DH;
   if (part == 0 && lane < DH / 8)
     *reinterpret_cast<u4_t*>(my_q + lane * 8) =
         *reinterpret_cast<const u4_t*>(a.q + (int64_t)seq * a.q_stride + head * DH + lane * 8);
   __syncthreads();
+
+  if (APPEND && appends) {
+    uint32_t p;
+    float mn, sc;
+    quantize_group_8lanes<H16>(new_v, p, mn, sc);
+    meta_t pair;
+    if constexpr (H16)
+      pair = (h2_t){(half_t)mn, (half_t)sc};
+    else
+      pair = make_float2(mn, sc);
+    const int hs = APPEND ? hl : 0;
+    sm_new[hs][new_group][lane & 7] = p;
+    sm_new_meta[hs][new_group] = pair;
+    if (lane < 16 * GPR) {
+      const int64_t g = (hrow + rows - 1) * GPR + (new_group & (GPR - 1));
+      uint8_t* codes = const_cast<uint8_t*>(new_group < GPR ? kc : vc);
+      *reinterpret_cast<uint32_t*>(codes + g * 32 + (lane & 7) * 4) = p;
+      if ((lane & 7) == 0) const_cast<meta_t*>(new_group < GPR ? km : vm)[g] = pair;
+    }
+  }
+  // the new row in the place of what the cache held there
+  auto put_new = [&](Buf& b, int chunk) {
+    const int hs = APPEND ? hl : 0, first = G - GPR, gbase = chunk << 7;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      int g = gbase + 32 * i + 2 * r + h;
+      g = (g < G ? g : G - 1) - first;
+      if (g >= 0) {
+        b.kq[i] = *reinterpret_cast<const u4_t*>(&sm_new[hs][g][half * 4]);
+        b.vq[i] = *reinterpret_cast<const u4_t*>(&sm_new[hs][GPR + g][half * 4]);
+      }
+    }
+    const int g0 = gbase + 2 * lane, g1 = g0 + 1;
+    const int c0 = (g0 < G ? g0 : G - 1) - first, c1 = (g1 < G ? g1 : G - 1) - first;
+    if (c0 >= 0) {
+      b.km0 = sm_new_meta[hs][c0];
+      b.vm0 = sm_new_meta[hs][GPR + c0];
+    }
+    if (c1 >= 0) {
+      b.km1 = sm_new_meta[hs][c1];
+      b.vm1 = sm_new_meta[hs][GPR + c1];
+    }
+  };
 
   QueryOps<DH> Q;
   query_setup<DH>(my_q, lane, Q);
@@ -252,10 +316,12 @@ __global__ __launch_bounds__(64 * block_waves(WPH), WPH > 4 ? WPH / 4 : 3) void 
     const bool more1 = chunk + WPH < n_chunks;
     if (more1) load(b1, chunk + WPH);
     __builtin_amdgcn_sched_barrier(0);
+    if (APPEND && chunk == n_chunks - 1) put_new(b0, chunk);
     process(b0, chunk);
     if (more1) {
       if (chunk + 2 * WPH < n_chunks) load(b0, chunk + 2 * WPH);
       __builtin_amdgcn_sched_barrier(0);
+      if (APPEND && chunk + WPH == n_chunks - 1) put_new(b1, chunk + WPH);
       process(b1, chunk + WPH);
     }
   }
@@ -302,8 +368,10 @@ __global__ __launch_bounds__(64 * block_waves(WPH), WPH > 4 ? WPH / 4 : 3) void 
 // directly (lane = row, 8 consecutive head dimensions per lane).
 // PAGED: a chunk of 64 rows is exactly one page of the sequence (FG_PAGE_ROWS = 64), found through the
 // page table; every sequence has its own length.
-template <int DH, int WPH, bool PAGED = false>
+// APPEND: the last cache row is the token's own, read where the projection left it and stored in the cache on the way.
+template <int DH, int WPH, bool PAGED = false, bool APPEND = false>
 __global__ __launch_bounds__(64 * block_waves(WPH)) void attn_decode_f16_kernel(AttnArgs a) {
+  static_assert(!(PAGED && APPEND), "rows of one sequence may meet in a paged call");
   constexpr int NU = DH / 32;        // 32-wide head-dimension blocks
   constexpr int NW = block_waves(WPH), HPB = NW / WPH;   // waves, heads per workgroup
   __shared__ __attribute__((aligned(16))) half_t sm_q[HPB * DH];
@@ -374,22 +442,30 @@ __global__ __launch_bounds__(64 * block_waves(WPH)) void attn_decode_f16_kernel(
   // chunk right after them, so a wave has 16 to 32 KiB on their way all the time instead of waiting
   // out one load latency for K and another for V in every chunk.
   h8_t kreg[4][NU], vreg[4][NU];
-  auto load_rows = [&](const half_t* base, int chunk, h8_t (&dst)[4][NU]) {
+  const half_t* k_new = APPEND ? a.k_new + (int64_t)seq * a.q_stride + head * DH : nullptr;
+  const half_t* v_new = APPEND ? a.v_new + (int64_t)seq * a.q_stride + head * DH : nullptr;
+  auto load_rows = [&](const half_t* base, const half_t* fresh, int chunk, h8_t (&dst)[4][NU]) {
     const int64_t crow0 = chunk_row0(chunk);
     const int last = n_rows - 1 - (chunk << 6);   // rows of the chunk past the end re-read its last valid row
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      int row = 16 * i + r;
-      row = row < last ? row : last;
+      const int row = 16 * i + r;
+      const half_t* src = base + (crow0 + (row < last ? row : last)) * DH;
+      if (APPEND) src = row < last ? src : fresh;
 #pragma unroll
-      for (int u = 0; u < NU; ++u)
-        dst[i][u] = *reinterpret_cast<const h8_t*>(base + (crow0 + row) * DH + 32 * u + 8 * q4);
+      for (int u = 0; u < NU; ++u) dst[i][u] = *reinterpret_cast<const h8_t*>(src + 32 * u + 8 * q4);
     }
   };
-  if (part < n_chunks) load_rows(kp, part, kreg);
+  if (part < n_chunks) load_rows(kp, k_new, part, kreg);
+  if (APPEND && part == 0 && lane < DH / 4) {   // lanes of the first half: K, of the second: V
+    const bool k = lane < DH / 8;
+    const int at = (k ? lane : lane - DH / 8) * 8;
+    *reinterpret_cast<h8_t*>(const_cast<half_t*>(k ? kp : vp) + (int64_t)(n_rows - 1) * DH + at) =
+        *reinterpret_cast<const h8_t*>((k ? k_new : v_new) + at);
+  }
   for (int chunk = part; chunk < n_chunks; chunk += WPH) {
     const int rbase = chunk << 6;
-    load_rows(vp, chunk, vreg);
+    load_rows(vp, v_new, chunk, vreg);
     __builtin_amdgcn_sched_barrier(0);
     float sc = 0.f;
 #pragma unroll
@@ -400,7 +476,7 @@ __global__ __launch_bounds__(64 * block_waves(WPH)) void attn_decode_f16_kernel(
       sc = q4 == i ? acc[0] : sc;
     }
     __builtin_amdgcn_sched_barrier(0);
-    if (chunk + WPH < n_chunks) load_rows(kp, chunk + WPH, kreg);
+    if (chunk + WPH < n_chunks) load_rows(kp, k_new, chunk + WPH, kreg);
     __builtin_amdgcn_sched_barrier(0);
     sc = (rbase + lane) < n_rows ? sc * a.scale : -INFINITY;
     const float cmax = wave_max(sc);
@@ -485,9 +561,18 @@ static int pick_waves_per_head(int64_t heads, int rows, int dh, bool q4) {
   return wph > by_length ? wph : by_length;
 }
 
+// Where the attention stores the token's own row: one launch less, but in every head's stream the wave with the last chunk
+// has more to do than the others.  Whole layers, appending first / fused, us: 4-bit 32 heads x 1000 rows 31.5 / 29.5, 768 x 300
+// 47.5 / 45.4, 2048 x 300 72.0 / 71.6, 2072 x 1000 151.7 / 149.9; but 13824 x 528 806 / 811, 49152 x 2048 4268 / 4312.  FP16 48
+// x 300 23.4 / 21.7, 512 x 300 47.9 / 46.4, 768 x 300 60.0 / 61.2, 1024 x 300 66.2 / 66.0, 2048 x 300 107.3 / 107.6, 4096 x 528 1499 / 1507 (four layers).
+bool decode_attention_appends(const fg_model_cfg& cfg, const fg_kv_cache& kv, int32_t b) {
+  return (int64_t)b * cfg.nh <= (kv.dtype == FG_F16 ? 512 : 2048);
+}
+
+// k_new, v_new (row stride q_stride): cache row rows - 1 is theirs and is stored on the way; NULL: the cache holds all rows
 int decode_attention_launch(const fg_model_cfg& cfg, const half_t* q, int64_t q_stride, int32_t b,
                             int32_t rows, const fg_kv_cache& kv, int32_t batch_offset, half_t* out,
-                            hipStream_t stream) {
+                            hipStream_t stream, const half_t* k_new, const half_t* v_new) {
   if (b == 0) return FG_OK;
   const int dh = cfg.h1 / cfg.nh;
   AttnArgs a;
@@ -498,6 +583,8 @@ int decode_attention_launch(const fg_model_cfg& cfg, const half_t* q, int64_t q_
   a.k_meta = kv.k_meta;
   a.v_meta = kv.v_meta;
   a.out = out;
+  a.k_new = k_new;
+  a.v_new = v_new;
   a.nh = cfg.nh;
   a.cap = kv.cap;
   a.rows = rows;
@@ -512,45 +599,48 @@ int decode_attention_launch(const fg_model_cfg& cfg, const half_t* q, int64_t q_
   const int wph = pick_waves_per_head(heads, rows, dh, q4);
   const dim3 grid((unsigned)ceil_div(heads * wph, block_waves(wph)));
   ProfScope prof(FG_K_ATTN_DECODE, stream);
-#define FG_ATTN_LAUNCH(DH_, ...)                                                                      \
-  do {                                                                                                \
-    if (wph == 1)                                                                                     \
-      hipLaunchKernelGGL((__VA_ARGS__<DH_, 1 FG_ATTN_EXTRA>), grid, dim3(256), 0, stream, a);         \
-    else if (wph == 2)                                                                                \
-      hipLaunchKernelGGL((__VA_ARGS__<DH_, 2 FG_ATTN_EXTRA>), grid, dim3(256), 0, stream, a);         \
-    else if (wph == 4)                                                                                \
-      hipLaunchKernelGGL((__VA_ARGS__<DH_, 4 FG_ATTN_EXTRA>), grid, dim3(256), 0, stream, a);         \
-    else                                                                                              \
-      hipLaunchKernelGGL((__VA_ARGS__<DH_, 8 FG_ATTN_EXTRA>), grid, dim3(512), 0, stream, a);         \
+  const bool append = k_new != nullptr;
+#define FG_ATTN_Q4(DH_, WPH_, H16_)                                                                                           \
+  do {                                                                                                                        \
+    if (append)                                                                                                               \
+      hipLaunchKernelGGL((attn_decode_q4_kernel<DH_, WPH_, H16_, false, true>), grid, dim3(64 * block_waves(WPH_)), 0, stream, a); \
+    else                                                                                                                      \
+      hipLaunchKernelGGL((attn_decode_q4_kernel<DH_, WPH_, H16_>), grid, dim3(64 * block_waves(WPH_)), 0, stream, a);         \
   } while (0)
-  if (q4 && h16) {
-#define FG_ATTN_EXTRA , true
-    if (dh == 128)
-      FG_ATTN_LAUNCH(128, attn_decode_q4_kernel);
-    else
-      FG_ATTN_LAUNCH(64, attn_decode_q4_kernel);
-#undef FG_ATTN_EXTRA
-  } else if (q4) {
-#define FG_ATTN_EXTRA , false
-    if (dh == 128)
-      FG_ATTN_LAUNCH(128, attn_decode_q4_kernel);
-    else
-      FG_ATTN_LAUNCH(64, attn_decode_q4_kernel);
-#undef FG_ATTN_EXTRA
+#define FG_ATTN_F16(DH_, WPH_, H16_)                                                                       \
+  do {                                                                                                     \
+    if (append)                                                                                            \
+      hipLaunchKernelGGL((attn_decode_f16_kernel<DH_, WPH_, false, true>), grid, dim3(256), 0, stream, a); \
+    else                                                                                                   \
+      hipLaunchKernelGGL((attn_decode_f16_kernel<DH_, WPH_>), grid, dim3(256), 0, stream, a);              \
+  } while (0)
+#define FG_ATTN_WPH(LAUNCH_, DH_, H16_)   \
+  do {                                    \
+    if (wph == 1)                         \
+      LAUNCH_(DH_, 1, H16_);              \
+    else if (wph == 2)                    \
+      LAUNCH_(DH_, 2, H16_);              \
+    else                                  \
+      LAUNCH_(DH_, 4, H16_);              \
+  } while (0)
+  if (wph == 8) {   // 4-bit caches only
+    if (dh == 128) {
+      if (h16) FG_ATTN_Q4(128, 8, true); else FG_ATTN_Q4(128, 8, false);
+    } else {
+      if (h16) FG_ATTN_Q4(64, 8, true); else FG_ATTN_Q4(64, 8, false);
+    }
+  } else if (dh == 128) {
+    if (h16) FG_ATTN_WPH(FG_ATTN_Q4, 128, true);
+    else if (q4) FG_ATTN_WPH(FG_ATTN_Q4, 128, false);
+    else FG_ATTN_WPH(FG_ATTN_F16, 128, false);
   } else {
-#define FG_ATTN_F16(DH_)                                                                              \
-  do {                                                                                                \
-    if (wph == 1)                                                                                     \
-      hipLaunchKernelGGL((attn_decode_f16_kernel<DH_, 1>), grid, dim3(256), 0, stream, a);            \
-    else if (wph == 2)                                                                                \
-      hipLaunchKernelGGL((attn_decode_f16_kernel<DH_, 2>), grid, dim3(256), 0, stream, a);            \
-    else                                                                                              \
-      hipLaunchKernelGGL((attn_decode_f16_kernel<DH_, 4>), grid, dim3(256), 0, stream, a);            \
-  } while (0)
-    if (dh == 128) FG_ATTN_F16(128); else FG_ATTN_F16(64);
-#undef FG_ATTN_F16
+    if (h16) FG_ATTN_WPH(FG_ATTN_Q4, 64, true);
+    else if (q4) FG_ATTN_WPH(FG_ATTN_Q4, 64, false);
+    else FG_ATTN_WPH(FG_ATTN_F16, 64, false);
   }
-#undef FG_ATTN_LAUNCH
+#undef FG_ATTN_WPH
+#undef FG_ATTN_F16
+#undef FG_ATTN_Q4
   FG_LAUNCH_CHECK();
   return FG_OK;
 }
@@ -568,6 +658,7 @@ int decode_attention_paged_launch(const fg_model_cfg& cfg, const half_t* q, int6
   a.k_meta = pages.k_meta;
   a.v_meta = pages.v_meta;
   a.out = out;
+  a.k_new = a.v_new = nullptr;
   a.nh = cfg.nh;
   a.cap = 0;
   a.rows = 0;

@@ -112,9 +112,10 @@ int argmax_launch(const float* logits, int64_t rows, int64_t cols, int32_t* out,
 int kv_append_launch(const fg_model_cfg& cfg, const half_t* k, const half_t* v, int64_t row_stride,
                      int32_t b, int32_t s, const fg_kv_cache& kv, int32_t batch_offset, int32_t pos0,
                      hipStream_t stream);
+bool decode_attention_appends(const fg_model_cfg& cfg, const fg_kv_cache& kv, int32_t b);
 int decode_attention_launch(const fg_model_cfg& cfg, const half_t* q, int64_t q_stride, int32_t b,
                             int32_t rows, const fg_kv_cache& kv, int32_t batch_offset, half_t* out,
-                            hipStream_t stream);
+                            hipStream_t stream, const half_t* k_new = nullptr, const half_t* v_new = nullptr);
 int prefill_attention_launch(const fg_model_cfg& cfg, const half_t* qkv, int32_t b, int32_t s,
                              half_t* out, hipStream_t stream);
 // paged cache (sequences at different steps): s rows per sequence from position pos[i] (nullptr: 0);

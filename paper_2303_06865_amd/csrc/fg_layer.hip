@@ -283,11 +283,14 @@ static int run_layer(const fg_model_cfg& c, const fg_layer_weights& w, const hal
     if ((rc = prefill_attention_launch(c, L.qkv, b, s, L.o, st))) return rc;
     if ((rc = kv_append_launch(c, L.qkv + h1, L.qkv + 2 * h1, 3 * h1, b, s, kv, batch_offset, 0, st))) return rc;
   } else {
-    if ((rc = kv_append_launch(c, L.qkv + h1, L.qkv + 2 * h1, 3 * h1, b, 1, kv, batch_offset, t, st))) return rc;
-    if (topk > 0 && topk < t + 1)   // Section 5, sparse attention (with topk >= rows it IS the dense one)
+    const bool sparse = topk > 0 && topk < t + 1;   // Section 5, sparse attention (with topk >= rows it IS the dense one)
+    const half_t *k = L.qkv + h1, *v = L.qkv + 2 * h1;
+    const bool fused = !sparse && decode_attention_appends(c, kv, b);   // the attention stores the new row itself
+    if (!fused && (rc = kv_append_launch(c, k, v, 3 * h1, b, 1, kv, batch_offset, t, st))) return rc;
+    if (sparse)
       rc = decode_attention_topk_launch(c, L.qkv, 3 * h1, b, t + 1, topk, kv, batch_offset, L.o, nullptr, st);
     else
-      rc = decode_attention_launch(c, L.qkv, 3 * h1, b, t + 1, kv, batch_offset, L.o, st);
+      rc = decode_attention_launch(c, L.qkv, 3 * h1, b, t + 1, kv, batch_offset, L.o, st, fused ? k : nullptr, fused ? v : nullptr);
     if (rc) return rc;
   }
   if ((rc = linear_launch(make_linear(w.wo, w.bo, L.o, h1, rows, x_in, h1, 0, L.x1, h1), L.gemm, L.gemm_bytes,
