@@ -21,6 +21,7 @@ SOURCES = [
     "fg_gemm_large_m.hip",
     "fg_gemm_stream.hip",
     "fg_gemm_f16w.hip",
+    "fg_gemm_f16_tiles.hip",
     "fg_attn_decode.hip",
     "fg_attn_topk.hip",
     "fg_attn_prefill.hip",

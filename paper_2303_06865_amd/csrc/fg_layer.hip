@@ -155,7 +155,14 @@ size_t linear_workspace_bytes(int dtype, int64_t n, int64_t k, int64_t m) {
 
 int linear_launch(const LinearArgs& a, void* ws, size_t ws_bytes, hipStream_t stream) {
   if (use_fewrows(a.dtype, a.n, a.k, a.m)) return gemm_fewrows_launch(a, stream);
-  if (use_f16w(a.dtype, a.n, a.k, a.m)) return gemm_f16w_launch(a, ws, ws_bytes, stream);
+  const bool f16w = use_f16w(a.dtype, a.n, a.k, a.m);
+  if (!(f16w && gemm_f16w_forced(a.n)) && gemm_f16_tiles_takes(a)) {
+    // what the kernels that it takes the call from are refused without; more than that changes nothing
+    const size_t need = linear_workspace_bytes(a.dtype, a.n, a.k, a.m);
+    if (!ws || ws_bytes < need) return FG_ERR_WORKSPACE;
+    return gemm_f16_tiles_launch(a, ws, need, stream);
+  }
+  if (f16w) return gemm_f16w_launch(a, ws, ws_bytes, stream);
   if (use_stream(a.dtype, a.n, a.m)) return gemm_stream_launch(a, ws, ws_bytes, stream);
   if (a.m > kSmallMLimit) return gemm_large_m_launch(a, stream);
   return gemm_small_m_launch(a, ws, ws_bytes, stream);

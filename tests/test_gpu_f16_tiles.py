@@ -1,0 +1,95 @@
+"""fg_linear on FP16 weights from 33 rows up (csrc/fg_gemm_f16_tiles.hip) against binary32: every tile shape, with the contraction
+whole and in two, four and eight ranges, fewer steps than the stages that are copied ahead, rows and columns that end inside
+a tile, both sides of the rows at which it takes over; and what it must leave to the other kernels."""
+import pytest
+import torch
+
+from paper_2303_06865_amd import binding as B
+from tests.util import assert_close
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # m, n, k                 tile (32 x rows, 32 x columns), ranges
+    (1500, 32, 320),        # 1 x 2, one column tile of which half is there
+    (1500, 32, 2048),       # ... four ranges
+    (1500, 32, 64),         # 2 x 2, a single step
+    (2049, 32, 3072),       # ... four ranges, one row in the last block
+    (1500, 32, 4096),       # ... eight
+    (33, 8224, 512),        # 33 rows, the fewest
+    (2049, 512, 64),        # 2 x 3
+    (33, 8224, 8192),       # ... two ranges
+    (33, 6144, 4096),       # ... four
+    (33, 2080, 8192),       # ... eight
+    (129, 8224, 2048),      # 2 x 4
+    (3000, 512, 64),        # 3 x 2
+    (65, 6144, 4096),       # ... two ranges
+    (2049, 96, 4096),       # ... four
+    (2049, 32, 4096),       # ... eight
+    (2049, 768, 128),       # 4 x 2, two steps
+    (1500, 288, 8192),      # ... four ranges
+    (97, 21504, 1088),      # 96 rows and one
+    (128, 20512, 1024),     # 128 rows, a last column tile of 32
+    (66, 17408, 7168),      # 4 x 3
+    (2049, 1056, 192),      # 4 x 4, three steps
+    (100, 4128, 8192),      # ... four ranges
+    (333, 1056, 8192),      # ... eight
+    (2049, 2080, 64),       # 6 x 3
+    (129, 8224, 4096),      # ... two ranges
+    (129, 4128, 8192),      # ... four
+    (193, 2080, 8256),      # ... eight, of 16 and 17 steps
+    (2048, 2304, 256),      # 6 x 4, four steps
+    (385, 12288, 1984),
+    (1500, 4128, 320),      # 8 x 4
+    (257, 20512, 704),
+]
+
+
+def _inputs(m, n, k):
+    g = torch.Generator(device="cuda").manual_seed(m + n + k)
+    half = lambda *s: torch.empty(s, dtype=torch.float16, device="cuda").normal_(0.0, 1.0, generator=g)
+    return half(n, k) * 0.05, half(m, k), half(n), half(m, n)
+
+
+@pytest.mark.parametrize("m,n,k", CASES)
+def test_linear_f16_tiles(m, n, k):
+    w, x, bias, res = _inputs(m, n, k)
+    mat = B.Mat.from_f16(w, False)
+    # the sums, then the results rounded to FP16: 2^-11 of up to about 5 sqrt(k) 0.05 in single values, 1e-2 at sums up to 20
+    y = x.float() @ w.float().t() + bias.float()
+    got = B.fg_linear(mat, bias, x, residual=res, relu=True)
+    top = float(y.abs().max()) + 5.0
+    want = torch.relu(y) + res.float()
+    assert_close(got.cpu().numpy(), want.cpu().numpy(), "m=%d n=%d k=%d" % (m, n, k), mabs=max(1e-2, top * 2.0 ** -11))
+    plain = B.fg_linear(mat, None, x)
+    assert_close(plain.cpu().numpy(), (x.float() @ w.float().t()).cpu().numpy(), "m=%d n=%d k=%d plain" % (m, n, k),
+                 mabs=max(1e-2, top * 2.0 ** -11))
+    assert torch.equal(B.fg_linear(mat, None, x), plain)   # the same bits on every call
+
+
+@pytest.mark.parametrize("m,n,k", [(200, 2304, 768), (64, 6144, 2048), (333, 4096, 1024)])
+def test_bias_and_residual_at_any_address(m, n, k):
+    """Both are FP16 arrays without an alignment of their own: one element past a 16-byte boundary."""
+    w, x, bias, res = _inputs(m, n, k)
+    off = lambda t: torch.cat([t.new_zeros(1), t.flatten()])[1:].view(t.shape)
+    b1, r1 = off(bias), off(res)
+    assert b1.data_ptr() % 16 and r1.data_ptr() % 16
+    mat = B.Mat.from_f16(w, False)
+    want = x.float() @ w.float().t() + bias.float() + res.float()
+    for b, r in ((b1, r1), (bias, r1), (b1, res)):
+        assert_close(B.fg_linear(mat, b, x, residual=r).cpu().numpy(), want.cpu().numpy(), "m=%d n=%d k=%d" % (m, n, k))
+
+
+@pytest.mark.parametrize("rows,vocab,h1", [(100, 34016, 768), (129, 8000, 768), (300, 8032, 1024), (512, 33024, 256)])
+def test_lm_head_rows(rows, vocab, h1):
+    g = torch.Generator(device="cuda").manual_seed(rows + vocab)
+    half = lambda *s: torch.empty(s, dtype=torch.float16, device="cuda").normal_(0.0, 1.0, generator=g)
+    cfg = B.Cfg(h1, h1 // 64, 4 * h1, vocab, 64)
+    emb, x = half(vocab, h1), half(rows, h1)
+    ones, zeros = torch.ones(h1, dtype=torch.float16, device="cuda"), torch.zeros(h1, dtype=torch.float16, device="cuda")
+    ids, logits = B.fg_lm_head_greedy(cfg, x, ones, zeros, emb)
+    want = B.fg_layernorm(x, ones, zeros, 1e-5).float() @ emb.float().t()
+    # binary32 sums in another order: about sqrt(h1) 2^-24 of sums of h1 products of about 1
+    assert float((logits.view(rows, vocab) - want).abs().max()) <= 1e-3
+    best = logits.view(rows, vocab).max(1).values
+    assert torch.equal(logits.view(rows, vocab).gather(1, ids.long().view(-1, 1))[:, 0], best)
