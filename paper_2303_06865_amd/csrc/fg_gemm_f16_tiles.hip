@@ -262,13 +262,8 @@ __global__ __launch_bounds__(256) void gemm_f16_tiles_finish_kernel(TileArgs a, 
   const int row0 = 16 * ((2 * mblk + wm) * mt + m) + 4 * (lane >> 4);
   const int col = 16 * ((2 * n_tile + wn) * nt + ct) + (lane & 15);
   if (row0 >= a.M || col >= a.N) return;
-  uint32_t bias_v = 0, res_v[4] = {0, 0, 0, 0};   // FP16 bits
-  if (a.bias) bias_v = reinterpret_cast<const uint16_t*>(a.bias)[col];
-  if (a.residual) {
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-      res_v[r] = reinterpret_cast<const uint16_t*>(a.residual)[(int64_t)(row0 + r < a.M ? row0 + r : a.M - 1) * a.ldr + col];
-  }
+  FinishRows fin;
+  fin.request(a.bias, a.residual, a.ldr, row0, a.M, col);
   const float4* src = reinterpret_cast<const float4*>(a.partial) +
                       ((int64_t)n_tile * a.splits * a.m_blocks + mblk) * (mt * nt * 256) + blockIdx.y * 256 + tid;
   const int64_t step = (int64_t)a.m_blocks * (mt * nt * 256);
@@ -286,19 +281,7 @@ __global__ __launch_bounds__(256) void gemm_f16_tiles_finish_kernel(TileArgs a, 
         o[3] += v[i].w;
       }
   }
-  auto f32 = [](uint32_t bits) { return (float)__builtin_bit_cast(half_t, (uint16_t)bits); };
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int row = row0 + r;
-    if (row >= a.M) break;
-    float v = o[r] + f32(bias_v);
-    if (a.relu) v = fmaxf(v, 0.f);
-    v += f32(res_v[r]);
-    if (a.out32)
-      a.out32[(int64_t)row * a.ldo + col] = v;
-    else
-      a.out16[(int64_t)row * a.ldo + col] = (half_t)v;
-  }
+  fin.store(make_float4(o[0], o[1], o[2], o[3]), a.relu, a.residual, a.out16, a.out32, a.ldo, row0, a.M, col);
 }
 
 template <int MT, int NT>

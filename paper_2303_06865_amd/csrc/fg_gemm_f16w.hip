@@ -263,23 +263,14 @@ __global__ __launch_bounds__(kNW * 64) void gemm_f16w_finish_kernel(F16wArgs a) 
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l16 = lane & 15, g4 = lane >> 4;
   if (16 * wave >= a.M) return;
   const int ct = blockIdx.y;
+  const int row0 = 16 * wave + 4 * g4;
+  if (row0 >= a.M) return;
+  const int col = ((int)((int64_t)a.rounds * kGrid + blockIdx.x)) * kBN + 16 * ct + l16;
+  FinishRows fin;
+  fin.request(a.bias, a.residual, a.ldr, row0, a.M, col);
   float4 v[1];
   sum_parts<1>(reinterpret_cast<const float4*>(a.partial), (int64_t)kNW * 16 * kBN / 4, tp, (int64_t)ct * (kNW * 64) + tid, 0, v);
-  const int col = ((int)((int64_t)a.rounds * kGrid + blockIdx.x)) * kBN + 16 * ct + l16;
-  const float o[4] = {v[0].x, v[0].y, v[0].z, v[0].w};
-  const float bvv = a.bias ? (float)a.bias[col] : 0.f;
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int row = 16 * wave + 4 * g4 + r;
-    if (row >= a.M) continue;
-    float x = o[r] + bvv;
-    if (a.relu) x = fmaxf(x, 0.f);
-    if (a.residual) x += (float)a.residual[(int64_t)row * a.ldr + col];
-    if (a.out32)
-      a.out32[(int64_t)row * a.ldo + col] = x;
-    else
-      a.out16[(int64_t)row * a.ldo + col] = (half_t)x;
-  }
+  fin.store(v[0], a.relu, a.residual, a.out16, a.out32, a.ldo, row0, a.M, col);
 }
 
 template <int MT32, int CT>
