@@ -9,11 +9,12 @@ namespace {
 // ---- work shared along K: `total` (tile, K step) units cut into `parts` equal contiguous ranges, parts <= total.
 // first unit of range p (p >= parts: the end)
 __device__ __forceinline__ int64_t work_begin(int64_t total, int parts, int p) { return p < parts ? (total * p) / parts : total; }
-// the range of workgroup blockIdx.x: consecutive ranges on one XCD, all XCDs equally loaded; >= parts: none
-__device__ __forceinline__ int part_of_block(int parts) {
-  const int per_xcd = (parts + 7) >> 3, i = blockIdx.x >> 3;
-  return i < per_xcd ? (int)(blockIdx.x & 7) * per_xcd + i : parts;
+// the range of workgroup `block`: consecutive ranges on one XCD, all XCDs equally loaded; >= parts: none
+__device__ __forceinline__ int part_of_block(int parts, int block) {
+  const int per_xcd = (parts + 7) >> 3, i = block >> 3;
+  return i < per_xcd ? (block & 7) * per_xcd + i : parts;
 }
+__device__ __forceinline__ int part_of_block(int parts) { return part_of_block(parts, (int)blockIdx.x); }
 // ranges lo .. hi share tile t of `ksteps` units; the tile is the first segment of every one of them but perhaps of lo
 struct TileParts {
   int lo, hi;

@@ -251,6 +251,30 @@ __device__ __forceinline__ void dequant8_exact(uint32_t x, float s24, float s20,
   p[3] = r3;
 }
 
+// The same numbers from a {min, scale} pair of FP16 numbers: codes placed at bits 6..9 of each half are the FP16 subnormals
+// c * 2^-18, scale * 2^18 is exact, and v_pk_fma_f16 rounds c * scale + min once, two weights at a time.  Sixteen VALU
+// instructions per eight weights, of 56 cycles together where the thirteen of dequant8_exact take 85 (v_fma_mixlo_f16 and
+// v_fma_mixhi_f16: 9 each).  For scales below 0.25, else scale * 2^18 is no finite FP16 number: dequant8_pk_takes().
+struct PkPair {
+  h2_t s18, mn;
+};
+__device__ __forceinline__ bool dequant8_pk_takes(uint32_t pair) { return (pair & 0x7fff0000u) < 0x34000000u; }
+__device__ __forceinline__ PkPair dequant8_pk_pair(uint32_t pair) {
+  const h2_t s = __builtin_bit_cast(h2_t, __builtin_amdgcn_perm(pair, pair, 0x03020302u));
+  const h2_t k = {(half_t)512.0f, (half_t)512.0f};
+  return {s * k * k, __builtin_bit_cast(h2_t, __builtin_amdgcn_perm(pair, pair, 0x01000100u))};
+}
+__device__ __forceinline__ void dequant8_pk(uint32_t x, const PkPair& q, uint32_t p[4]) {
+  uint32_t d[4] = {(x << 6) & 0x03C003C0u, (x << 2) & 0x03C003C0u, (x >> 2) & 0x03C003C0u, (x >> 6) & 0x03C003C0u};
+#pragma unroll
+  for (int i = 0; i < 4; ++i)   // halves: weights i and i + 4
+    d[i] = __builtin_bit_cast(uint32_t, __builtin_elementwise_fma(__builtin_bit_cast(h2_t, d[i]), q.s18, q.mn));
+  p[0] = __builtin_amdgcn_perm(d[1], d[0], 0x05040100u);
+  p[1] = __builtin_amdgcn_perm(d[3], d[2], 0x05040100u);
+  p[2] = __builtin_amdgcn_perm(d[1], d[0], 0x07060302u);
+  p[3] = __builtin_amdgcn_perm(d[3], d[2], 0x07060302u);
+}
+
 // Reorder eight consecutive FP16 values h0..h7 (four words) into the pair order produced by
 // unpack8_*: (h0,h4),(h1,h5),(h2,h6),(h3,h7), so that a contraction against unpacked codes lines up.
 __device__ __forceinline__ u4_t permute8_like_codes(u4_t d) {

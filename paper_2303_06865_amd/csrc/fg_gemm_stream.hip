@@ -531,7 +531,7 @@ __device__ __forceinline__ void mfma16_inplace_v(f4_t& acc, const h8_t& a, const
   __asm__ volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
 }
 
-template <int MT16, bool H16M>
+template <int MT16>
 struct Dec16Cfg {
   static constexpr int kMT32 = (MT16 + 1) / 2;
   static constexpr int kRowsLds = kMT32 * 32;             // rows of the activation tile in a stage (copied in 8-row pieces)
@@ -543,9 +543,9 @@ struct Dec16Cfg {
   static constexpr int kCopies = kACopies + 4;
 };
 
-template <int MT16, bool H16M>
+template <int MT16>
 __global__ __launch_bounds__(256) void gemm_decode16_kernel(StreamArgs a) {
-  using C = Dec16Cfg<MT16, H16M>;
+  using C = Dec16Cfg<MT16>;
   constexpr int kAStage = C::kAStage, kStageBytes = C::kStageBytes, kNST = C::kNST;
   constexpr int kACopies = C::kACopies, kCopies = C::kCopies;
   constexpr int kWait = (kNST - 2) * kCopies;
@@ -569,8 +569,8 @@ __global__ __launch_bounds__(256) void gemm_decode16_kernel(StreamArgs a) {
   for (int sl = 0; sl < 2; ++sl) a_off[sl] = (l16 * kKS + swz(l16, 4 * sl + g4) * 8) * 2;
   // code word of (column tile ct, slice sl): + (ct >> 1) * 1024 + (ct & 1) * 256 + sl * 512
   const int bq_off = kAStage + wave * 2 * 1024 + l16 * 16 + g4 * 4;
-  // {min, scale} of column tile ct: + (ct >> 1) * 256 + (ct & 1) * 16 * (H16M ? 4 : 8)
-  const int bm_off = kAStage + 8 * 1024 + wave * 2 * 256 + l16 * (H16M ? 4 : 8);
+  // {min, scale} of column tile ct: + (ct >> 1) * 256 + (ct & 1) * 128
+  const int bm_off = kAStage + 8 * 1024 + wave * 2 * 256 + l16 * 8;
   const uint32_t lds0 = (uint32_t)(uintptr_t)(lptr_t)smem;
 
   while (round < a.rounds || pos < rem_end) {
@@ -616,7 +616,7 @@ __global__ __launch_bounds__(256) void gemm_decode16_kernel(StreamArgs a) {
       nt = nt < a.n32 ? nt : a.n32 - 1;   // ragged last column block: load valid data, never store it
       w_src[j] = a.w + (int64_t)nt * a.ksteps * 1024 + lane * 16;
       m_src[j] = reinterpret_cast<const float*>(a.meta) +
-                 (H16M ? (int64_t)nt * a.ksteps * 32 + (lane & 31) : (int64_t)nt * a.ksteps * 64 + lane);
+                 (int64_t)nt * a.ksteps * 64 + lane;
     }
     auto copy_one = [&](int c, int ks, int stage) {
       const int kc = ks < ks1 ? ks : ks1 - 1;
@@ -630,7 +630,7 @@ __global__ __launch_bounds__(256) void gemm_decode16_kernel(StreamArgs a) {
           __builtin_amdgcn_global_load_lds((gptr_t)(w_src[j] + (int64_t)kc * 1024),
                                            (lptr_t)(st + kAStage + (wave * 2 + j) * 1024), 16, 0, 0);
         else
-          __builtin_amdgcn_global_load_lds((gptr_t)(m_src[j] + (int64_t)kc * (H16M ? 32 : 64)),
+          __builtin_amdgcn_global_load_lds((gptr_t)(m_src[j] + (int64_t)kc * 64),
                                            (lptr_t)(st + kAStage + 8 * 1024 + (wave * 2 + j) * 256), 4, 0, 0);
       }
     };
@@ -639,7 +639,6 @@ __global__ __launch_bounds__(256) void gemm_decode16_kernel(StreamArgs a) {
     u4_t bop[2][4];
     uint32_t cw[2][4];     // raw code words [slice][column tile] of the current stage
     float2 cm[4];
-    uint32_t cmh[4];
     float s24[4], s20[4], mn[4];
     auto read_a = [&](uint32_t st, int sl, h8_t* dst) {
       const uint32_t ad = st + a_off[sl];
@@ -655,8 +654,8 @@ __global__ __launch_bounds__(256) void gemm_decode16_kernel(StreamArgs a) {
         constexpr int qoff = (ct >> 1) * 1024 + (ct & 1) * 256;
         cw[0][ct] = lds_read32<qoff>(st + bq_off);
         cw[1][ct] = lds_read32<qoff + 512>(st + bq_off);
-        constexpr int moff = (ct >> 1) * 256 + (ct & 1) * 16 * (H16M ? 4 : 8);
-        if constexpr (H16M) cmh[ct] = lds_read32<moff>(st + bm_off); else cm[ct] = lds_read64<moff>(st + bm_off);
+        constexpr int moff = (ct >> 1) * 256 + (ct & 1) * 128;
+        cm[ct] = lds_read64<moff>(st + bm_off);
       });
     };
     auto landed_b = [&]() {
@@ -664,17 +663,12 @@ __global__ __launch_bounds__(256) void gemm_decode16_kernel(StreamArgs a) {
       for (int ct = 0; ct < 4; ++ct) {
         lds_landed(cw[0][ct]);
         lds_landed(cw[1][ct]);
-        if constexpr (H16M) lds_landed(cmh[ct]); else lds_landed(cm[ct]);
+        lds_landed(cm[ct]);
       }
     };
     auto set_meta = [&]() {
 #pragma unroll
       for (int ct = 0; ct < 4; ++ct) {
-        if constexpr (H16M) {
-          const h2_t pr = __builtin_bit_cast(h2_t, cmh[ct]);
-          cm[ct].x = (float)pr.x;
-          cm[ct].y = (float)pr.y;
-        }
         s24[ct] = cm[ct].y * 16777216.0f;
         s20[ct] = cm[ct].y * 1048576.0f;
         mn[ct] = cm[ct].x;
@@ -852,6 +846,227 @@ __global__ __launch_bounds__(256) void gemm_decode16_kernel(StreamArgs a) {
   __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
+// The same tiles and the same sums in the same order for weights with FP16 {min, scale} pairs, as two workgroups per CU: each
+// takes half of a tile's columns (four waves of 32 columns), so that every SIMD has two waves that share no barrier.  With one
+// wave per SIMD a step is a chain of LDS reads (470 cycles of a step's 1800), dequantization (530) and MFMAs (320, parts
+// left out one at a time); eight waves of one workgroup run it in step with each other and gain nothing (38.1 us against 38.5).
+// It pays with the dequantization that pairs of FP16 numbers allow: us at 37 rows, 21504 x 7168 39.4 -> 34.8, 7168 x 28672
+// 43.5 -> 38.4, 28672 x 7168 45.7 -> 40.1.  FP32 pairs keep the kernel above: 36864 x 12288 85.7 there, 86.7 so, 4096 x 4096 9.3, 11.4.
+// Four stages: five measure the same, seven 2 us more (every segment starts with a burst of copies).
+template <int MT16>
+struct Dec16HCfg {
+  static constexpr int kRows = MT16 * 16;
+  static constexpr int kAStage = kRows * kKS * 2;
+  static constexpr int kStageBytes = kAStage + kBStageQ4 / 2;
+  static constexpr int kNST = 4;
+  static constexpr int kAC0 = (2 * MT16 + 3) / 4, kAC1 = 2 * MT16 / 4, kMore = 2 * MT16 % 4;   // 8-row activation pieces per step: waves below kMore, the others
+  static_assert(2 * kNST * kStageBytes <= kLdsBytes, "two workgroups on a CU");
+};
+
+template <int MT16>
+__global__ __launch_bounds__(256, 2) void gemm_decode16h_kernel(StreamArgs a) {
+  using C = Dec16HCfg<MT16>;
+  constexpr int kAStage = C::kAStage, kStageBytes = C::kStageBytes, kNST = C::kNST;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, g4 = lane >> 4;
+
+  const int half_n = (blockIdx.x >> 3) & 1, block = (int)(blockIdx.x & 7) + 8 * (int)(blockIdx.x >> 4);   // (both halves on one XCD)
+  const int p = (block & 7) * (a.grid >> 3) + (block >> 3);
+  const int part = part_of_block(a.parts, block);
+  const int64_t rem_begin = work_begin(a.rem_work, a.parts, part), rem_end = work_begin(a.rem_work, a.parts, part + 1);
+  int64_t pos = rem_begin;
+  int round = 0, seg = 0;
+
+  // operand read offsets inside a stage
+  int a_off[2];
+#pragma unroll
+  for (int sl = 0; sl < 2; ++sl) a_off[sl] = (l16 * kKS + swz(l16, 4 * sl + g4) * 8) * 2;
+  const int bq_off = kAStage + wave * 1024 + l16 * 16 + g4 * 4;                       // + 256 ct + 512 sl
+  const int bm_off = kAStage + 4 * 1024 + wave * 256 + l16 * 4;                // + 64 ct
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(lptr_t)smem;
+
+  while (round < a.rounds || pos < rem_end) {
+    int64_t tile;
+    int ks0, ks1;
+    const bool whole_round = round < a.rounds;
+    if (whole_round) {
+      tile = (int64_t)round * a.grid + p;
+      ks0 = 0;
+      ks1 = a.ksteps;
+    } else {
+      const int64_t t = pos / a.ksteps;
+      tile = (int64_t)a.rounds * a.grid + t;
+      ks0 = (int)(pos - t * a.ksteps);
+      const int64_t left = rem_end - pos;
+      ks1 = (int)((int64_t)(a.ksteps - ks0) < left ? a.ksteps : ks0 + left);
+    }
+    int mblk, n_tile;
+    tile_coords(tile, a.m_blocks, a.n_tiles, mblk, n_tile);
+    const int m0 = mblk * C::kRows;
+    const int nt0 = n_tile * 8 + half_n * 4 + wave;   // this wave's 32-column tile
+
+    f4_t acc[MT16][2];
+#pragma unroll
+    for (int m = 0; m < MT16; ++m)
+#pragma unroll
+      for (int ct = 0; ct < 2; ++ct) acc[m][ct] = (f4_t){0.f, 0.f, 0.f, 0.f};
+
+    const half_t* a_src[C::kAC0];
+#pragma unroll
+    for (int i = 0; i < C::kAC0; ++i) {
+      const int prow = 8 * (wave + 4 * i) + (lane >> 3);
+      const int row = m0 + prow < a.M ? m0 + prow : a.M - 1;
+      a_src[i] = a.x + (int64_t)row * a.ldx + swz(prow, lane & 7) * 8;
+    }
+    const uint8_t* w_src;
+    const uint32_t* m_src;   // (32 pairs per step; the other lanes' copies of them are never read)
+    {
+      const int nt = nt0 < a.n32 ? nt0 : a.n32 - 1;   // ragged last column block: load valid data, never store it
+      w_src = a.w + (int64_t)nt * a.ksteps * 1024 + lane * 16;
+      m_src = reinterpret_cast<const uint32_t*>(a.meta) + (int64_t)nt * a.ksteps * 32 + (lane & 31);
+    }
+    auto copy_step = [&](int ks, int stage) {
+      const int kc = ks < ks1 ? ks : ks1 - 1;   // past the end the last step is fetched again
+      unsigned char* st = smem + stage * kStageBytes;
+      __builtin_amdgcn_global_load_lds((gptr_t)(w_src + (int64_t)kc * 1024), (lptr_t)(st + kAStage + wave * 1024), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds((gptr_t)(m_src + (int64_t)kc * 32), (lptr_t)(st + kAStage + 4 * 1024 + wave * 256), 4, 0, 0);
+#pragma unroll
+      for (int i = 0; i < C::kAC0; ++i)
+        if (i < C::kAC1 || wave < C::kMore)
+          __builtin_amdgcn_global_load_lds((gptr_t)(a_src[i] + kc * kKS), (lptr_t)(st + (wave + 4 * i) * 1024), 16, 0, 0);
+    };
+
+    // this wave's copies have landed, all but those of the newest N steps
+    auto wait_steps = [&](auto N_) __attribute__((always_inline)) {
+      constexpr int n = decltype(N_)::value;
+      if (C::kMore == 0 || wave < C::kMore)
+        __asm__ volatile("s_waitcnt vmcnt(%0)" ::"n"(n * (C::kAC0 + 2)) : "memory");
+      else
+        __asm__ volatile("s_waitcnt vmcnt(%0)" ::"n"(n * (C::kAC1 + 2)) : "memory");
+    };
+    // the operands of this step and of the next one
+    h8_t aop[2][2][MT16];
+    uint32_t cw[2][4], pairs[2][2];   // code words [2 ct + sl]
+    auto read = [&](uint32_t st, auto B_) __attribute__((always_inline)) {
+      constexpr int b = decltype(B_)::value;
+      static_for<0, 2>([&](auto CT) __attribute__((always_inline)) {
+        constexpr int ct = decltype(CT)::value;
+        pairs[b][ct] = lds_read32<ct * 64>(st + bm_off);
+        cw[b][2 * ct] = lds_read32<ct * 256>(st + bq_off);
+        cw[b][2 * ct + 1] = lds_read32<ct * 256 + 512>(st + bq_off);
+      });
+      static_for<0, 2 * MT16>([&](auto I) __attribute__((always_inline)) {
+        constexpr int sl = decltype(I)::value / MT16, m = decltype(I)::value - sl * MT16;
+        aop[b][sl][m] = __builtin_bit_cast(h8_t, lds_read128<m * 16 * kKS * 2>(st + a_off[sl]));
+      });
+    };
+    auto landed = [&](auto B_) __attribute__((always_inline)) {
+      constexpr int b = decltype(B_)::value;
+      lds_wait();
+#pragma unroll
+      for (int i = 0; i < 4; ++i) lds_landed(cw[b][i]);
+#pragma unroll
+      for (int ct = 0; ct < 2; ++ct) lds_landed(pairs[b][ct]);
+#pragma unroll
+      for (int sl = 0; sl < 2; ++sl)
+#pragma unroll
+        for (int m = 0; m < MT16; ++m) lds_landed(aop[b][sl][m]);
+    };
+
+    __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < kNST; ++t) copy_step(ks0 + t, t);
+    wait_steps(IdxC<kNST - 1>{});   // step ks0 has landed
+    __builtin_amdgcn_s_barrier();
+    read(lds0, IdxC<0>{});
+    landed(IdxC<0>{});
+
+    int stage = 0;
+    auto step = [&](int ks, auto B_) __attribute__((always_inline)) {
+      constexpr int b = decltype(B_)::value;
+      const int stage1 = stage + 1 == kNST ? 0 : stage + 1;
+      // every wave has read its operands of step ks, and every wave's copies of step ks + 1 have landed
+      wait_steps(IdxC<kNST - 2>{});
+      __builtin_amdgcn_s_barrier();   // bare barrier: no fence, the copies in flight stay in flight
+      __builtin_amdgcn_sched_barrier(0);
+      read(lds0 + stage1 * kStageBytes, IdxC<1 - b>{});
+      copy_step(ks + kNST, stage);
+      __builtin_amdgcn_sched_barrier(0);
+      // column tile and slice i = 2 sl + ct: eight weights per lane, three MFMAs each
+      auto contract = [&](auto dequant) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int sl = i >> 1, ct = i & 1;
+          u4_t w;
+          dequant(ct, cw[b][2 * ct + sl], reinterpret_cast<uint32_t*>(&w));
+#pragma unroll
+          for (int m = 0; m < MT16; ++m)
+            acc[m][ct] = __builtin_amdgcn_mfma_f32_16x16x32_f16(aop[b][sl][m], __builtin_bit_cast(h8_t, w), acc[m][ct], 0, 0, 0);
+        }
+      };
+      if (__all(dequant8_pk_takes(pairs[b][0]) && dequant8_pk_takes(pairs[b][1]))) {
+        const PkPair q[2] = {dequant8_pk_pair(pairs[b][0]), dequant8_pk_pair(pairs[b][1])};
+        contract([&](int ct, uint32_t x, uint32_t* w) __attribute__((always_inline)) { dequant8_pk(x, q[ct], w); });
+      } else {
+        contract([&](int ct, uint32_t x, uint32_t* w) __attribute__((always_inline)) {
+          const h2_t pr = __builtin_bit_cast(h2_t, pairs[b][ct]);
+          dequant8_exact(x, (float)pr.y * 16777216.0f, (float)pr.y * 1048576.0f, (float)pr.x, w);
+        });
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      landed(IdxC<1 - b>{});   // (here, so that no read is in flight where the compiler may move registers, at the loop's end)
+      stage = stage1;
+    };
+    int ks = ks0;
+    for (; ks + 1 < ks1; ks += 2) {
+      step(ks, IdxC<0>{});
+      step(ks + 1, IdxC<1>{});
+    }
+    if (ks < ks1) step(ks, IdxC<0>{});
+
+    // ---- epilogue: lane holds column l16, rows 4 g4 + 0..3 of each 16 x 16 tile
+    const bool full = (ks0 == 0) && (ks1 == a.ksteps);
+    if (full) {
+      if (nt0 < a.n32) {
+        const int m_end = m0 + C::kRows < a.M ? m0 + C::kRows : a.M;
+        FinishRows fin[MT16][2];
+#pragma unroll
+        for (int m = 0; m < MT16; ++m)
+#pragma unroll
+          for (int ct = 0; ct < 2; ++ct)
+            fin[m][ct].request(a.bias, a.residual, a.ldr, m0 + 16 * m + 4 * g4, m_end, nt0 * 32 + ct * 16 + l16);
+#pragma unroll
+        for (int m = 0; m < MT16; ++m)
+#pragma unroll
+          for (int ct = 0; ct < 2; ++ct)
+            fin[m][ct].store(make_float4(acc[m][ct][0], acc[m][ct][1], acc[m][ct][2], acc[m][ct][3]), a.relu, a.residual, a.out16,
+                             a.out32, a.ldo, m0 + 16 * m + 4 * g4, m_end, nt0 * 32 + ct * 16 + l16);
+      }
+    } else {
+      // partial sums as the reduction pass takes them: float4 number (4 m + column tile of 64 columns) of thread
+      // 64 (column / 64) + lane holds rows 16 m + 4 g4 + 0..3 of one column -> every store is 1 KiB contiguous per wave
+      float4* dst = reinterpret_cast<float4*>(a.partial + ((int64_t)part * 2 + (seg == 0 ? 0 : 1)) * ((int64_t)C::kRows * kBN)) +
+                    ((wave & 1) * 2 * 256 + (half_n * 2 + (wave >> 1)) * 64 + lane);
+#pragma unroll
+      for (int m = 0; m < MT16; ++m)
+#pragma unroll
+        for (int ct = 0; ct < 2; ++ct)
+          dst[(m * 4 + ct) * 256] = make_float4(acc[m][ct][0], acc[m][ct][1], acc[m][ct][2], acc[m][ct][3]);
+    }
+    if (whole_round) {
+      ++round;
+    } else {
+      pos += ks1 - ks0;
+      ++seg;
+    }
+  }
+  __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
+}
+
 // One half of d = nearest FP16 of (FP16 half SEL of x) * s + b, computed in FP32 with a single rounding; the
 // other half of d is kept.  Written as instructions so that the two halves of an operand register can be
 // produced in different gaps between MFMAs (the compiler would merge separately computed halves with
@@ -889,7 +1104,7 @@ constexpr int spread7(int i, int n) { return i * 7 / n > 7 ? 7 : i * 7 / n; }
 // the four column tiles), so the partial-sum layout and the reduction pass are those of the kernel above.
 template <int MT16, bool H16M>
 __global__ __launch_bounds__(512) void gemm_decode16x2_kernel(StreamArgs a) {
-  using C = Dec16Cfg<MT16, H16M>;
+  using C = Dec16Cfg<MT16>;
   constexpr int kAStage = C::kAStage, kStageBytes = C::kStageBytes, kNST = C::kNST;
   constexpr int kPieces = C::kRowsLds / 8;                          // 8-row activation pieces per stage
   constexpr int kAC0 = (kPieces + 7) / 8, kAC1 = kPieces / 8;       // activation copies per step: waves 0..3, waves 4..7
@@ -1941,25 +2156,28 @@ int launch_prefill16_any(const StreamArgs& a, int dtype, hipStream_t stream) {
 
 template <int MT16, bool H16M>
 int launch_dec16(const StreamArgs& a, hipStream_t stream) {
-  using C = Dec16Cfg<MT16, H16M>;
-  const size_t smem = (size_t)C::kNST * C::kStageBytes;
-  constexpr bool kEight = MT16 >= 5;
-  static bool attr_done = false;
-  if constexpr (kEight) {
-    if (!attr_done) {
-      FG_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_decode16x2_kernel<MT16, H16M>),
-                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
-      attr_done = true;
-    }
-    hipLaunchKernelGGL((gemm_decode16x2_kernel<MT16, H16M>), dim3(a.grid), dim3(512), smem, stream, a);
+  static_assert(MT16 == 3 || MT16 >= 5, "others run on 32-row tiles");
+  const void* kernel;
+  int smem = Dec16Cfg<MT16>::kNST * Dec16Cfg<MT16>::kStageBytes;
+  if constexpr (MT16 >= 5) {
+    kernel = reinterpret_cast<const void*>(&gemm_decode16x2_kernel<MT16, H16M>);
+  } else if constexpr (H16M) {
+    kernel = reinterpret_cast<const void*>(&gemm_decode16h_kernel<MT16>);
+    smem = Dec16HCfg<MT16>::kNST * Dec16HCfg<MT16>::kStageBytes;
   } else {
-    if (!attr_done) {
-      FG_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_decode16_kernel<MT16, H16M>),
-                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
-      attr_done = true;
-    }
-    hipLaunchKernelGGL((gemm_decode16_kernel<MT16, H16M>), dim3(a.grid), dim3(256), smem, stream, a);
+    kernel = reinterpret_cast<const void*>(&gemm_decode16_kernel<MT16>);
   }
+  static bool attr_done = false;
+  if (!attr_done) {
+    FG_HIP(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, smem));
+    attr_done = true;
+  }
+  if constexpr (MT16 >= 5)
+    hipLaunchKernelGGL((gemm_decode16x2_kernel<MT16, H16M>), dim3(a.grid), dim3(512), smem, stream, a);
+  else if constexpr (H16M)
+    hipLaunchKernelGGL((gemm_decode16h_kernel<MT16>), dim3(2 * a.grid), dim3(256), smem, stream, a);
+  else
+    hipLaunchKernelGGL((gemm_decode16_kernel<MT16>), dim3(a.grid), dim3(256), smem, stream, a);
   FG_LAUNCH_CHECK();
   return FG_OK;
 }
