@@ -1485,50 +1485,62 @@ __device__ __forceinline__ void prefill16_finish_tile(const StreamArgs& a, f4_t 
       const int c0 = nt0 * 32 + l16, c1 = c0 + 16;
       const float b0 = a.bias ? (float)a.bias[c0] : 0.f, b1 = a.bias ? (float)a.bias[c1] : 0.f;
       const int cs = odd ? c1 - 1 : c0;   // first of the two adjacent columns this lane stores
-      // the residual of two row tiles at a time, requested a pair of row tiles ahead of its use: read where it is added, each
-      // row waits for a round trip to memory (12288 x 12288 at 18432 rows, tiled: 4563 us so, 4435 requested ahead; FP16
-      // 4096 x 4096 at 4096 rows 132.4, 128.0)
-      uint32_t res[2][8];   // pairs of FP16 numbers
-      const auto request = [&](int m, uint32_t (&r8)[8]) __attribute__((always_inline)) {
+      const auto rows = [&](auto HAS_RES) __attribute__((always_inline)) {
+        constexpr bool kRes = decltype(HAS_RES)::value != 0;
+        // the residual of two row tiles at a time, requested a pair of row tiles ahead of its use: read where it is added, each
+        // row waits for a round trip to memory (12288 x 12288 at 18432 rows, tiled: 4518 us so, 4395 requested
+        // ahead; FP16 4096 x 4096 at 4096 rows 132.6, 122.0)
+        uint32_t res[2][8];   // pairs of FP16 numbers
+        const auto request = [&](int m, uint32_t (&r8)[8]) __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const int row = m0 + 16 * (m + (i >> 2)) + 4 * g4 + (i & 3);
-          r8[i] = *reinterpret_cast<const uint32_t*>(a.residual + (int64_t)(row < a.M ? row : a.M - 1) * a.ldr + cs);
+          for (int i = 0; i < 8; ++i) {
+            const int row = m0 + 16 * (m + (i >> 2)) + 4 * g4 + (i & 3);
+            r8[i] = *reinterpret_cast<const uint32_t*>(a.residual + (int64_t)(row < a.M ? row : a.M - 1) * a.ldr + cs);
+          }
+        };
+        if constexpr (kRes) request(0, res[0]);
+        int row = m0 + 4 * g4;
+        int64_t o_off = (int64_t)row * a.ldo + cs;
+#pragma unroll
+        for (int m = 0; m < 4 * RG; ++m) {
+          if constexpr (kRes)
+            if ((m & 1) == 0 && m + 2 < 4 * RG) request(m + 2, res[(m >> 1) + 1 & 1]);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            float x0 = acc[m][0][r] + b0, x1 = acc[m][1][r] + b1;
+            if (a.relu) {
+              x0 = fmaxf(x0, 0.f);
+              x1 = fmaxf(x1, 0.f);
+            }
+            const float keep = odd ? x1 : x0, send = odd ? x0 : x1;
+            // lane l <-> lane l ^ 1 (quad_perm [1, 0, 3, 2])
+            const float recv = __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, send), 0xB1, 0xF, 0xF, true));
+            float lo = odd ? recv : keep, hi = odd ? keep : recv;
+            if constexpr (kRes) {
+              const h2_t rr = __builtin_bit_cast(h2_t, res[(m >> 1) & 1][(m & 1) * 4 + r]);
+              lo += (float)rr.x;
+              hi += (float)rr.y;
+            }
+            if (row < a.M) {
+              if (a.out32)
+                *reinterpret_cast<float2*>(a.out32 + o_off) = make_float2(lo, hi);
+              else
+                *reinterpret_cast<h2_t*>(a.out16 + o_off) = (h2_t){(half_t)lo, (half_t)hi};
+            }
+            const int step = r == 3 ? 13 : 1;   // rows 16 m + 4 g4 + r
+            row += step;
+            o_off += step * a.ldo;
+          }
         }
       };
-      if (a.residual) request(0, res[0]);
-      int row = m0 + 4 * g4;
-      int64_t o_off = (int64_t)row * a.ldo + cs;
-#pragma unroll
-      for (int m = 0; m < 4 * RG; ++m) {
-        if (a.residual && (m & 1) == 0 && m + 2 < 4 * RG) request(m + 2, res[(m >> 1) + 1 & 1]);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          float x0 = acc[m][0][r] + b0, x1 = acc[m][1][r] + b1;
-          if (a.relu) {
-            x0 = fmaxf(x0, 0.f);
-            x1 = fmaxf(x1, 0.f);
-          }
-          const float keep = odd ? x1 : x0, send = odd ? x0 : x1;
-          // lane l <-> lane l ^ 1 (quad_perm [1, 0, 3, 2])
-          const float recv = __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, send), 0xB1, 0xF, 0xF, true));
-          float lo = odd ? recv : keep, hi = odd ? keep : recv;
-          if (a.residual) {
-            const h2_t rr = __builtin_bit_cast(h2_t, res[(m >> 1) & 1][(m & 1) * 4 + r]);
-            lo += (float)rr.x;
-            hi += (float)rr.y;
-          }
-          if (row < a.M) {
-            if (a.out32)
-              *reinterpret_cast<float2*>(a.out32 + o_off) = make_float2(lo, hi);
-            else
-              *reinterpret_cast<h2_t*>(a.out16 + o_off) = (h2_t){(half_t)lo, (half_t)hi};
-          }
-          const int step = r == 3 ? 13 : 1;   // rows 16 m + 4 g4 + r
-          row += step;
-          o_off += step * a.ldo;
-        }
-      }
+      // Without a residual nothing may wait for loads: the counter that such a wait looks at also counts stores, and a wait
+      // that stands where a residual may or may not be on its way is one for every store before it (K = 64, FP16 38912
+      // columns at 530 rows: 31.1 us with such waits, 22.4 without; 6144 x 2048 at 2670 rows 92.4, 86.2; tiled 12288 x 4096 at 4047
+      // rows 348.5, 333.0).
+      if (a.residual)
+        rows(IdxC<1>{});
+      else
+        rows(IdxC<0>{});
     }
   } else {
     // Partial sums in the layout of gemm_stream_kernel<2 RG, 1, 1, 8> (its reduction pass finishes these
