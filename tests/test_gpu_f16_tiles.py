@@ -5,6 +5,7 @@ import pytest
 import torch
 
 from paper_2303_06865_amd import binding as B
+from tests import routes
 from tests.util import assert_close
 
 pytestmark = pytest.mark.gpu
@@ -67,17 +68,39 @@ def test_linear_f16_tiles(m, n, k):
     assert torch.equal(B.fg_linear(mat, None, x), plain)   # the same bits on every call
 
 
-@pytest.mark.parametrize("m,n,k", [(200, 2304, 768), (64, 6144, 2048), (333, 4096, 1024)])
-def test_bias_and_residual_at_any_address(m, n, k):
-    """Both are FP16 arrays without an alignment of their own: one element past a 16-byte boundary."""
+@pytest.mark.parametrize("m,n,k,few", [(333, 4096, 4096, False), (512, 7168, 7168, False), (100, 4128, 8192, False),
+                                       (129, 8224, 2048, False), (333, 1056, 8192, False), (200, 2304, 768, True)])
+def test_bias_and_residual_at_any_address(m, n, k, few):
+    """Both are FP16 arrays without an alignment of their own: one element past a 16-byte boundary the results are the same bits,
+    from whole contractions and from ranges of them, and from the few-rows kernel."""
+    assert routes.f16_tiles(n, k, m) and routes.few_rows(B.FG_F16, n, k, m) == few
     w, x, bias, res = _inputs(m, n, k)
     off = lambda t: torch.cat([t.new_zeros(1), t.flatten()])[1:].view(t.shape)
     b1, r1 = off(bias), off(res)
     assert b1.data_ptr() % 16 and r1.data_ptr() % 16
     mat = B.Mat.from_f16(w, False)
-    want = x.float() @ w.float().t() + bias.float() + res.float()
+    want = B.fg_linear(mat, bias, x, residual=res)
     for b, r in ((b1, r1), (bias, r1), (b1, res)):
-        assert_close(B.fg_linear(mat, b, x, residual=r).cpu().numpy(), want.cpu().numpy(), "m=%d n=%d k=%d" % (m, n, k))
+        assert torch.equal(B.fg_linear(mat, b, x, residual=r), want)
+
+
+def test_logits_at_any_address():
+    rows, vocab, h1 = 100, 34016, 768
+    assert routes.f16_tiles(vocab, h1, rows) and not routes.few_rows(B.FG_F16, vocab, h1, rows)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    half = lambda *s: torch.empty(s, dtype=torch.float16, device="cuda").normal_(0.0, 1.0, generator=g)
+    cfg = B.Cfg(h1, h1 // 64, 4 * h1, vocab, 64)
+    emb, x = half(vocab, h1), half(rows, h1)
+    ones, zeros = torch.ones(h1, dtype=torch.float16, device="cuda"), torch.zeros(h1, dtype=torch.float16, device="cuda")
+    ids, logits = B.fg_lm_head_greedy(cfg, x, ones, zeros, emb)
+    ids1, buf = torch.empty_like(ids), torch.zeros(rows * vocab + 2, dtype=torch.float32, device="cuda")
+    n = B.lib().fg_lm_head_workspace_bytes(B.C.byref(cfg.c), rows)
+    ws = torch.empty(n, dtype=torch.uint8, device="cuda")
+    rc = B.lib().fg_lm_head_greedy(B.C.byref(cfg.c), x.data_ptr(), h1, rows, ones.data_ptr(), zeros.data_ptr(), emb.data_ptr(),
+                                   ids1.data_ptr(), 1, buf.data_ptr() + 4, ws.data_ptr(), n, torch.cuda.current_stream().cuda_stream)
+    assert rc == 0
+    assert torch.equal(buf[1:-1], logits.view(-1)) and torch.equal(ids1, ids)
+    assert buf[0] == 0 and buf[-1] == 0
 
 
 @pytest.mark.parametrize("rows,vocab,h1", [(100, 34016, 768), (129, 8000, 768), (300, 8032, 1024), (512, 33024, 256)])
