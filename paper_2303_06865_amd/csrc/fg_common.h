@@ -95,9 +95,10 @@ int gemm_f16w_forced(int64_t n);   // column tiles fixed by the environment, or 
 size_t gemm_f16w_workspace(int64_t n, int64_t k, int64_t m);
 int gemm_f16w_launch(const LinearArgs& a, void* ws, size_t ws_bytes, hipStream_t stream);
 // row-major FP16 weights, some hundred rows (csrc/fg_gemm_f16_tiles.hip); any workspace will do
-bool gemm_f16_tiles_takes(int dtype, int64_t n, int64_t k, int64_t m);
+bool gemm_f16_tiles_takes(int dtype, int64_t n, int64_t k, int64_t m, bool residual);
 int gemm_f16_tiles_launch(const LinearArgs& a, void* ws, size_t ws_bytes, hipStream_t stream);
 size_t gemm_stream_workspace(int64_t n, int64_t k, int64_t m);
+float gemm_stream_f16_us(int64_t n, int64_t k, int64_t m);   // expected time on FP16 weights, from 321 rows up
 int gemm_stream_launch(const LinearArgs& a, void* ws, size_t ws_bytes, hipStream_t stream);
 int pack_weights_launch(const void* codes, const void* meta, bool meta_f16, int64_t n, int64_t k, void* codes_out, void* meta_out,
                         hipStream_t stream);

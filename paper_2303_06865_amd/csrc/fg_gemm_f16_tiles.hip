@@ -319,10 +319,11 @@ constexpr TileShape kShapes[] = {
 };
 struct TilePick {
   int shape, splits;
+  int64_t items;   // workgroups
+  float us;
 };
 TilePick pick_tile(int64_t n, int64_t k, int64_t m, size_t ws_bytes) {
-  TilePick best = {-1, 1};
-  float best_t = 0.f;
+  TilePick best = {-1, 1, 0, 0.f};
   const int n32 = (int)n, m32 = (int)m, steps = (int)(k / kTS);
   for (int i = 0; i < (int)(sizeof(kShapes) / sizeof(kShapes[0])); ++i) {
     const TileShape& s = kShapes[i];
@@ -333,10 +334,7 @@ TilePick pick_tile(int64_t n, int64_t k, int64_t m, size_t ws_bytes) {
       if (bytes > (int64_t)ws_bytes) break;
       const float t = s.first + (float)((tiles * sp + 255) >> 8) * (s.round + (float)((steps + sp - 1) / sp) * s.step) +
                       (sp == 1 ? 0.f : 4.f + (float)bytes * 0.33e-6f);
-      if (best.shape < 0 || t < best_t) {
-        best = {i, sp};
-        best_t = t;
-      }
+      if (best.shape < 0 || t < best.us) best = {i, sp, tiles * sp, t};
       if (tiles * sp >= 512) break;   // the chip is full: more ranges only add partial sums
     }
   }
@@ -355,13 +353,38 @@ TilePick pick_tile(int64_t n, int64_t k, int64_t m, size_t ws_bytes) {
 //   More rows: where tiles of 256 x 256 are less than one round of the chip and the contraction is not long (9000 x 768 x 3072
 //   1.52, 6000 x 2048 x 2048 1.36, 18432 x 768 x 768 1.53, 3000 x 4096 x 4096 1.36, but 4096 x 4096 x 4096 0.94, 9000 x 2048 x 2048
 //   0.90, 6000 x 2048 x 8192 0.98).
-bool gemm_f16_tiles_takes(int dtype, int64_t n, int64_t k, int64_t m) {
+// Not within these lines (measured over 2500 shapes, this kernel's time over the other's):
+//   65 to 96 rows, contractions beyond 8192, where the tiles leave more than a quarter of the chip without work (the copies of those
+//   that there are don't take what HBM gives): 92 x 8352 x 13312 1.30, 70 x 8576 x 23744 1.23, 82 x 4256 x 17536 1.21, 78 x 5408 x
+//   15488 1.05; but 80 x 4096 x 10560 0.85, 85 x 7168 x 16768 0.94.  Beyond 20000 wherever the narrow tiles don't take the call: 72 x
+//   5504 x 28928 1.13, 94 x 8128 x 22336 1.03, but 69 x 4864 x 28480 0.85.  More rows, matrices of more than 60 M, where nearly half
+//   of the chip has no work: 97 x 4256 x 24320 1.22, 224 x 16448 x 9984 1.09, 225 x 16480 x 7936 1.08.
+//   Contractions of up to 256 in more than one round, without a residual: a workgroup is its start and its epilogue, and the other
+//   kernel's stay on: 1089 x 27488 x 64 2.05, 343 x 36896 x 192 1.32, 800 x 15328 x 128 1.08, 1247 x 8640 x 64 0.97.
+//   Matrices of more than 70 M in three rounds and more: 383 x 33408 x 2496 1.21, 1491 x 12416 x 13248 1.09, 231 x 41120 x 2816 1.05,
+//   1260 x 27200 x 4864 1.04.  From 321 rows by what both are expected to take: kept 0.90 (29 shapes), left to the other 1.00 (81);
+//   below, with a residual 0.68 to 0.84.  (In one or two rounds 0.70 to 0.82.)
+bool gemm_f16_tiles_takes(int dtype, int64_t n, int64_t k, int64_t m, bool residual) {
   if (dtype != FG_F16 || n % 32 != 0 || m <= 32) return false;
   const int64_t size = n * k;
   const bool head = n > 32768;
-  if (m <= 128) return head ? m > 96 && size <= 380000000 : size >= 4000000 && size <= 230000000;
-  if (m <= 2048) return size <= 210000000 && (!head || m <= 512);
-  return k <= 4096 && ceil_div(m, 256) * ceil_div(n, 256) <= 224;
+  if (m <= 128) {
+    if (head ? m <= 96 || size > 380000000 : size < 4000000 || size > 230000000) return false;
+  } else if (m <= 2048) {
+    if (size > 210000000 || (head && m > 512)) return false;
+  } else if (k > 4096 || ceil_div(m, 256) * ceil_div(n, 256) > 224) {
+    return false;
+  }
+  const bool short_k = m > 320 && k <= 256 && !residual, long_k = m > 64 && k > 7000;
+  if (!short_k && !long_k && size <= 70000000) return true;
+  const TilePick pick = pick_tile(n, k, m, linear_workspace_bytes(dtype, n, k, m));
+  const int64_t rounds = ceil_div(pick.items, 256);
+  const float fill = (float)pick.items / (float)(rounds * 256);
+  if (short_k && rounds >= 2) return false;
+  if (m > 64 && m <= 96 && k > 8192 && (fill < 0.75f || (k > 20000 && !gemm_f16w_pick_cols(n, k, m)))) return false;
+  if (m > 96 && k > 7000 && size > 60000000 && fill < 0.55f) return false;
+  if (m > 128 && rounds >= 3 && size > 70000000) return m <= 320 ? residual : pick.us < 0.94f * gemm_stream_f16_us(n, k, m);
+  return true;
 }
 
 int gemm_f16_tiles_launch(const LinearArgs& la, void* ws, size_t ws_bytes, hipStream_t stream) {

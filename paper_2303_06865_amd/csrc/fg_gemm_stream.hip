@@ -2203,6 +2203,15 @@ size_t gemm_stream_workspace(int64_t n, int64_t k, int64_t m) {
   return (size_t)sh.grid() * 2 * rows * kBN * sizeof(float);
 }
 
+// Whole rounds of 256 workgroups, and a rest that is cut along the contraction, in blocks of 256 or 192 rows.  Fitted to 110
+// measured matrices of 70 to 210 M elements without a residual, 321 to 2048 rows: off by 4 % (one standard deviation).
+float gemm_stream_f16_us(int64_t n, int64_t k, int64_t m) {
+  const bool tall = pick_shape(m, FG_F16, n, k).mt == 8;
+  const int64_t tiles = ceil_div(m, tall ? 256 : 192) * ceil_div(n, kBN), whole = tiles / 256, steps = k / kKS;
+  const float rest = (float)(tiles - whole * 256) / 256.f;
+  return tall ? 47.6f + (float)steps * (1.673f * (float)whole + 2.25f * rest) : 31.7f + (float)steps * (1.371f * (float)whole + 1.885f * rest);
+}
+
 int gemm_stream_launch(const LinearArgs& la, void* ws, size_t ws_bytes, hipStream_t stream) {
   if (la.m == 0 || la.n == 0) return FG_OK;
   const Shape sh = pick_shape(la.m, la.dtype, la.n, la.k);

@@ -156,7 +156,7 @@ size_t linear_workspace_bytes(int dtype, int64_t n, int64_t k, int64_t m) {
 int linear_launch(const LinearArgs& a, void* ws, size_t ws_bytes, hipStream_t stream) {
   if (use_fewrows(a.dtype, a.n, a.k, a.m)) return gemm_fewrows_launch(a, stream);
   const bool f16w = use_f16w(a.dtype, a.n, a.k, a.m);
-  if (!(f16w && gemm_f16w_forced(a.n)) && gemm_f16_tiles_takes(a.dtype, a.n, a.k, a.m)) {
+  if (!(f16w && gemm_f16w_forced(a.n)) && gemm_f16_tiles_takes(a.dtype, a.n, a.k, a.m, a.residual != nullptr)) {
     // what the kernels that it takes the call from are refused without; more than that changes nothing
     const size_t need = linear_workspace_bytes(a.dtype, a.n, a.k, a.m);
     if (!ws || ws_bytes < need) return FG_ERR_WORKSPACE;

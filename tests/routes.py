@@ -6,7 +6,7 @@ from paper_2303_06865_amd import binding as B
 
 def _rule(name, *args):
     f = getattr(B.lib(), name)
-    f.restype, f.argtypes = C.c_bool, [C.c_int if isinstance(a, B.C.c_int) else C.c_int64 for a in args]
+    f.restype, f.argtypes = C.c_bool, [C.c_int64 if isinstance(a, int) else type(a) for a in args]
     return bool(f(*args))
 
 
@@ -15,6 +15,6 @@ def few_rows(dtype, n, k, m):
     return _rule("_ZN2fg18gemm_fewrows_takesEilll", C.c_int(dtype), n, k, m)
 
 
-def f16_tiles(n, k, m):
+def f16_tiles(n, k, m, residual=True):
     """fg::gemm_f16_tiles_takes (csrc/fg_gemm_f16_tiles.hip)"""
-    return _rule("_ZN2fg20gemm_f16_tiles_takesEilll", C.c_int(B.FG_F16), n, k, m)
+    return _rule("_ZN2fg20gemm_f16_tiles_takesEilllb", C.c_int(B.FG_F16), n, k, m, C.c_bool(residual))
