@@ -929,15 +929,21 @@ __global__ __launch_bounds__(256, 2) void gemm_decode16h_kernel(StreamArgs a) {
       w_src = a.w + (int64_t)nt * a.ksteps * 1024 + lane * 16;
       m_src = reinterpret_cast<const uint32_t*>(a.meta) + (int64_t)nt * a.ksteps * 32 + (lane & 31);
     }
-    auto copy_step = [&](int ks, int stage) {
+    // weights, pairs and the activation pieces that every wave copies; then the piece that only some waves have
+    auto copy_step = [&](int ks, int stage) __attribute__((always_inline)) {
       const int kc = ks < ks1 ? ks : ks1 - 1;   // past the end the last step is fetched again
       unsigned char* st = smem + stage * kStageBytes;
       __builtin_amdgcn_global_load_lds((gptr_t)(w_src + (int64_t)kc * 1024), (lptr_t)(st + kAStage + wave * 1024), 16, 0, 0);
       __builtin_amdgcn_global_load_lds((gptr_t)(m_src + (int64_t)kc * 32), (lptr_t)(st + kAStage + 4 * 1024 + wave * 256), 4, 0, 0);
 #pragma unroll
-      for (int i = 0; i < C::kAC0; ++i)
-        if (i < C::kAC1 || wave < C::kMore)
-          __builtin_amdgcn_global_load_lds((gptr_t)(a_src[i] + kc * kKS), (lptr_t)(st + (wave + 4 * i) * 1024), 16, 0, 0);
+      for (int i = 0; i < C::kAC1; ++i)
+        __builtin_amdgcn_global_load_lds((gptr_t)(a_src[i] + kc * kKS), (lptr_t)(st + (wave + 4 * i) * 1024), 16, 0, 0);
+    };
+    auto copy_last_piece = [&](int ks, int stage) __attribute__((always_inline)) {
+      const int kc = ks < ks1 ? ks : ks1 - 1;
+      if (wave < C::kMore)
+        __builtin_amdgcn_global_load_lds((gptr_t)(a_src[C::kAC0 - 1] + kc * kKS),
+                                         (lptr_t)(smem + stage * kStageBytes + (wave + 4 * (C::kAC0 - 1)) * 1024), 16, 0, 0);
     };
 
     // this wave's copies have landed, all but those of the newest N steps
@@ -980,15 +986,22 @@ __global__ __launch_bounds__(256, 2) void gemm_decode16h_kernel(StreamArgs a) {
     __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
 #pragma unroll
-    for (int t = 0; t < kNST; ++t) copy_step(ks0 + t, t);
+    for (int t = 0; t < kNST; ++t) {
+      copy_step(ks0 + t, t);
+      copy_last_piece(ks0 + t, t);
+    }
     wait_steps(IdxC<kNST - 1>{});   // step ks0 has landed
     __builtin_amdgcn_s_barrier();
     read(lds0, IdxC<0>{});
     landed(IdxC<0>{});
 
     int stage = 0;
-    auto step = [&](int ks, auto B_) __attribute__((always_inline)) {
+    // One step, on operands of buffer B.  The reads of the next step are in flight from read() to landed(), and the compiler does
+    // not know it: it may move their registers where paths of the program part or meet.  So a step is one straight line, how to
+    // dequantize is decided outside it, and what only some waves copy comes behind it.
+    auto step = [&](int ks, auto B_, auto PACKED) __attribute__((always_inline)) {
       constexpr int b = decltype(B_)::value;
+      constexpr bool packed = decltype(PACKED)::value != 0;
       const int stage1 = stage + 1 == kNST ? 0 : stage + 1;
       // every wave has read its operands of step ks, and every wave's copies of step ks + 1 have landed
       wait_steps(IdxC<kNST - 2>{});
@@ -997,37 +1010,51 @@ __global__ __launch_bounds__(256, 2) void gemm_decode16h_kernel(StreamArgs a) {
       read(lds0 + stage1 * kStageBytes, IdxC<1 - b>{});
       copy_step(ks + kNST, stage);
       __builtin_amdgcn_sched_barrier(0);
-      // column tile and slice i = 2 sl + ct: eight weights per lane, three MFMAs each
-      auto contract = [&](auto dequant) __attribute__((always_inline)) {
+      PkPair q[2];
+      if constexpr (packed) {
+        q[0] = dequant8_pk_pair(pairs[b][0]);
+        q[1] = dequant8_pk_pair(pairs[b][1]);
+      }
+      // column tile and slice i = 2 sl + ct: eight weights per lane, MT16 MFMAs each
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int sl = i >> 1, ct = i & 1;
-          u4_t w;
-          dequant(ct, cw[b][2 * ct + sl], reinterpret_cast<uint32_t*>(&w));
-#pragma unroll
-          for (int m = 0; m < MT16; ++m)
-            acc[m][ct] = __builtin_amdgcn_mfma_f32_16x16x32_f16(aop[b][sl][m], __builtin_bit_cast(h8_t, w), acc[m][ct], 0, 0, 0);
-        }
-      };
-      if (__all(dequant8_pk_takes(pairs[b][0]) && dequant8_pk_takes(pairs[b][1]))) {
-        const PkPair q[2] = {dequant8_pk_pair(pairs[b][0]), dequant8_pk_pair(pairs[b][1])};
-        contract([&](int ct, uint32_t x, uint32_t* w) __attribute__((always_inline)) { dequant8_pk(x, q[ct], w); });
-      } else {
-        contract([&](int ct, uint32_t x, uint32_t* w) __attribute__((always_inline)) {
+      for (int i = 0; i < 4; ++i) {
+        const int sl = i >> 1, ct = i & 1;
+        u4_t w;
+        if constexpr (packed) {
+          dequant8_pk(cw[b][2 * ct + sl], q[ct], reinterpret_cast<uint32_t*>(&w));
+        } else {
           const h2_t pr = __builtin_bit_cast(h2_t, pairs[b][ct]);
-          dequant8_exact(x, (float)pr.y * 16777216.0f, (float)pr.y * 1048576.0f, (float)pr.x, w);
-        });
+          dequant8_exact(cw[b][2 * ct + sl], (float)pr.y * 16777216.0f, (float)pr.y * 1048576.0f, (float)pr.x, reinterpret_cast<uint32_t*>(&w));
+        }
+#pragma unroll
+        for (int m = 0; m < MT16; ++m)
+          acc[m][ct] = __builtin_amdgcn_mfma_f32_16x16x32_f16(aop[b][sl][m], __builtin_bit_cast(h8_t, w), acc[m][ct], 0, 0, 0);
       }
       __builtin_amdgcn_sched_barrier(0);
-      landed(IdxC<1 - b>{});   // (here, so that no read is in flight where the compiler may move registers, at the loop's end)
+      landed(IdxC<1 - b>{});
+      copy_last_piece(ks + kNST, stage);
       stage = stage1;
     };
+    auto small = [&](auto B_) __attribute__((always_inline)) {   // (wave-uniform; waves may differ: every step has the same barriers)
+      constexpr int b = decltype(B_)::value;
+      return (bool)__all(dequant8_pk_takes(pairs[b][0]) && dequant8_pk_takes(pairs[b][1]));
+    };
+    // Packed steps up to the first large scale in this wave's columns, exact ones from there.
     int ks = ks0;
-    for (; ks + 1 < ks1; ks += 2) {
-      step(ks, IdxC<0>{});
-      step(ks + 1, IdxC<1>{});
+    bool second = false;   // the operands of step ks are in buffer 1
+    while (ks < ks1 && small(IdxC<0>{})) {
+      step(ks++, IdxC<0>{}, IdxC<1>{});
+      second = true;
+      if (ks >= ks1 || !small(IdxC<1>{})) break;
+      step(ks++, IdxC<1>{}, IdxC<1>{});
+      second = false;
     }
-    if (ks < ks1) step(ks, IdxC<0>{});
+    if (ks < ks1 && second) step(ks++, IdxC<1>{}, IdxC<0>{});
+    for (; ks + 1 < ks1; ks += 2) {
+      step(ks, IdxC<0>{}, IdxC<0>{});
+      step(ks + 1, IdxC<1>{}, IdxC<0>{});
+    }
+    if (ks < ks1) step(ks, IdxC<0>{}, IdxC<0>{});
 
     // ---- epilogue: lane holds column l16, rows 4 g4 + 0..3 of each 16 x 16 tile
     const bool full = (ks0 == 0) && (ks1 == a.ksteps);
