@@ -1,19 +1,22 @@
 """fg_linear at 33 to 48 rows on tiled 4-bit weights with FP16 {min, scale} pairs (gemm_decode16h_kernel in csrc/fg_gemm_stream.hip)
 against the same matrix with its pairs in FP32: another kernel and another dequantization, but the same weights and the same order
-of additions, so the same bits.  One K step, even and odd numbers of them, ranges that end inside a tile, a ragged last column
-block; scales from FP16's subnormals up, below and from the 0.25 at which the dequantization changes, of one column or of all."""
+of additions, so the same bits.  Sizes beyond those of the few-rows kernel: one K step, even and odd numbers of them, ranges that
+end inside a tile, whole tiles and ranges in one call, a ragged last column block, all rows of the tiles and few; scales from FP16's subnormals up, below and from the 0.25 at which the dequantization changes, of one column or of all."""
 import pytest
 import torch
 
 from paper_2303_06865_amd import binding as B
+from tests import routes
 
 pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("scales", ["small", "one column", "all", "subnormal"])
-@pytest.mark.parametrize("m,n,k", [(33, 12320, 64), (48, 12320, 128), (37, 21504, 192), (40, 7200, 4160), (41, 70016, 320),
-                                   (35, 28672, 1088)])
+@pytest.mark.parametrize("m,n,k", [(33, 32800, 64), (48, 33056, 128), (37, 36896, 192), (40, 14368, 4160), (41, 70016, 320),
+                                   (35, 28672, 2112), (48, 7200, 8192)])
 def test_f16_pairs_same_bits_as_f32_pairs(m, n, k, scales):
+    # neither matrix is the few-rows kernel's: both run on tiles of three 16-row tiles, which 33 to 48 rows take
+    assert not any(routes.few_rows(t, n, k, m) for t in (B.FG_Q4G64_H16_TILED, B.FG_Q4G64_TILED))
     g = torch.Generator(device="cuda").manual_seed(m + n + k)
     half = lambda *s: torch.empty(s, dtype=torch.float16, device="cuda").normal_(0.0, 1.0, generator=g)
     codes = torch.randint(0, 256, (n, k // 2), dtype=torch.uint8, device="cuda", generator=g)
