@@ -217,6 +217,7 @@ __global__ __launch_bounds__(64 * block_waves(WPH), WPH > 4 ? WPH / 4 : 3) void 
       *reinterpret_cast<uint32_t*>(codes + g * 32 + (lane & 7) * 4) = p;
       if ((lane & 7) == 0) const_cast<meta_t*>(new_group < GPR ? km : vm)[g] = pair;
     }
+    wave_lds_fence();   // put_new() reads what other lanes wrote
   }
   // the new row in the place of what the cache held there
   auto put_new = [&](Buf& b, int chunk) {

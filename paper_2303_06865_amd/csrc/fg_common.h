@@ -200,6 +200,14 @@ __device__ __forceinline__ float wave_sum(float v) {
   return v + dpp_f32<kDppXor1>(v);
 }
 
+// Between LDS writes of a wave's lanes and LDS reads of the same wave's other lanes.  No instruction comes of it (a wave's
+// LDS accesses complete in order), but the compiler, which thinks lane by lane, may not exchange them.
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Unpack one 32-bit word of eight 4-bit codes c0..c7 (c0 in the lowest nibble) into four FP16
 // pairs WITHOUT leaving the register file.  The pairs come out in the order
 //   p[0] = (c0, c4) + 1024,  p[1] = (c1, c5) + 64,  p[2] = (c2, c6) + 1024,  p[3] = (c3, c7) + 64

@@ -220,6 +220,7 @@ __global__ __launch_bounds__(512) void gemm_f16_tiles_kernel(TileArgs a) {
     for (int ct = 0; ct < NT; ++ct)
 #pragma unroll
       for (int r = 0; r < 4; ++r) sums[(16 * m + 4 * g4 + r) * kLdsRow + 16 * ct + l16] = acc[m][ct][r];
+  wave_lds_fence();
   const int r0 = m0 + wm * (MT * 16), c0 = n0 + wn * kCols;
   h8_t res[kItems];
 #pragma unroll

@@ -21,6 +21,11 @@ def stream_code(tmp_path_factory):
     return _code("fg_gemm_stream.hip", tmp_path_factory.mktemp("asm"))
 
 
+@pytest.fixture(scope="module")
+def tiles_code(tmp_path_factory):
+    return _code("fg_gemm_f16_tiles.hip", tmp_path_factory.mktemp("asm"))
+
+
 def test_whole_tiles_without_a_residual_store_without_waits(stream_code):
     """A lane stores one piece of each of its 16 RG rows of a finished tile, in FP16 or in FP32.  Where no residual is added
     none of these stores may wait for the memory (that would be for the store before it)."""
@@ -121,10 +126,10 @@ def test_reads_in_flight_are_seen():
     assert _reads_in_flight(code % "v_mov_b32_e32 v3, v8") == (1, [], [])
 
 
-def test_no_register_of_an_lds_read_in_flight_is_touched(stream_code, tmp_path):
+def test_no_register_of_an_lds_read_in_flight_is_touched(stream_code, tiles_code, tmp_path):
     """The compiler takes the registers of hand-placed LDS reads as written at once."""
     found = 0
-    for text in (stream_code, _code("fg_gemm_f16_tiles.hip", tmp_path), _code("fg_gemm_f16w.hip", tmp_path)):
+    for text in (stream_code, tiles_code, _code("fg_gemm_f16w.hip", tmp_path)):
         for name, body in _kernels(text):
             reads, touched, branches = _reads_in_flight(body)
             found += reads > 0
@@ -133,3 +138,19 @@ def test_no_register_of_an_lds_read_in_flight_is_touched(stream_code, tmp_path):
             if "gemm_decode16h_kernel" in name or "gemm_f16_tiles_kernel" in name:
                 assert reads and not branches, (name, branches)
     assert found >= 60
+
+
+def test_lanes_that_exchange_through_lds_are_fenced(tiles_code, tmp_path):
+    """Where a wave's lanes read from LDS what its other lanes wrote, with no barrier of the workgroup between, a barrier of the
+    wave stands there, which is no instruction but holds the compiler: the finished sums of the FP16 tiles, and the new cache
+    row of the decode attention that stores it."""
+    for name, body in _kernels(tiles_code):
+        if "gemm_f16_tiles_kernel" in name:
+            tail = body[body.rindex("; wave barrier"):] if "; wave barrier" in body else body
+            first = body.index("ds_write")
+            assert first < len(body) - len(tail) and "ds_read" in tail and "ds_write" not in tail, name
+            assert "ds_read" not in body[first:len(body) - len(tail)], name
+    stores = [(name, body) for name, body in _kernels(_code("fg_attn_decode.hip", tmp_path))
+              if re.search(r"attn_decode_q4_kernelILi\d+ELi\d+ELb[01]ELb0ELb1E", name)]
+    assert len(stores) == 16   # two head sizes, one to eight waves per head, FP32 and FP16 pairs
+    assert all("; wave barrier" in body for _, body in stores)
