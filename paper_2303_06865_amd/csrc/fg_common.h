@@ -200,6 +200,29 @@ __device__ __forceinline__ float wave_sum(float v) {
   return v + dpp_f32<kDppXor1>(v);
 }
 
+// The places of LayerNorm where a product could be rounded before it is added, or a result once or twice on its way to FP16:
+// written out, because what one kernel leaves to the compiler another one, that normalizes the same rows, may get otherwise.
+// q plus the squared distances of a piece of eight; of the first piece's first two squares the second one is rounded.
+__device__ __forceinline__ float ln_add_squares(const h8_t v, float mean, float q, bool first) {
+  float d[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) d[i] = (float)v[i] - mean;
+  q = first ? __builtin_fmaf(d[0], d[0], d[1] * d[1]) : __builtin_fmaf(d[1], d[1], __builtin_fmaf(d[0], d[0], q));
+#pragma unroll
+  for (int i = 2; i < 8; ++i) q = __builtin_fmaf(d[i], d[i], q);
+  return q;
+}
+__device__ __forceinline__ h8_t ln_normalize(const h8_t v, float mean, float rstd, const h8_t gamma, const h8_t beta) {
+  h8_t o;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    float y = __builtin_fmaf(((float)v[i] - mean) * rstd, (float)gamma[i], (float)beta[i]);
+    __asm__("" : "+v"(y));   // a binary32 number: v_fma_mixlo_f16 would round only once
+    o[i] = (half_t)y;
+  }
+  return o;
+}
+
 // Between LDS writes of a wave's lanes and LDS reads of the same wave's other lanes.  No instruction comes of it (a wave's
 // LDS accesses complete in order), but the compiler, which thinks lane by lane, may not exchange them.
 __device__ __forceinline__ void wave_lds_fence() {

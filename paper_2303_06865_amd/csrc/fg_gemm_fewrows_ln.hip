@@ -259,16 +259,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_fewrows_ln_kernel(LnArgs a) {
       float q = 0.f;
 #pragma unroll
       for (int j = 0; j < NC; ++j)
-        if (64 * vw + lane + 256 * j < pieces) {
-          const h8_t v = __builtin_bit_cast(h8_t, xv[i][j]);
-          float d[8];
-#pragma unroll
-          for (int e = 0; e < 8; ++e) d[e] = (float)v[e] - mean[i];
-          // of the first two squares the second one is rounded, as in layernorm_reg_kernel
-          q = j == 0 ? __builtin_fmaf(d[0], d[0], d[1] * d[1]) : __builtin_fmaf(d[1], d[1], __builtin_fmaf(d[0], d[0], q));
-#pragma unroll
-          for (int e = 2; e < 8; ++e) q = __builtin_fmaf(d[e], d[e], q);
-        }
+        if (64 * vw + lane + 256 * j < pieces) q = ln_add_squares(__builtin_bit_cast(h8_t, xv[i][j]), mean[i], q, j == 0);
       q = wave_sum(q);
       if (lane == 0) ln_red[1][row][vw] = q;
     }
@@ -284,10 +275,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_fewrows_ln_kernel(LnArgs a) {
       for (int j = 0; j < NC; ++j) {
         const int c = 64 * vw + lane + 256 * j;
         if (c < a.steps * 16) {   // 16-byte chunk c of row r lies at chunk c ^ (r & 15) of its row; past K: zeros
-          const h8_t v = __builtin_bit_cast(h8_t, xv[i][j]), g = __builtin_bit_cast(h8_t, gv[j]), be = __builtin_bit_cast(h8_t, bv[j]);
-          h8_t o;
-#pragma unroll
-          for (int e = 0; e < 8; ++e) o[e] = (half_t)__builtin_fmaf(((float)v[e] - mean[i]) * rstd, (float)g[e], (float)be[e]);
+          const h8_t o = ln_normalize(__builtin_bit_cast(h8_t, xv[i][j]), mean[i], rstd, __builtin_bit_cast(h8_t, gv[j]), __builtin_bit_cast(h8_t, bv[j]));
           *reinterpret_cast<u4_t*>(smem + row * row_bytes + ((c ^ (row & 15)) << 4)) = c < pieces ? __builtin_bit_cast(u4_t, o) : zero4;
         }
       }

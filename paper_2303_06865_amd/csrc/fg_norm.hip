@@ -37,7 +37,7 @@ __global__ __launch_bounds__(256) void layernorm_kernel(const half_t* __restrict
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       const float d = (float)v[i] - mean;
-      q += d * d;
+      q = __builtin_fmaf(d, d, q);
     }
   }
   const float var = block_sum_256(q, red[1]) / (float)cols;
@@ -46,10 +46,7 @@ __global__ __launch_bounds__(256) void layernorm_kernel(const half_t* __restrict
     const h8_t v = *reinterpret_cast<const h8_t*>(xr + c * 8);
     const h8_t g = *reinterpret_cast<const h8_t*>(gamma + c * 8);
     const h8_t b = *reinterpret_cast<const h8_t*>(beta + c * 8);
-    h8_t o;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) o[i] = (half_t)(((float)v[i] - mean) * rstd * (float)g[i] + (float)b[i]);
-    *reinterpret_cast<h8_t*>(orow + c * 8) = o;
+    *reinterpret_cast<h8_t*>(orow + c * 8) = ln_normalize(v, mean, rstd, g, b);
   }
 }
 
@@ -94,13 +91,7 @@ __global__ __launch_bounds__(256) void layernorm_reg_kernel(const half_t* __rest
   float q = 0.f;
 #pragma unroll
   for (int j = 0; j < NC; ++j)
-    if (threadIdx.x + 256 * j < nchunk) {
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const float d = (float)v[j][i] - mean;
-        q += d * d;
-      }
-    }
+    if (threadIdx.x + 256 * j < nchunk) q = ln_add_squares(v[j], mean, q, j == 0);
   const float var = block_sum_256(q, red[1]) / (float)cols;
   const float rstd = 1.0f / sqrtf(var + eps);
 #pragma unroll
@@ -108,10 +99,7 @@ __global__ __launch_bounds__(256) void layernorm_reg_kernel(const half_t* __rest
     const int c = threadIdx.x + 256 * j;
     if (c < nchunk) {
       if (!AHEAD) load_gb(j);
-      h8_t o;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) o[i] = (half_t)(((float)v[j][i] - mean) * rstd * (float)g[j][i] + (float)b[j][i]);
-      *reinterpret_cast<h8_t*>(orow + c * 8) = o;
+      *reinterpret_cast<h8_t*>(orow + c * 8) = ln_normalize(v[j], mean, rstd, g[j], b[j]);
     }
   }
 }
