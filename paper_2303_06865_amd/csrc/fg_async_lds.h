@@ -83,8 +83,8 @@ __device__ __forceinline__ void sum_parts(const float4* partial, int64_t slot4, 
 // The end of a reduction pass: rows row0 .. row0 + 3 of column `col`.  Bias and residual are requested before the partial
 // sums, so that they arrive with them; read where they are added, row by row behind the store of the row before (which the
 // compiler has to take for an alias), they are four more round trips to memory, one after the other.  A projection of tiled
-// weights with a residual, both passes, us, so -> requested ahead: 12288 x 12288 at 80 rows 46.8 -> 46.0, 144 rows 66.7 ->
-// 65.5, 512 rows 169.5 -> 165.6; 7168 x 7168 at 1000 rows 130.5 -> 126.5.
+// weights with a residual, both passes, us, so -> requested ahead: 12288 x 12288 at 80 rows 47.2 -> 46.4, 144 rows 66.3 ->
+// 66.0, 512 rows 170.3 -> 164.7; 7168 x 7168 at 1000 rows 133.7 -> 128.8.
 struct FinishRows {
   uint32_t bias, res[4];   // FP16 bits
   __device__ __forceinline__ void request(const half_t* b, const half_t* residual, int64_t ldr, int row0, int M, int col) {
@@ -98,7 +98,10 @@ struct FinishRows {
     }
   }
   __device__ __forceinline__ void store(const float4& sum, int relu, bool residual, half_t* out16, float* out32, int64_t ldo, int row0,
-                                        int M, int col) const {
+                                        int M, int col) {
+    __asm__ volatile("" : "+v"(bias));   // (else converted, that is waited for, where it was requested)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) __asm__ volatile("" : "+v"(res[r]));
     const float o[4] = {sum.x, sum.y, sum.z, sum.w};
     const float b = (float)__builtin_bit_cast(half_t, (uint16_t)bias);
 #pragma unroll

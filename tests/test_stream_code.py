@@ -154,3 +154,14 @@ def test_lanes_that_exchange_through_lds_are_fenced(tiles_code, tmp_path):
               if re.search(r"attn_decode_q4_kernelILi\d+ELi\d+ELb[01]ELb0ELb1E", name)]
     assert len(stores) == 16   # two head sizes, one to eight waves per head, FP32 and FP16 pairs
     assert all("; wave barrier" in body for _, body in stores)
+
+
+def test_residual_is_on_its_way_with_the_partial_sums(stream_code, tiles_code):
+    """The reduction passes ask for the residual's four rows, and wait for none of them before they ask for partial sums."""
+    finish = [(name, body) for text in (stream_code, tiles_code) for name, body in _kernels(text) if "_finish_kernel" in name]
+    assert len(finish) == 5   # one and two items per thread on two layouts, and the FP16 tiles'
+    for name, body in finish:
+        kinds = {"global_load_ushort": "R", "global_load_dwordx4": "P"}
+        seq = "".join(kinds.get(m.group(0), "W") for m in re.finditer(r"global_load_ushort|global_load_dwordx4|s_waitcnt[^\n]*vmcnt", body))
+        assert "RRRR" in seq and "P" in seq, name
+        assert not re.search("RRRRR*W", seq), (name, seq)
