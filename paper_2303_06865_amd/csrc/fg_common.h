@@ -95,6 +95,12 @@ int gemm_f16w_forced(int64_t n);   // column tiles fixed by the environment, or 
 size_t gemm_f16w_workspace(int64_t n, int64_t k, int64_t m);
 int gemm_f16w_launch(const LinearArgs& a, void* ws, size_t ws_bytes, hipStream_t stream);
 // row-major FP16 weights, some hundred rows (csrc/fg_gemm_f16_tiles.hip); any workspace will do
+struct F16TilePick {
+  int mt, nt, splits;   // tiles of 32 mt x 32 nt, ranges of the contraction
+  int64_t items;        // workgroups
+  float us;             // expected time
+};
+F16TilePick gemm_f16_tiles_pick(int64_t n, int64_t k, int64_t m, size_t ws_bytes);
 bool gemm_f16_tiles_takes(int dtype, int64_t n, int64_t k, int64_t m, bool residual);
 int gemm_f16_tiles_launch(const LinearArgs& a, void* ws, size_t ws_bytes, hipStream_t stream);
 size_t gemm_stream_workspace(int64_t n, int64_t k, int64_t m);

@@ -7,7 +7,7 @@
 // to be as large as leaves none of the CUs idle.  The kernels that this one took these sizes from have one tile of 192 or
 // 256 x 256; at these sizes they cut it along the contraction to fill the chip, and pay with partial sums and a second pass.
 //   * Tiles from 32 x 64 to 256 x 128, each with the whole contraction to itself where there are enough of them; which one, and
-//     into how many ranges a long contraction is cut, is decided by what each measured (pick_tile).
+//     into how many ranges a long contraction is cut, is decided by what each measured (gemm_f16_tiles_pick).
 //   * Four waves compute, as 2 x 2, one per SIMD: of 16 MT x 16 NT each, so an operand that is in LDS is read twice and not
 //     eight times.  Four other waves do nothing but copy, global -> LDS, three to five steps ahead.  A copy holds the
 //     wave that issues it for as long as the path into the CU is busy; in the computing waves that was time without an MFMA
@@ -318,13 +318,11 @@ constexpr TileShape kShapes[] = {
     {3, 2, -1.0f, 3.84f, 0.282f}, {4, 2, -0.6f, 3.68f, 0.397f}, {4, 3, 2.1f, 5.90f, 0.478f},   {4, 4, -5.5f, 10.14f, 0.511f},
     {6, 3, -4.7f, 10.59f, 0.528f}, {6, 4, -3.6f, 10.84f, 0.650f}, {8, 4, -5.0f, 14.04f, 0.794f},
 };
-struct TilePick {
-  int shape, splits;
-  int64_t items;   // workgroups
-  float us;
-};
-TilePick pick_tile(int64_t n, int64_t k, int64_t m, size_t ws_bytes) {
-  TilePick best = {-1, 1, 0, 0.f};
+
+}  // namespace
+
+F16TilePick gemm_f16_tiles_pick(int64_t n, int64_t k, int64_t m, size_t ws_bytes) {
+  F16TilePick best = {0, 0, 1, 0, 0.f};
   const int n32 = (int)n, m32 = (int)m, steps = (int)(k / kTS);
   for (int i = 0; i < (int)(sizeof(kShapes) / sizeof(kShapes[0])); ++i) {
     const TileShape& s = kShapes[i];
@@ -335,14 +333,12 @@ TilePick pick_tile(int64_t n, int64_t k, int64_t m, size_t ws_bytes) {
       if (bytes > (int64_t)ws_bytes) break;
       const float t = s.first + (float)((tiles * sp + 255) >> 8) * (s.round + (float)((steps + sp - 1) / sp) * s.step) +
                       (sp == 1 ? 0.f : 4.f + (float)bytes * 0.33e-6f);
-      if (best.shape < 0 || t < best.us) best = {i, sp, tiles * sp, t};
+      if (!best.mt || t < best.us) best = {s.mt, s.nt, sp, tiles * sp, t};
       if (tiles * sp >= 512) break;   // the chip is full: more ranges only add partial sums
     }
   }
   return best;
 }
-
-}  // namespace
 
 // Which calls this kernel takes, by measurement against the kernels that otherwise run (their time over this one's):
 //   33 to 128 rows: matrices of 4 to 230 M elements (71 x 8064 x 2048 1.92, 35 x 7168 x 7168 1.31, 128 x 4096 x 4096 1.36,
@@ -378,7 +374,7 @@ bool gemm_f16_tiles_takes(int dtype, int64_t n, int64_t k, int64_t m, bool resid
   }
   const bool short_k = m > 320 && k <= 256 && !residual, long_k = m > 64 && k > 7000;
   if (!short_k && !long_k && size <= 70000000) return true;
-  const TilePick pick = pick_tile(n, k, m, linear_workspace_bytes(dtype, n, k, m));
+  const F16TilePick pick = gemm_f16_tiles_pick(n, k, m, linear_workspace_bytes(dtype, n, k, m));
   const int64_t rounds = ceil_div(pick.items, 256);
   const float fill = (float)pick.items / (float)(rounds * 256);
   if (short_k && rounds >= 2) return false;
@@ -389,8 +385,7 @@ bool gemm_f16_tiles_takes(int dtype, int64_t n, int64_t k, int64_t m, bool resid
 }
 
 int gemm_f16_tiles_launch(const LinearArgs& la, void* ws, size_t ws_bytes, hipStream_t stream) {
-  const TilePick pick = pick_tile(la.n, la.k, la.m, ws_bytes);
-  const TileShape& s = kShapes[pick.shape];
+  const F16TilePick s = gemm_f16_tiles_pick(la.n, la.k, la.m, ws_bytes);
   TileArgs a;
   a.w = reinterpret_cast<const half_t*>(la.w_data);
   a.x = la.x;
@@ -400,7 +395,7 @@ int gemm_f16_tiles_launch(const LinearArgs& la, void* ws, size_t ws_bytes, hipSt
   a.K = (int)la.k;
   a.m_blocks = (int)ceil_div(la.m, 32 * s.mt);
   a.n_tiles = (int)ceil_div(la.n, 32 * s.nt);
-  a.splits = pick.splits;
+  a.splits = s.splits;
   a.ksteps = (int)(la.k / kTS);
   a.bias = la.bias;
   a.residual = la.residual;

@@ -1,6 +1,7 @@
 """fg_linear on FP16 weights from 33 rows up (csrc/fg_gemm_f16_tiles.hip) against binary32: every tile shape, with the contraction
-whole and in two, four and eight ranges, fewer steps than the stages that are copied ahead, rows and columns that end inside
-a tile, both sides of the rows at which it takes over; and what it must leave to the other kernels."""
+whole and in two, four and eight ranges, fewer steps than the stages that are copied ahead, rows and columns that end inside a
+tile.  That a size runs there, and on which tiles, is asked of the library's own rule; tests/test_f16_tiles_lines.py has sizes
+on both sides of it, tests/test_gpu_split_k.py what the former kernels keep."""
 import pytest
 import torch
 
@@ -11,38 +12,38 @@ from tests.util import assert_close
 pytestmark = pytest.mark.gpu
 
 CASES = [
-    # m, n, k                 tile (32 x rows, 32 x columns), ranges
-    (1500, 32, 320),        # 1 x 2, one column tile of which half is there
-    (1500, 32, 2048),       # ... four ranges
-    (1500, 32, 64),         # 2 x 2, a single step
-    (2049, 32, 3072),       # ... four ranges, one row in the last block
-    (1500, 32, 4096),       # ... eight
-    (33, 8224, 512),        # 33 rows, the fewest
-    (2049, 512, 64),        # 2 x 3
-    (33, 8224, 8192),       # ... two ranges
-    (33, 6144, 4096),       # ... four
-    (33, 2080, 8192),       # ... eight
-    (129, 8224, 2048),      # 2 x 4
-    (3000, 512, 64),        # 3 x 2
-    (65, 6144, 4096),       # ... two ranges
-    (2049, 96, 4096),       # ... four
-    (2049, 32, 4096),       # ... eight
-    (2049, 768, 128),       # 4 x 2, two steps
-    (1500, 288, 8192),      # ... four ranges
-    (97, 21504, 1088),      # 96 rows and one
-    (128, 20512, 1024),     # 128 rows, a last column tile of 32
-    (66, 17408, 7168),      # 4 x 3
-    (2049, 1056, 192),      # 4 x 4, three steps
-    (100, 4128, 8192),      # ... four ranges
-    (333, 1056, 8192),      # ... eight
-    (2049, 2080, 64),       # 6 x 3
-    (129, 8224, 4096),      # ... two ranges
-    (129, 4128, 8192),      # ... four
-    (193, 2080, 8256),      # ... eight, of 16 and 17 steps
-    (2048, 2304, 256),      # 6 x 4, four steps
-    (385, 12288, 1984),
-    (1500, 4128, 320),      # 8 x 4
-    (257, 20512, 704),
+    # m, n, k, (tile rows / 32, tile columns / 32, ranges of the contraction)
+    (1500, 32, 320, (1, 2, 1)),       # one column tile of which half is there
+    (1500, 32, 2048, (1, 2, 4)),
+    (1500, 32, 64, (2, 2, 1)),        # a single step
+    (2049, 32, 3072, (2, 2, 4)),      # one row in the last block
+    (1500, 32, 4096, (2, 2, 8)),
+    (2049, 512, 64, (2, 3, 1)),
+    (33, 8224, 8192, (2, 3, 2)),      # 33 rows, the fewest
+    (33, 6144, 4096, (2, 3, 4)),
+    (33, 2080, 8192, (2, 3, 8)),
+    (129, 8224, 2048, (2, 4, 1)),
+    (3000, 512, 64, (3, 2, 1)),
+    (65, 6144, 4096, (3, 2, 2)),
+    (2049, 96, 4096, (3, 2, 4)),
+    (2049, 32, 4096, (3, 2, 8)),
+    (2049, 768, 128, (4, 2, 1)),      # two steps
+    (1500, 288, 8192, (4, 2, 4)),
+    (97, 21504, 1088, (4, 4, 1)),     # 96 rows and one
+    (128, 20512, 1024, (4, 4, 1)),    # 128 rows, a last column tile of 32
+    (66, 17408, 7168, (4, 3, 1)),
+    (2049, 1056, 192, (4, 4, 1)),     # three steps
+    (100, 4128, 8192, (4, 4, 4)),
+    (333, 1056, 8192, (4, 4, 8)),
+    (2049, 2080, 64, (6, 3, 1)),
+    (129, 8224, 4096, (6, 3, 2)),
+    (129, 4128, 8192, (6, 3, 4)),
+    (192, 2080, 8256, (6, 3, 8)),     # ranges of 16 and 17 steps
+    (193, 2080, 8256, (3, 2, 2)),     # ... and one row more
+    (2048, 2304, 256, (6, 4, 1)),     # four steps
+    (385, 12288, 1984, (8, 4, 1)),
+    (1500, 4128, 320, (8, 4, 1)),
+    (257, 20512, 704, (4, 4, 1)),
 ]
 
 
@@ -52,8 +53,10 @@ def _inputs(m, n, k):
     return half(n, k) * 0.05, half(m, k), half(n), half(m, n)
 
 
-@pytest.mark.parametrize("m,n,k", CASES)
-def test_linear_f16_tiles(m, n, k):
+@pytest.mark.parametrize("m,n,k,tile", CASES)
+def test_linear_f16_tiles(m, n, k, tile):
+    assert all(routes.f16_tiles(n, k, m, residual) for residual in (True, False)) and not routes.few_rows(B.FG_F16, n, k, m)
+    assert routes.f16_tile(n, k, m) == tile
     w, x, bias, res = _inputs(m, n, k)
     mat = B.Mat.from_f16(w, False)
     # the sums, then the results rounded to FP16: 2^-11 of up to about 5 sqrt(k) 0.05 in single values, 1e-2 at sums up to 20
@@ -103,8 +106,9 @@ def test_logits_at_any_address():
     assert buf[0] == 0 and buf[-1] == 0
 
 
-@pytest.mark.parametrize("rows,vocab,h1", [(100, 34016, 768), (129, 8000, 768), (300, 8032, 1024), (512, 33024, 256)])
+@pytest.mark.parametrize("rows,vocab,h1", [(100, 34016, 768), (129, 20000, 768), (300, 8032, 1024), (512, 33024, 320)])
 def test_lm_head_rows(rows, vocab, h1):
+    assert routes.f16_tiles(vocab, h1, rows, False) and not routes.few_rows(B.FG_F16, vocab, h1, rows)
     g = torch.Generator(device="cuda").manual_seed(rows + vocab)
     half = lambda *s: torch.empty(s, dtype=torch.float16, device="cuda").normal_(0.0, 1.0, generator=g)
     cfg = B.Cfg(h1, h1 // 64, 4 * h1, vocab, 64)
