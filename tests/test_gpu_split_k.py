@@ -1,11 +1,13 @@
 """fg_linear where the contraction is shared by workgroups and a second pass adds the partial sums: less work than
 workgroups (down to one range), ranges that end inside a tile, begin at one or hold several, rows and columns that end
 inside a tile, one and two items per thread of the second pass, and the same bits on every call.  The sizes are beyond
-those that csrc/fg_gemm_fewrows.hip takes."""
+those that csrc/fg_gemm_fewrows.hip takes, but for two (FP16 and tiled 4-bit, 500 rows); FP16 weights of most of them run on
+csrc/fg_gemm_f16_tiles.hip, so those kernels on 256 columns have FP16 sizes of their own below."""
 import pytest
 import torch
 
 from paper_2303_06865_amd import binding as B
+from tests import routes
 from tests.util import assert_close
 
 pytestmark = pytest.mark.gpu
@@ -72,7 +74,7 @@ def _check(m, n, k, quant, tiled, h16):
     (577, 8224, 512),
     (1152, 11040, 320),
     (1344, 9248, 192),
-    (1281, 4096, 7168),    # FP16: blocks of 256 rows here, and of 192 in the next four
+    (1281, 4096, 7168),
     (1281, 4064, 7168),
     (1281, 4096, 7104),
     (1344, 12320, 7168),
@@ -80,6 +82,33 @@ def _check(m, n, k, quant, tiled, h16):
 ])
 def test_linear_blocks_of_192_rows(m, n, k, fmt):
     test_linear_shared_contraction(m, n, k, fmt)
+
+
+# FP16 weights that neither the few-rows kernel nor the FP16 tiles take: the kernels on 256 columns, at every number of 32-row tiles,
+# one and two row blocks of them, blocks of 192 and of 256 rows, whole tiles and ranges, ragged rows and columns, one K step and many.
+@pytest.mark.parametrize("m,n,k,residual", [
+    (24, 33056, 1088, True), (60, 57376, 1088, True), (81, 65536, 320, True), (72, 8352, 13312, True), (80, 8352, 21824, False),
+    (82, 4256, 17536, True), (112, 12832, 18048, True), (128, 18464, 12864, True), (129, 33056, 6400, True),
+    (200, 38912, 2560, False), (231, 41120, 2816, False), (257, 36896, 3072, False), (320, 33056, 6400, True),
+    (321, 32800, 64, False), (384, 33024, 128, False), (343, 36896, 192, False), (385, 33024, 192, False), (513, 33056, 256, True),
+    (576, 33056, 448, True), (577, 33056, 320, True), (1100, 33056, 64, True), (1152, 32800, 320, True),
+    (1281, 12288, 17152, True),   # blocks of 256 rows
+    (1281, 12320, 17152, True),   # ... and of 192
+    (2049, 8224, 64, True), (2100, 8224, 320, True), (2100, 96, 4160, True), (2304, 2080, 4160, True), (3000, 8224, 448, False),
+])
+def test_linear_f16_past_the_tiles(m, n, k, residual):
+    assert not routes.few_rows(B.FG_F16, n, k, m) and not routes.f16_tiles(n, k, m, residual)
+    g = torch.Generator(device="cuda").manual_seed(m + n + k)
+    half = lambda *s: torch.empty(s, dtype=torch.float16, device="cuda").normal_(0.0, 1.0, generator=g)
+    w, x, bias, res = half(n, k) * 0.05, half(m, k), half(n), half(m, n) if residual else None
+    y = x.float() @ w.float().t() + bias.float()
+    want = torch.relu(y) + (res.float() if residual else 0.0)
+    mat = B.Mat.from_f16(w, False)
+    got = B.fg_linear(mat, bias, x, residual=res, relu=True)
+    # results are rounded to FP16: half a unit of the largest, 2^-11 of it
+    assert_close(got.cpu().numpy(), want.cpu().numpy(), "f16 past the tiles m=%d n=%d k=%d" % (m, n, k),
+                 mabs=max(1e-2, float(want.abs().max()) * 2.0 ** -11))
+    assert torch.equal(B.fg_linear(mat, bias, x, residual=res, relu=True), got)
 
 
 # Canonical 4-bit weights past the lines of the few-rows kernel, and FP16 weights whose columns 32 does not divide, which
