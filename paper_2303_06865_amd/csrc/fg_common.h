@@ -293,6 +293,7 @@ __device__ __forceinline__ void dequant8_exact(uint32_t x, float s24, float s20,
 // c * 2^-18, scale * 2^18 is exact, and v_pk_fma_f16 rounds c * scale + min once, two weights at a time.  Sixteen VALU
 // instructions per eight weights, of 56 cycles together where the thirteen of dequant8_exact take 85 (v_fma_mixlo_f16 and
 // v_fma_mixhi_f16: 9 each).  For scales below 0.25, else scale * 2^18 is no finite FP16 number: dequant8_pk_takes().
+// (gemm_decode16h_kernel uses it; on the other kernels that read such pairs it has not been tried.)
 struct PkPair {
   h2_t s18, mn;
 };

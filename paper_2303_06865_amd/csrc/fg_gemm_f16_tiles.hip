@@ -2,7 +2,7 @@
 //
 // out[M, N] = act(x[M, K] . W[N, K]^T + bias) + residual
 //
-// What bounds them: how fast a CU takes operands in.  256 CUs together read 26 TB/s from L2, but 60 to 75 GB/s each while
+// What bounds them: how fast a CU takes operands in.  256 CUs together read 30 TB/s from L2, but 60 to 75 GB/s each while
 // part of it comes from HBM, and a tile of BM x BN takes in BM + BN rows of 128 bytes per step of 64, so the tiles have
 // to be as large as leaves none of the CUs idle.  The kernels that this one took these sizes from have one tile of 192 or
 // 256 x 256; at these sizes they cut it along the contraction to fill the chip, and pay with partial sums and a second pass.
@@ -18,8 +18,8 @@
 //   * The accumulators are updated in place by hand-placed instructions: left to the compiler, the loop moves them between
 //     register files (92 -> 82 us at 16384 x 4096 when that was changed).
 // Measured against those kernels, GEMM and second pass, us: 333 rows 12288 x 4096 72.5 -> 46.2, 4096 x 4096 32.9 -> 21.2, 16384 x
-// 4096 74.3 -> 55.8, 4096 x 16384 69.6 -> 60.3; 512 rows 12288 x 4096 100.6 -> 61.4, 7168 x 7168 105 -> 62; 1000 rows 2304 x 768
-// 29.7 -> 12.3; 2048 rows 12288 x 4096 247 -> 195.
+// 4096 74.3 -> 55.8, 4096 x 16384 69.6 -> 60.3; 512 rows 12288 x 4096 100.6 -> 61.4, 7168 x 7168 105 -> 62; 2048 rows 12288 x
+// 4096 247 -> 195.
 #include "fg_common.h"
 #include "fg_async_lds.h"
 

@@ -414,6 +414,8 @@ int launch_few_fmt(const FewArgs& a, hipStream_t stream) {
 //   canonical       16384 x 64 x 128 (65536) 13.7 vs 17.7, x 200 (114688) 23 vs 18; 50272 x 192 x 128 (201088) 50 vs 63,
 //                   x 200 (351904) 82 vs 76; 50272 x 384 x 320 (502720) 104 vs 130, x 512 164 vs 124; 16384 x 512 x 512
 //                   (262144) 61 vs 28; beyond 512 rows 4096 x 64 x 1000 (131072) 26 vs 29, 16384 x 256 x 1000 116 vs 43
+// The FP16 lines beyond 32 rows are older than gemm_f16_tiles_kernel, which takes what lies past them now: measured against the
+// kernels before it, they keep sizes at which it would be the faster one (2304 x 768 at 1000 rows 29.7 us here, 12.3 there).
 // (FP16 columns that 32 does not divide are outside the FP16 exceptions: the kernel they would fall to is the slow one.)
 bool gemm_fewrows_takes(int dtype, int64_t n, int64_t k, int64_t m) {
   if (m < 1 || m > 1024 || k % kGroup != 0) return false;
