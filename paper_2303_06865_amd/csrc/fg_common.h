@@ -104,7 +104,10 @@ F16TilePick gemm_f16_tiles_pick(int64_t n, int64_t k, int64_t m, size_t ws_bytes
 bool gemm_f16_tiles_takes(int dtype, int64_t n, int64_t k, int64_t m, bool residual);
 int gemm_f16_tiles_launch(const LinearArgs& a, void* ws, size_t ws_bytes, hipStream_t stream);
 size_t gemm_stream_workspace(int64_t n, int64_t k, int64_t m);
-float gemm_stream_f16_us(int64_t n, int64_t k, int64_t m);   // expected time on FP16 weights, from 321 rows up
+// FP16 weights: are the tiles the largest of their kind (160, 192 or 256 rows) and their number one that keeps all workgroups
+// busy to the end; the expected time, from 321 rows up
+bool gemm_stream_f16_whole_rounds(int64_t n, int64_t k, int64_t m);
+float gemm_stream_f16_us(int64_t n, int64_t k, int64_t m);
 int gemm_stream_launch(const LinearArgs& a, void* ws, size_t ws_bytes, hipStream_t stream);
 int pack_weights_launch(const void* codes, const void* meta, bool meta_f16, int64_t n, int64_t k, void* codes_out, void* meta_out,
                         hipStream_t stream);

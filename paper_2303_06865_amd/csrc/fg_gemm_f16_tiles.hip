@@ -351,13 +351,16 @@ F16TilePick gemm_f16_tiles_pick(int64_t n, int64_t k, int64_t m, size_t ws_bytes
 //   1.52, 6000 x 2048 x 2048 1.36, 18432 x 768 x 768 1.53, 3000 x 4096 x 4096 1.36, but 4096 x 4096 x 4096 0.94, 9000 x 2048 x 2048
 //   0.90, 6000 x 2048 x 8192 0.98).
 // Not within these lines (measured over 2500 shapes, this kernel's time over the other's):
-//   65 to 96 rows, contractions beyond 8192, where the tiles leave more than a quarter of the chip without work (the copies of those
-//   that there are don't take what HBM gives): 92 x 8352 x 13312 1.30, 70 x 8576 x 23744 1.23, 82 x 4256 x 17536 1.21, 78 x 5408 x
-//   15488 1.05; but 80 x 4096 x 10560 0.85, 85 x 7168 x 16768 0.94.  Beyond 20000 wherever the narrow tiles don't take the call: 72 x
+//   65 to 96 rows, contractions beyond 8192, where the tiles leave a quarter of the chip and more without work (the copies of those
+//   that there are don't take what HBM gives): 92 x 8352 x 13312 1.30, 70 x 8576 x 23744 1.23, 82 x 4256 x 17536 1.21, 80 x 12288 x
+//   12288 1.05, but 80 x 4096 x 10560 0.85, 85 x 7168 x 16768 0.94; or where ranges make several rounds: 80 x 12288 x 16384 1.06.  Beyond 20000 wherever the narrow tiles don't take the call: 72 x
 //   5504 x 28928 1.13, 94 x 8128 x 22336 1.03, but 69 x 4864 x 28480 0.85.  More rows, matrices of more than 60 M, where nearly half
 //   of the chip has no work: 97 x 4256 x 24320 1.22, 224 x 16448 x 9984 1.09, 225 x 16480 x 7936 1.08.
 //   Contractions of up to 256 in more than one round, without a residual: a workgroup is its start and its epilogue, and the other
 //   kernel's stay on: 1089 x 27488 x 64 2.05, 343 x 36896 x 192 1.32, 800 x 15328 x 128 1.08, 1247 x 8640 x 64 0.97.
+//   Sizes that fill whole rounds of the other kernel, 256 tiles each, without a residual: of 256 x 256 1000 x 16384 x 320 1.29, x 1024
+//   1.15, x 4096 1.05, x 7168 1.02, 2000 x 8192 x 768 1.22, 500 x 32768 x 2048 1.08; of 160 x 256 320 x 32768 x 1024 1.10, 160 x 65536 x
+//   2048 1.06; but 2048 x 7936 x 4096 0.75, 256 x 32768 x 1024 (tiles of 128 rows) 0.87.
 //   Matrices of more than 70 M in three rounds and more: 383 x 33408 x 2496 1.21, 1491 x 12416 x 13248 1.09, 231 x 41120 x 2816 1.05,
 //   1260 x 27200 x 4864 1.04.  From 321 rows by what both are expected to take: kept 0.90 (29 shapes), left to the other 1.00 (81);
 //   below, with a residual 0.68 to 0.84.  (In one or two rounds 0.70 to 0.82.)
@@ -372,13 +375,16 @@ bool gemm_f16_tiles_takes(int dtype, int64_t n, int64_t k, int64_t m, bool resid
   } else if (k > 4096 || ceil_div(m, 256) * ceil_div(n, 256) > 224) {
     return false;
   }
+  if (m > 128 && !residual && gemm_stream_f16_whole_rounds(n, k, m)) return false;
   const bool short_k = m > 320 && k <= 256 && !residual, long_k = m > 64 && k > 7000;
   if (!short_k && !long_k && size <= 70000000) return true;
   const F16TilePick pick = gemm_f16_tiles_pick(n, k, m, linear_workspace_bytes(dtype, n, k, m));
   const int64_t rounds = ceil_div(pick.items, 256);
   const float fill = (float)pick.items / (float)(rounds * 256);
   if (short_k && rounds >= 2) return false;
-  if (m > 64 && m <= 96 && k > 8192 && (fill < 0.75f || (k > 20000 && !gemm_f16w_pick_cols(n, k, m)))) return false;
+  if (m > 64 && m <= 96 && k > 8192 &&
+      (fill <= 0.75f || (k > 20000 ? !gemm_f16w_pick_cols(n, k, m) : pick.splits > 1 && rounds > 1)))
+    return false;
   if (m > 96 && k > 7000 && size > 60000000 && fill < 0.55f) return false;
   if (m > 128 && rounds >= 3 && size > 70000000) return m <= 320 ? residual : pick.us < 0.94f * gemm_stream_f16_us(n, k, m);
   return true;

@@ -2230,13 +2230,18 @@ size_t gemm_stream_workspace(int64_t n, int64_t k, int64_t m) {
   return (size_t)sh.grid() * 2 * rows * kBN * sizeof(float);
 }
 
+bool gemm_stream_f16_whole_rounds(int64_t n, int64_t k, int64_t m) {
+  const Shape sh = pick_shape(m, FG_F16, n, k);
+  return (sh.nw == 8 || sh.mt == kMaxMT) && ceil_div(m, sh.rows()) * ceil_div(n, kBN) % sh.grid() == 0;
+}
 // Whole rounds of 256 workgroups, and a rest that is cut along the contraction, in blocks of 256 or 192 rows.  Fitted to 110
 // measured matrices of 70 to 210 M elements without a residual, 321 to 2048 rows: off by 4 % (one standard deviation).
 float gemm_stream_f16_us(int64_t n, int64_t k, int64_t m) {
-  const bool tall = pick_shape(m, FG_F16, n, k).mt == 8;
-  const int64_t tiles = ceil_div(m, tall ? 256 : 192) * ceil_div(n, kBN), whole = tiles / 256, steps = k / kKS;
-  const float rest = (float)(tiles - whole * 256) / 256.f;
-  return tall ? 47.6f + (float)steps * (1.673f * (float)whole + 2.25f * rest) : 31.7f + (float)steps * (1.371f * (float)whole + 1.885f * rest);
+  const Shape sh = pick_shape(m, FG_F16, n, k);
+  const bool tall = sh.mt == 8;
+  const int64_t tiles = ceil_div(m, sh.rows()) * ceil_div(n, kBN), steps = k / kKS;
+  const float whole = (float)(tiles / 256), rest = (float)(tiles % 256) / 256.f;
+  return tall ? 47.6f + (float)steps * (1.673f * whole + 2.25f * rest) : 31.7f + (float)steps * (1.371f * whole + 1.885f * rest);
 }
 
 int gemm_stream_launch(const LinearArgs& la, void* ws, size_t ws_bytes, hipStream_t stream) {
