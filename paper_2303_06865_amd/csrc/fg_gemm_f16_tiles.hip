@@ -351,11 +351,13 @@ F16TilePick gemm_f16_tiles_pick(int64_t n, int64_t k, int64_t m, size_t ws_bytes
 //   1.52, 6000 x 2048 x 2048 1.36, 18432 x 768 x 768 1.53, 3000 x 4096 x 4096 1.36, but 4096 x 4096 x 4096 0.94, 9000 x 2048 x 2048
 //   0.90, 6000 x 2048 x 8192 0.98).
 // Not within these lines (measured over 2500 shapes, this kernel's time over the other's):
-//   65 to 96 rows, contractions beyond 8192, where the tiles leave a quarter of the chip and more without work (the copies of those
-//   that there are don't take what HBM gives): 92 x 8352 x 13312 1.30, 70 x 8576 x 23744 1.23, 82 x 4256 x 17536 1.21, 80 x 12288 x
-//   12288 1.05, but 80 x 4096 x 10560 0.85, 85 x 7168 x 16768 0.94; or where ranges make several rounds: 80 x 12288 x 16384 1.06.  Beyond 20000 wherever the narrow tiles don't take the call: 72 x
-//   5504 x 28928 1.13, 94 x 8128 x 22336 1.03, but 69 x 4864 x 28480 0.85.  More rows, matrices of more than 60 M, where nearly half
-//   of the chip has no work: 97 x 4256 x 24320 1.22, 224 x 16448 x 9984 1.09, 225 x 16480 x 7936 1.08.
+//   65 to 96 rows, contractions beyond 8192 of matrices of more than 58 M, where tiles of up to 96 x 64 leave a quarter of the
+//   chip and more without work, larger ones a third (the copies of those that there are don't take what HBM gives): 92 x 8352
+//   x 13312 1.30, 70 x 8576 x 23744 1.23, 82 x 4256 x 17536 1.21, 80 x 12288 x 12288 1.05, but 89 x 6016 x 9408 (57 M) 0.90,
+//   80 x 4096 x 10560 0.85, 85 x 7168 x 16768 0.94, 89 x 5760 x 20928 (128 x 128) 0.80; or where ranges of the small ones make
+//   several rounds: 80 x 12288 x 16384 1.06, and beyond 20000 wherever the narrow tiles don't take the call: 72 x 5504 x 28928
+//   1.13, 94 x 8128 x 22336 1.03, but 69 x 4864 x 28480 0.85.  97 to 128 rows, matrices of more than 80 M, where nearly half
+//   of the chip has no work: 97 x 4256 x 24320 1.22, 108 x 8576 x 10176 1.07.
 //   Contractions of up to 256 in more than one round, without a residual: a workgroup is its start and its epilogue, and the other
 //   kernel's stay on: 1089 x 27488 x 64 2.05, 343 x 36896 x 192 1.32, 800 x 15328 x 128 1.08, 1247 x 8640 x 64 0.97.
 //   Sizes that fill whole rounds of the other kernel, 256 tiles each, without a residual: of 256 x 256 1000 x 16384 x 320 1.29, x 1024
@@ -376,16 +378,18 @@ bool gemm_f16_tiles_takes(int dtype, int64_t n, int64_t k, int64_t m, bool resid
     return false;
   }
   if (m > 128 && !residual && gemm_stream_f16_whole_rounds(n, k, m)) return false;
-  const bool short_k = m > 320 && k <= 256 && !residual, long_k = m > 64 && k > 7000;
+  const bool short_k = m > 320 && k <= 256 && !residual, long_k = m > 64 && m <= 128 && k > 8192;
   if (!short_k && !long_k && size <= 70000000) return true;
   const F16TilePick pick = gemm_f16_tiles_pick(n, k, m, linear_workspace_bytes(dtype, n, k, m));
   const int64_t rounds = ceil_div(pick.items, 256);
   const float fill = (float)pick.items / (float)(rounds * 256);
   if (short_k && rounds >= 2) return false;
-  if (m > 64 && m <= 96 && k > 8192 &&
-      (fill <= 0.75f || (k > 20000 ? !gemm_f16w_pick_cols(n, k, m) : pick.splits > 1 && rounds > 1)))
-    return false;
-  if (m > 96 && k > 7000 && size > 60000000 && fill < 0.55f) return false;
+  if (m > 64 && m <= 96 && k > 8192 && size > 58000000) {
+    const bool small = pick.mt * pick.nt <= 6;   // up to 96 x 64
+    if (fill <= (small ? 0.75f : 0.65f)) return false;
+    if (small && (k > 20000 ? !gemm_f16w_pick_cols(n, k, m) : pick.splits > 1 && rounds > 1)) return false;
+  }
+  if (m > 96 && m <= 128 && k > 8192 && size > 80000000 && fill < 0.55f) return false;
   if (m > 128 && rounds >= 3 && size > 70000000) return m <= 320 ? residual : pick.us < 0.94f * gemm_stream_f16_us(n, k, m);
   return true;
 }
